@@ -166,7 +166,6 @@ gwq_status gwq_pack(const void *W_f16, const void *score, int32_t score_dtype, g
     if (((uintptr_t)workspace & 3) || ((uintptr_t)W_f16 & 15) || ((uintptr_t)score & 15)) return GWQ_ERR_SHAPE;
     hipError_t e = gwq::launch_pack(W_f16, score, score_dtype == GWQ_SCORE_F16, *dst,
                                     static_cast<uint32_t *>(workspace), g_pack_full != 0, static_cast<hipStream_t>(stream));
-    if (e == hipSuccess && dst->index) e = gwq::launch_gemm_index(*dst, dst->index, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? GWQ_OK : GWQ_ERR_DEVICE;
 }
 

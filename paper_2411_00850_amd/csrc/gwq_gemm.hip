@@ -50,15 +50,8 @@ constexpr int kLd = kBK + 8;            // LDS row stride in halves: 144 bytes, 
 constexpr int kAhead = 8;               // outlier entries per (channel, group) fetched ahead
 
 // ------------------------------------------------------------------------------------------------
-// Per (channel, group) record for the GEMM's producers: the CSR index of the group's first outlier
-// and the group's scale and zero point, so that one 8-byte load fetches everything a group needs
-// besides its codes.  gpr + 1 records per channel; the last one holds the channel's end index.
-// One wave per channel.
-struct GroupRecord {
-    int32_t first;
-    uint32_t scale_zero;                                // scale bits | zero point << 16
-};
-
+// Fills the records of an index (GroupRecord, gwq_internal.h) from a packed layer; gwq_pack writes them itself.
+// gpr + 1 records per channel, one wave per channel.
 __global__ __launch_bounds__(256) void group_index_kernel(const int32_t *__restrict__ row_ptr,
                                                           const uint16_t *__restrict__ col_idx,
                                                           const uint16_t *__restrict__ scales,
@@ -97,9 +90,6 @@ __global__ __launch_bounds__(256) void group_index_kernel(const int32_t *__restr
     for (int i = 0; i < 8; ++i) {
         const int g = 8 * lane + i;
         if (g < gpr) {
-            // The GEMM multiplies FP16 operands s * (q - z): a scale is capped at the largest FP16 value whose
-            // product with 2^bits - 1 is still finite (only ranges beyond 65460 reach it; positive FP16
-            // patterns order like integers).
             const uint32_t sc = scales ? scales[row_group + g] : 0u, zp = scales ? zeros[row_group + g] : 0u;
             out[g] = GroupRecord{(int32_t)first, (sc < scale_cap ? sc : scale_cap) | zp << 16};
         }
@@ -593,7 +583,6 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restr
 // kCUs is the compute-unit count of the MI355X, which the scratch size reported by gwq_layout (a pure host
 // call) is based on; a launch plans with the current device's count, never beyond kCUs.
 constexpr int kMaxSplits = 8, kSplitBelowTiles = 160, kCUs = 256;
-size_t record_bytes(int64_t N, int64_t K) { return ((size_t)(N * (K / kGroup + 1)) * sizeof(GroupRecord) + 255) / 256 * 256; }
 int launch_cus()
 {
     const int n = device_cus();
@@ -675,7 +664,7 @@ hipError_t launch_ms(const gwq_packed &P, const void *X, int M, void *Y, const G
         if (e != hipSuccess) return e;
     }
     // The half-slot pairs of a layer with small groups follow the records.
-    const uint32_t *fine = reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(rec) + record_bytes(P.N, P.K));
+    const uint32_t *fine = reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(rec) + index_record_bytes(P.N, P.K));
     gemm_kernel<BITS, MSW, WN, WM, FINE, BF16><<<tiles_m * tiles_n * splits, kThreads, lds, st>>>(
         P.qweight, P.col_idx, P.out_val, rec, fine, static_cast<const _Float16 *>(X),
         static_cast<_Float16 *>(Y), partial, split_groups, P.N, P.K, M, tiles_m, tiles_n,
@@ -692,7 +681,7 @@ hipError_t launch_ms(const gwq_packed &P, const void *X, int M, void *Y, const G
 
 size_t gemm_index_bytes(int64_t N, int64_t K, int group)
 {
-    return record_bytes(N, K) + (group < kGroup ? ((size_t)N * (K / 16) * 4 + 255) / 256 * 256 : 0);
+    return index_record_bytes(N, K) + (group < kGroup ? ((size_t)N * (K / 16) * 4 + 255) / 256 * 256 : 0);
 }
 
 // Scratch for the FP32 partial sums of a K-split launch with up to M_max rows.  Splitting stops
@@ -707,8 +696,7 @@ size_t gemm_scratch_bytes(int64_t N, int64_t M_max)
 
 hipError_t launch_gemm_index(const gwq_packed &P, void *workspace, hipStream_t st)
 {
-    // 4364 * 15 = 65460 and 9352 * 7 = 65464: the last scales on the FP16 grid that keep s * (q - z) finite.
-    const uint32_t scale_cap = P.bits == 4 ? 0x6C43u : 0x7091u;
+    const uint32_t scale_cap = index_scale_cap(P.bits);
     if (P.group == kGroup) {
         group_index_kernel<<<(P.N + 3) / 4, 256, 0, st>>>(P.row_ptr, P.col_idx, P.scales, P.zeros, P.N, P.K / kGroup,
                                                          scale_cap, static_cast<GroupRecord *>(workspace));
@@ -720,7 +708,7 @@ hipError_t launch_gemm_index(const gwq_packed &P, void *workspace, hipStream_t s
     const size_t count = (size_t)P.N * (P.K / 16);
     fine_index_kernel<<<(unsigned)((count + 255) / 256), 256, 0, st>>>(
         P.scales, P.zeros, count, P.K, P.group, scale_cap,
-        reinterpret_cast<uint32_t *>(static_cast<char *>(workspace) + record_bytes(P.N, P.K)));
+        reinterpret_cast<uint32_t *>(static_cast<char *>(workspace) + index_record_bytes(P.N, P.K)));
     return hipGetLastError();
 }
 

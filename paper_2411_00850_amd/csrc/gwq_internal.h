@@ -22,6 +22,21 @@ int device_cus();
 // record (bit d: done on device d); the HIP call is idempotent, so a race between threads is harmless.
 hipError_t allow_dynamic_lds(const void *kernel, int bytes, std::atomic<uint32_t> &done);
 
+// ---- The layer's index (gwq_packed.index) -----------------------------------------------------
+// One record per (channel, block of 128 codes) for the GEMM's producers - the CSR index of the block's first outlier, and
+// the block's scale and zero point, so that one 8-byte load fetches everything a block needs besides its codes - and one
+// more per channel that holds the channel's end.  For groups below 128 the records carry no scale, and behind them (at
+// index_record_bytes) lie eight words scale bits | zero point << 16 per channel and block, one per 16 columns.
+struct GroupRecord {
+    int32_t first;
+    uint32_t scale_zero;                                // scale bits | zero point << 16
+};
+inline size_t index_record_bytes(int64_t N, int64_t K) { return ((size_t)(N * (K / kGroup + 1)) * sizeof(GroupRecord) + 255) / 256 * 256; }
+// The GEMM multiplies FP16 operands s * (q - z): in the index a scale is capped at the largest FP16 value whose product
+// with 2^bits - 1 is still finite (4364 * 15 = 65460, 9352 * 7 = 65464; only ranges beyond 65460 reach it; positive FP16
+// patterns order like integers).
+__host__ __device__ constexpr uint32_t index_scale_cap(int bits) { return bits == 4 ? 0x6C43u : 0x7091u; }
+
 // ---- gwq_pack workspace: uint32 words -------------------------------------------------------
 // [0, 3*kSelBins)        histograms of the three radix-select passes
 // kWsPrefix              key bits fixed by the passes done so far

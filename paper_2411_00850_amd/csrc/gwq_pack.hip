@@ -2,8 +2,8 @@
 // bit patterns of |score|, CSR build in flat-index order, then per (row, group of 16 to 128) the scale,
 // zero point and codes of Eq. 6, 7 and 9 and the word layout documented in gwq.h.
 //
-// Everything is integer work or exactly specified IEEE arithmetic (fp64 division, round half to
-// even), so the output is a function of the inputs alone.  Integer atomics are used for the
+// Everything is integer work or arithmetic whose result is that of exact arithmetic rounded once (see the encoder),
+// so the output is a function of the inputs alone.  Integer atomics are used for the
 // histograms (order-independent); there are no floating-point atomics.
 #include "gwq_internal.h"
 
@@ -313,7 +313,7 @@ __global__ __launch_bounds__(kThreads) void row_scan_kernel(uint32_t *ws, int N,
             s_eq[l] = n < N ? ws[kWsRows + N + n] : 0u;
         }
         __syncthreads();
-        const int local = threadIdx.x * kRowsPerThread, base = n0 + local;
+        const int local = threadIdx.x * kRowsPerThread;
         uint32_t gt[kRowsPerThread], eq[kRowsPerThread], eq_sum = 0;
 #pragma unroll
         for (int i = 0; i < kRowsPerThread; ++i) {
@@ -350,161 +350,267 @@ __global__ __launch_bounds__(kThreads) void row_scan_kernel(uint32_t *ws, int N,
     if (threadIdx.x == 0) row_ptr[N] = (int32_t)kept_before;
 }
 
-__device__ inline double half_bits_to_double(uint16_t h)
+// ---- the encoder ---------------------------------------------------------------------------------
+//
+// One wave walks a row (or, where there are few rows, one of four consecutive parts of it) in flat-index order, 512
+// weights per trip, eight per lane: it marks the kept entries, appends them to the CSR arrays, and quantises and packs the
+// rest.  No barrier and no LDS: positions come from the compare masks (mbcnt), a group's 2 to 16 lanes meet by DPP, the
+// 3-bit words are put together across a quad of lanes.  The next trip's weights and scores are requested before this
+// trip's are worked on.
+//
+// Bound by HBM (6.56 bytes per weight at FP32 scores), which needs the instruction stream short: about 300 vector
+// instructions per trip and wave.  A kept weight is replaced by 0: a group's range always contains 0 and 0 gets the code
+// z, so masking it once serves the range and the code.  The quotient w / s is one reciprocal per group and three
+// instructions per weight (see quotient).
+//
+// Measured, 11008 x 4096 and 4096 x 11008, 4 bits, FP32 scores, with the layer's index: 53 us = 5.7 TB/s (a block of four
+// waves per row with a barrier per 2048 weights, IEEE divisions and fp64 scales took 88 .. 92 us, and 7 .. 12 us more for a
+// kernel that wrote the index).
+
+// w / s for an FP16 number w and the FP16 scale s (r: its reciprocal to 1 ulp): the product with r is within 2^-22 of the
+// quotient, its residual w - t s has at most 13 significant bits and is exact, and the correction leaves an error below
+// 2^-44 before the last rounding.  What follows rounds to an integer, half to even: a quotient that is exactly a
+// half-integer is representable and comes out exactly; any other (mw 2^a / ms 2^b with 11-bit mw, ms) is at least
+// 1 / (4 ms) >= 2^-13 away from one while below 2^6 in magnitude, and larger ones are clamped to the same end whatever
+// their rounding.  So the code is the one that exact arithmetic gives.
+__device__ inline float quotient(float w, float s, float r)
 {
-    return (double)(float)__builtin_bit_cast(_Float16, h);
+    const float t = w * r;
+    return __builtin_fmaf(__builtin_fmaf(-t, s, w), r, t);
 }
 
-// Eq. 6 / Eq. 7 for one group from its masked min and max (both already widened to contain 0).
-template <int BITS> __device__ inline void scale_and_zero(float mn, float mx, uint16_t &s_bits, int &z)
+__device__ inline float half_bits_to_float(uint32_t h) { return (float)__builtin_bit_cast(_Float16, (uint16_t)h); }
+
+// Eq. 6 / Eq. 7 for one group from its masked min and max (both already widened to contain 0): the smallest FP16 s with
+// s * maxq >= mx - mn, and z = clamp(rint(-mn / s), 0, maxq).  The range is held exactly as d + err (two-sum), products
+// s * maxq are exact in FP32, so comparing them is exact.  The guess RN(d / maxq) is the wanted s or its neighbour.
+template <int BITS> __device__ inline void scale_and_zero(float mn, float mx, uint32_t &s_bits, float &s, float &r, float &z)
 {
-    constexpr int maxq = (1 << BITS) - 1;
-    const double R = (double)mx - (double)mn;
-    if (R == 0.0) { s_bits = 0x3C00; z = 0; return; }
-    // First guess near R/maxq, then walk to the smallest FP16 s with s*maxq >= R; the walk makes
-    // the result independent of how the guess was rounded.
-    uint16_t sb = __builtin_bit_cast(uint16_t, (_Float16)(float)(R / maxq));
-    if (sb == 0) sb = 1;
-    while (sb < 0x7BFF && half_bits_to_double(sb) * maxq < R) ++sb;
-    while (sb > 1 && half_bits_to_double((uint16_t)(sb - 1)) * maxq >= R) --sb;
-    const double zr = rint(-(double)mn / half_bits_to_double(sb));
-    z = !(zr > 0.0) ? 0 : (zr > maxq ? maxq : (int)zr);
+    constexpr float maxq = (float)((1 << BITS) - 1);
+    const float d = mx - mn, bb = d - mx, err = (mx - (d - bb)) + (-mn - bb);
+    auto covers = [&](uint32_t sb) {
+        const float top = half_bits_to_float(sb) * maxq;
+        return top > d || (top == d && err <= 0.f);
+    };
+    uint32_t sb = __builtin_bit_cast(uint16_t, (_Float16)(d * (1.f / maxq)));
+    sb = sb == 0 ? 1 : sb;
+    sb = sb < 0x7BFFu && !covers(sb) ? sb + 1 : sb;
+    sb = sb > 1 && covers(sb - 1) ? sb - 1 : sb;
+    if (d == 0.f) sb = 0x3C00u;                         // an empty range: s = 1 and, as -mn / 1 = 0, z = 0
     s_bits = sb;
+    s = half_bits_to_float(sb);
+    r = __builtin_amdgcn_rcpf(s);
+    z = rintf(__builtin_amdgcn_fmed3f(quotient(-mn, s, r), 0.f, maxq));     // (a NaN gives the lower end)
 }
 
-// One block per output channel n.  Walks the row in flat-index order: marks the kept entries,
-// appends them to the CSR arrays, and quantises each group (16 to 128 weights: 2 to 16 consecutive threads) and packs each block of 128 codes.
-template <int BITS, bool F16>
-__global__ __launch_bounds__(kThreads) void encode_kernel(const uint16_t *__restrict__ W,
-                                                          const void *__restrict__ score, int N, int K,
-                                                          int group, const uint32_t *__restrict__ ws,
-                                                          const int32_t *__restrict__ row_ptr,
-                                                          uint32_t *__restrict__ qweight,
-                                                          uint16_t *__restrict__ scales,
-                                                          uint8_t *__restrict__ zeros,
-                                                          uint16_t *__restrict__ col_idx,
-                                                          uint16_t *__restrict__ out_val)
+template <int CTRL> __device__ inline float dpp_f32(float v)
 {
-    constexpr int maxq = (1 << BITS) - 1;
-    constexpr int wpg = words_per_group(BITS);
-    __shared__ uint32_t smem[kWaves];
-    __shared__ uint8_t code_lds[BITS == 3 ? kElemsPerIter : 8];
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+}
+template <int CTRL> __device__ inline uint32_t dpp_u32(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
+}
+// DPP controls: lanes exchange within pairs, within quads, halves of eight and of sixteen are mirrored, a row rotates.
+constexpr int kDppPair = 0xB1, kDppQuad = 0x4E, kDppHalfMirror = 0x141, kDppMirror = 0x140, kDppRor4 = 0x124, kDppRor8 = 0x128;
 
-    const int n = blockIdx.x, tid = threadIdx.x;
-    const int gpr = K / kGroup;
-    const int spr = K / group, lanes = group / 8;       // scale groups per row; threads that share one
-    const uint32_t thr = ws[kWsPrefix];
-    const uint32_t take = ws[kWsRows + 2 * N + n];
-    uint32_t ties_seen = 0, gt_seen = 0;                // of the chunks before the current one
-    const uint32_t out_pos = (uint32_t)row_ptr[n];
+// Lanes below this one whose bit is set, added to `base`.
+__device__ inline uint32_t count_below(uint64_t mask, uint32_t base)
+{
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, base));
+}
 
-    for (int k0 = 0; k0 < K; k0 += kElemsPerIter) {
-        const int k = k0 + tid * 8;
-        const bool active = k < K;          // a group is 16 consecutive threads: all or none active
-        uint16_t w[8];
-        uint32_t key[8];
-        uint32_t gt_mask = 0, eq_mask = 0;
-        if (active) {
-            const uint4 v = *reinterpret_cast<const uint4 *>(W + (size_t)n * K + k);
-            const uint32_t vw[4] = {v.x, v.y, v.z, v.w};
+// What a lane holds of one trip: eight weights and their scores as they lie in memory.
+template <bool F16> struct EncodeRegs {
+    uint4 w, s[F16 ? 1 : 2];
+    __device__ inline void load(const uint16_t *W, const void *score, size_t idx)
+    {
+        w = *reinterpret_cast<const uint4 *>(W + idx);
+        if (F16) {
+            s[0] = *reinterpret_cast<const uint4 *>(static_cast<const uint16_t *>(score) + idx);
+        } else {
+            const uint4 *p = reinterpret_cast<const uint4 *>(static_cast<const uint32_t *>(score) + idx);
+            s[0] = p[0];
+            s[F16 ? 0 : 1] = p[1];
+        }
+    }
+    __device__ inline void keys(uint32_t key[8]) const
+    {
+        if (F16) {
+            const uint32_t v[4] = {s[0].x, s[0].y, s[0].z, s[0].w};
 #pragma unroll
-            for (int i = 0; i < 4; ++i) { w[2 * i] = (uint16_t)(vw[i] & 0xFFFF); w[2 * i + 1] = (uint16_t)(vw[i] >> 16); }
-            load_keys8<F16>(score, (size_t)n * K + k, key);
+            for (int i = 0; i < 4; ++i) {
+                key[2 * i] = key_from_f16((uint16_t)(v[i] & 0xFFFF));
+                key[2 * i + 1] = key_from_f16((uint16_t)(v[i] >> 16));
+            }
+        } else {
+            const uint4 &b = s[F16 ? 0 : 1];
+            key[0] = key_from_f32(s[0].x); key[1] = key_from_f32(s[0].y); key[2] = key_from_f32(s[0].z); key[3] = key_from_f32(s[0].w);
+            key[4] = key_from_f32(b.x); key[5] = key_from_f32(b.y); key[6] = key_from_f32(b.z); key[7] = key_from_f32(b.w);
+        }
+    }
+};
+
+constexpr int kTrip = 512;                              // weights per wave and trip
+
+// STEPS: log2 of the lanes that share a group (group = 16, 32, 64, 128: 1 to 4).  parts: waves per row, 1 or 4.
+// rec, fine: the layer's index (gwq_internal.h), or NULL.
+template <int BITS, bool F16, int STEPS>
+__global__ __launch_bounds__(kThreads) void encode_kernel(const uint16_t *__restrict__ W, const void *__restrict__ score, int N, int K,
+                                                          int parts, const uint32_t *__restrict__ ws,
+                                                          const int32_t *__restrict__ row_ptr, uint32_t *__restrict__ qweight,
+                                                          uint16_t *__restrict__ scales, uint8_t *__restrict__ zeros,
+                                                          uint16_t *__restrict__ col_idx, uint16_t *__restrict__ out_val,
+                                                          GroupRecord *__restrict__ rec, uint32_t *__restrict__ fine)
+{
+    constexpr int group = 8 << STEPS;
+    constexpr int wpg = words_per_group(BITS);
+    constexpr float maxq = (float)((1 << BITS) - 1);
+    constexpr uint32_t cap = index_scale_cap(BITS);
+    __shared__ uint32_t part_gt[kWaves], part_eq[kWaves];
+
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int n = parts == 1 ? (int)blockIdx.x * kWaves + wave : (int)blockIdx.x;
+    if (n >= N) return;                                 // whole waves, and only where nobody waits for them (parts = 1)
+    const int trips = (K + kTrip - 1) / kTrip, per_part = (trips + parts - 1) / parts;
+    const int t_begin = parts == 1 ? 0 : wave * per_part;
+    const int t_end = t_begin + per_part < trips ? t_begin + per_part : trips;
+    const size_t row = (size_t)n * K;
+    const uint32_t thr = ws[kWsPrefix];
+    const uint32_t take = ws[kWsRows + 2 * N + n];      // of the row's keys equal to the threshold the first `take` are kept
+    const int gpr = K / kGroup, spr = K / group;
+    uint32_t pos = (uint32_t)row_ptr[n], ties_seen = 0;
+    if (rec && lane == 0 && t_begin == 0) rec[(size_t)n * (gpr + 1) + gpr] = GroupRecord{row_ptr[n + 1], 0u};
+
+    // Lanes beyond the end of the row (whole groups of lanes) repeat its last weights and keep nothing.
+    auto column = [&](int t) { return t * kTrip + lane * 8; };
+    auto request = [&](int t, EncodeRegs<F16> &R) {
+        const int k = column(t < t_end ? t : t_end - 1);
+        R.load(W, score, row + (k < K ? k : K - 8));
+    };
+    EncodeRegs<F16> next;
+    if (t_begin < t_end) request(t_begin, next);
+
+    if (parts > 1) {                                    // what the parts before this one keep
+        uint32_t gt = 0, eq = 0;
+        for (int t = t_begin; t < t_end; ++t) {
+            EncodeRegs<F16> R;
+            request(t, R);
+            uint32_t key[8];
+            R.keys(key);
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                gt_mask |= (uint32_t)(key[i] > thr) << i;
-                eq_mask |= (uint32_t)(key[i] == thr) << i;
+                gt += column(t) < K && key[i] > thr;
+                eq += column(t) < K && key[i] == thr;
             }
-        } else {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) w[i] = 0;
         }
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) { gt += __shfl_xor(gt, d); eq += __shfl_xor(eq, d); }
+        if (lane == 0) { part_gt[wave] = gt; part_eq[wave] = eq; }
+        __syncthreads();
+        for (int w = 0; w < wave; ++w) { pos += part_gt[w]; ties_seen += part_eq[w]; }
+        pos += ties_seen < take ? ties_seen : take;
+    }
 
-        // One scan for both counts (each at most 2048 per chunk: 16 bits apiece): the keys above the
-        // threshold and the threshold ties before this thread, in flat-index order.  The first `take`
-        // ties of the row are kept, so of the ties before this thread min(their number, take) are, and
-        // the thread's first kept entry goes behind those and the larger keys before it.
-        uint32_t both_total;
-        const uint32_t both = block_exclusive_scan((uint32_t)__popc(gt_mask) | (uint32_t)__popc(eq_mask) << 16, smem, both_total);
-        const uint32_t tie_rank = ties_seen + (both >> 16);
-        uint32_t sel_mask = gt_mask;
+    for (int t = t_begin; t < t_end; ++t) {
+        const EncodeRegs<F16> R = next;
+        request(t + 1, next);
+        const int k = column(t);
+        const bool active = k < K;
+        const uint32_t vw[4] = {R.w.x, R.w.y, R.w.z, R.w.w};
+        bool keep[8];
         {
-            uint32_t r = tie_rank;
+            uint32_t key[8];
+            R.keys(key);
+            if (take == 0) {                            // uniform over the wave; nearly every row
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
-                if (eq_mask >> i & 1) { if (r < take) sel_mask |= 1u << i; ++r; }
-        }
-        uint32_t pos = out_pos + gt_seen + (both & 0xFFFFu) + (tie_rank < take ? tie_rank : take);
+                for (int i = 0; i < 8; ++i) keep[i] = active && key[i] > thr;
+            } else {
+                uint32_t rank = ties_seen;
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
-            if (sel_mask >> i & 1) { col_idx[pos] = (uint16_t)(k + i); out_val[pos] = w[i]; ++pos; }
-        ties_seen += both_total >> 16;
-        gt_seen += both_total & 0xFFFFu;
-
-        // Masked min / max of the group (range always contains 0), reduced over the group's 2 to 16 lanes.
-        float mn = 0.f, mx = 0.f;
+                for (int i = 0; i < 8; ++i) {
+                    const uint64_t m = __ballot(active && key[i] == thr);
+                    rank = count_below(m, rank);
+                    ties_seen += (uint32_t)__builtin_popcountll(m);
+                }
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
-            if (!(sel_mask >> i & 1)) {
-                const float v = (float)__builtin_bit_cast(_Float16, w[i]);
-                mn = v < mn ? v : mn;
-                mx = v > mx ? v : mx;
+                for (int i = 0; i < 8; ++i) {
+                    const bool tie = active && key[i] == thr;
+                    keep[i] = (active && key[i] > thr) || (tie && rank < take);
+                    rank += tie;
+                }
             }
-#pragma unroll
-        for (int d = 1; d < 16; d <<= 1) {
-            const float a = __shfl_xor(mn, d), b = __shfl_xor(mx, d);
-            mn = d < lanes && a < mn ? a : mn;
-            mx = d < lanes && b > mx ? b : mx;
         }
-        uint16_t s_bits;
-        int z;
-        scale_and_zero<BITS>(mn, mx, s_bits, z);
-
-        // Eq. 9 per weight; an outlier takes the code z.  The quotient is taken in FP32 (a correctly
-        // rounded division, as the oracle's is in fp64): for FP16 operands w = mw 2^a and s = ms 2^b with
-        // 11-bit mw, ms the exact quotient is either a half-integer, which FP32 holds exactly, or at
-        // least 1 / (4 ms) >= 2^-13 away from one while below 2^6 in magnitude, far more than the 2^-18
-        // an FP32 rounding can move it: both precisions round to the same integer.  Quotients too large
-        // for that argument are clamped to 0 or maxq either way.
-        const float s32 = (float)__builtin_bit_cast(_Float16, s_bits);
-        uint32_t code[8];
+        uint32_t at = pos;                              // CSR position of this lane's first kept entry
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            const float qr = rintf((float)__builtin_bit_cast(_Float16, w[i]) / s32) + (float)z;
-            const int q = !(qr > 0.f) ? 0 : (qr > (float)maxq ? maxq : (int)qr);
-            code[i] = (sel_mask >> i & 1) ? (uint32_t)z : (uint32_t)q;
+            const uint64_t m = __ballot(keep[i]);
+            at = count_below(m, at);
+            pos += (uint32_t)__builtin_popcountll(m);
+        }
+        const uint32_t first = at;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (keep[i]) {
+                col_idx[at] = (uint16_t)(k + i);
+                out_val[at] = (uint16_t)(i & 1 ? vw[i >> 1] >> 16 : vw[i >> 1] & 0xFFFFu);
+                ++at;
+            }
+
+        float w[8], mn = 0.f, mx = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) w[i] = keep[i] || !active ? 0.f : half_bits_to_float(i & 1 ? vw[i >> 1] >> 16 : vw[i >> 1] & 0xFFFFu);
+#pragma unroll
+        for (int i = 0; i < 8; i += 2) {
+            mn = __builtin_fminf(__builtin_fminf(w[i], w[i + 1]), mn);      // a NaN loses against a number
+            mx = __builtin_fmaxf(__builtin_fmaxf(w[i], w[i + 1]), mx);
+        }
+        mn = __builtin_fminf(mn, dpp_f32<kDppPair>(mn)); mx = __builtin_fmaxf(mx, dpp_f32<kDppPair>(mx));
+        if (STEPS > 1) { mn = __builtin_fminf(mn, dpp_f32<kDppQuad>(mn)); mx = __builtin_fmaxf(mx, dpp_f32<kDppQuad>(mx)); }
+        if (STEPS > 2) { mn = __builtin_fminf(mn, dpp_f32<kDppHalfMirror>(mn)); mx = __builtin_fmaxf(mx, dpp_f32<kDppHalfMirror>(mx)); }
+        if (STEPS > 3) { mn = __builtin_fminf(mn, dpp_f32<kDppMirror>(mn)); mx = __builtin_fmaxf(mx, dpp_f32<kDppMirror>(mx)); }
+        uint32_t s_bits;
+        float s, r, zf;
+        scale_and_zero<BITS>(mn, mx, s_bits, s, r, zf);
+        const uint32_t z = (uint32_t)(int)zf;
+
+        // Eq. 9: rint(w / s) by adding 1.5 * 2^23 (an even number: halves go to even); its low bits, shifted to their
+        // places and summed, carry a known multiple of that number's pattern, taken off with z added for all eight at once.
+        // Even positions in the low half-word, odd ones in the high half-word, `BITS` bits apiece.
+        constexpr uint32_t ones = BITS == 4 ? 0x11111111u : 0x02490249u;
+        const float lo = -zf, hi = maxq - zf;
+        uint32_t codes = 0u - (0x4B400000u - z) * ones;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const float q = __builtin_amdgcn_fmed3f(quotient(w[i], s, r), lo, hi) + 12582912.f;
+            codes += __builtin_bit_cast(uint32_t, q) << (16 * (i & 1) + BITS * (i >> 1));
         }
 
-        const int g = k / kGroup;           // block of 128 codes within the row
-        const int j = tid & 15;             // this thread's 8 codes are k_local = 8j .. 8j+7
+        const size_t block = (size_t)n * gpr + (k >> 7);
         if (BITS == 4) {
-            uint32_t word = 0;
-#pragma unroll
-            for (int t = 0; t < 8; ++t) word |= code[t] << (16 * (t & 1) + 4 * (t >> 1));
-            if (active) qweight[((size_t)n * gpr + g) * wpg + j] = word;
+            if (active) qweight[block * wpg + (lane & 15)] = codes;
         } else {
-            __syncthreads();                // previous iteration's readers are done
-#pragma unroll
-            for (int t = 0; t < 8; ++t) code_lds[tid * 8 + t] = (uint8_t)code[t];
-            __syncthreads();
-            const uint8_t *c = code_lds + (tid >> 4) * kGroup;
-            if (active && j < 13) {
-                uint32_t word = 0;
-                if (j < 12) {
-                    const int base = 32 * (j / 3) + 10 * (j % 3);
-#pragma unroll
-                    for (int t = 0; t < 10; ++t) word |= (uint32_t)c[base + t] << (16 * (t & 1) + 3 * (t >> 1));
-                } else {
-#pragma unroll
-                    for (int b = 0; b < 4; ++b)
-                        word |= (uint32_t)c[32 * b + 30] << (3 * b) | (uint32_t)c[32 * b + 31] << (16 + 3 * b);
-                }
-                qweight[((size_t)n * gpr + g) * wpg + j] = word;
-            }
+            // A quad of lanes holds a slot: 16 codes of the even and 16 of the odd positions, 48 bits each.  Lane q < 3 of the
+            // quad makes word q of the slot (15 bits of each), lane 3 the slot's two codes of the tail word.
+            const uint32_t p0 = dpp_u32<0x00>(codes), p1 = dpp_u32<0x55>(codes), p2 = dpp_u32<0xAA>(codes), p3 = dpp_u32<0xFF>(codes);
+            auto stream = [&](int sh) {
+                return (uint64_t)((p0 >> sh & 0xFFFu) | (p1 >> sh & 0xFFFu) << 12) | (uint64_t)((p2 >> sh & 0xFFFu) | (p3 >> sh & 0xFFFu) << 12) << 24;
+            };
+            const int q = lane & 3, b = (lane >> 2) & 3;
+            const uint32_t even = (uint32_t)(stream(0) >> (15 * q)) & 0x7FFFu, odd = (uint32_t)(stream(16) >> (15 * q)) & 0x7FFFu;
+            uint32_t tail = q == 3 ? (even & 7u) << (3 * b) | (odd & 7u) << (16 + 3 * b) : 0u;
+            tail |= dpp_u32<kDppRor4>(tail);
+            tail |= dpp_u32<kDppRor8>(tail);
+            if (active && (q < 3 || b == 3)) qweight[block * wpg + 3 * b + q] = q < 3 ? even | odd << 16 : tail;
         }
-        if (active && (tid & (lanes - 1)) == 0) {
-            scales[(size_t)n * spr + k / group] = s_bits;
+        if (active && (lane & ((1 << STEPS) - 1)) == 0) {
+            scales[(size_t)n * spr + k / group] = (uint16_t)s_bits;
             zeros[(size_t)n * spr + k / group] = (uint8_t)z;
+        }
+        if (rec && active) {
+            const uint32_t pair = (s_bits < cap ? s_bits : cap) | z << 16;
+            if ((lane & 15) == 0) rec[(size_t)n * (gpr + 1) + (k >> 7)] = GroupRecord{(int32_t)first, STEPS == 4 ? pair : 0u};
+            if (STEPS < 4 && (lane & 1) == 0) fine[(size_t)n * (K / 16) + (k >> 4)] = pair;
         }
     }
 }
@@ -541,13 +647,28 @@ hipError_t run_select(const void *score, int N, int K, uint32_t *ws, int32_t *ro
     return hipGetLastError();
 }
 
+template <int BITS, bool F16, int STEPS>
+hipError_t run_encode(const void *W, const void *score, const gwq_packed &P, const uint32_t *ws, hipStream_t st)
+{
+    // A wave per row fills the chip from about a thousand rows on; below, four waves share a row (and count its parts
+    // first, which reads the scores once more).
+    const int parts = P.N < 1024 ? kWaves : 1;
+    const int blocks = parts == 1 ? (P.N + kWaves - 1) / kWaves : P.N;
+    GroupRecord *rec = static_cast<GroupRecord *>(P.index);
+    uint32_t *fine = rec ? reinterpret_cast<uint32_t *>(static_cast<char *>(P.index) + index_record_bytes(P.N, P.K)) : nullptr;
+    encode_kernel<BITS, F16, STEPS><<<blocks, kThreads, 0, st>>>(static_cast<const uint16_t *>(W), score, P.N, P.K, parts, ws, P.row_ptr,
+                                                                P.qweight, P.scales, P.zeros, P.col_idx, P.out_val, rec, fine);
+    return hipGetLastError();
+}
 template <int BITS, bool F16>
 hipError_t run_encode(const void *W, const void *score, const gwq_packed &P, const uint32_t *ws, hipStream_t st)
 {
-    encode_kernel<BITS, F16><<<P.N, kThreads, 0, st>>>(static_cast<const uint16_t *>(W), score, P.N, P.K, P.group, ws,
-                                                       P.row_ptr, P.qweight, P.scales, P.zeros, P.col_idx,
-                                                       P.out_val);
-    return hipGetLastError();
+    switch (P.group) {
+    case 16: return run_encode<BITS, F16, 1>(W, score, P, ws, st);
+    case 32: return run_encode<BITS, F16, 2>(W, score, P, ws, st);
+    case 64: return run_encode<BITS, F16, 3>(W, score, P, ws, st);
+    default: return run_encode<BITS, F16, 4>(W, score, P, ws, st);
+    }
 }
 
 }  // namespace

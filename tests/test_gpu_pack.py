@@ -295,3 +295,26 @@ def test_pack_7b_shape_both_ways(bits):
         gwq.tuning_set("pack_full_passes", 0)
     a, b = download_packed(D), download_packed(D2)
     assert all(np.array_equal(a[k], b[k]) for k in a)
+
+
+@pytest.mark.parametrize("bits", [4, 3])
+@pytest.mark.parametrize("N,K,group", [(3, 128, 128), (1, 640, 16), (1023, 2176, 64), (1024, 640, 128), (1030, 512, 32), (5, 4096, 128)])
+def test_pack_rows_and_index_at_the_encoders_edges(bits, N, K, group):
+    """The encoder at its edges: four waves per row (below 1024 rows) with fewer, as many and more trips of 512 weights
+    than waves, one wave per row, rows that end inside a trip; with ties at the threshold spread over many rows.  The
+    packed bytes are the oracle's, and the index it writes is the one gwq_linear_index makes of them."""
+    import torch
+    import paper_2411_00850_amd as gwq
+    from gpu_helpers import assert_packed_equal, to_gpu
+    rng = np.random.default_rng(N + K + group + bits)
+    W = gs.weight(N, K, rng, planted_cols=min(2, K // 64))
+    S = np.round(rng.random((N, K)) * 50).astype(np.float32)        # 51 values: about 2 % of the entries share the threshold
+    P = orc.pack(W, S, bits, 30000, group=group)
+    D = gwq.pack(to_gpu(W), to_gpu(S), bits, 30000, group=group)
+    assert_packed_equal(D, P)
+    used = N * (K // 128 + 1) * 8                                   # records; then, from the next multiple of 256, the pairs
+    want = gwq.linear_index(D)
+    assert torch.equal(D.index[:used], want[:used])
+    if group < 128:
+        at = (used + 255) // 256 * 256
+        assert torch.equal(D.index[at:at + N * (K // 16) * 4], want[at:at + N * (K // 16) * 4])
