@@ -5,7 +5,8 @@
 // and the entry point writes score = beta * score + alpha * g, so that the mean over calibration
 // samples (Sec. 4.3, ablation on the number of calibration samples) is a sequence of calls with alpha = 1 / samples.
 //
-// A dense contraction over the samples m with both operands stored m-major, bound by MFMA.  A block of
+// A dense contraction over the samples m with both operands stored m-major, bound by MFMA.  Two kernels: this one for
+// outputs too small to fill the chip with larger tiles, and score_big_kernel below.  A block of
 // four waves owns a 128 (n) x 128 (k) tile of the score and walks m in steps of 64; a wave owns 64 x 64
 // of it as 2 x 2 tiles of v_mfma_f32_32x32x16_f16 (FP32 accumulators, exact FP16 products).  The MFMA
 // wants, per lane, eight consecutive m of one n (or k), while memory has eight consecutive n of one m:
@@ -191,22 +192,280 @@ __global__ __launch_bounds__(kScoreThreads, N8 ? 2 : 1) void score_kernel(const 
         }
 }
 
+// ---- 256 x 256 tiles ------------------------------------------------------------------------------
+//
+// A 128 x 128 tile reads 512 bytes of operands per sample for 128 x 128 products: at the matrix cores' rate 64 bytes per
+// clock and CU, twice what the L2 delivers when all CUs ask.  This kernel's tile needs half of that.  Eight waves, two per
+// SIMD, own 128 (n) x 64 (k) each: 4 x 2 tiles of v_mfma_f32_32x32x16_f16.  Steps of 32 samples pass through a ring of four
+// LDS buffers, [operand][32 samples][256 columns] as the rows lie in memory, which loads with an LDS destination fill three
+// steps ahead, and the transposition the MFMA operands need is done by the LDS reads (ds_read_b64_tr_b16: of the sixteen
+// lanes of a group, lanes 4 j .. 4 j + 3 address sixteen columns of sample j, and lane i receives column i of samples
+// 0 .. 3), so the multiplying waves issue nothing but reads, MFMAs and a few requests.  The 16-byte units of a sample's row
+// are permuted by sample (unit u of sample m at u ^ 4 (m % 4)): the four samples of a read fall into different banks.
+// One barrier per step, in its middle: behind it the next step is staged and this one's operands are in registers.
+//
+// Measured at M = 2048 (128 x 128 tiles before): 4096 x 4096, one round of tiles, 72.6 us = 946 TFLOP/s (101.9 us);
+// 4096 x 11008 238 us (343), accumulating 262 us (381); with 3333 or 9001 channels 3.4 to 3.6 times as fast.  What is left at
+// 4096 x 11008: 688 tiles on 256 CUs are three rounds at 2.69 rounds' work, and 180 MB of FP32 scores (36 us at HBM speed)
+// are written at the rounds' ends.  Four waves of 128 x 128 (a third less LDS traffic, one wave per SIMD): 10 % slower.
+//
+// N8 = false: rows of dY are not 16-byte aligned.  Their pieces come through registers (loads at 2-byte alignment, requested
+// a step before they are stored); only the piece that would reach beyond the end of dY is read from 16 bytes before
+// the end and shifted (N >= 8).
+constexpr int kBig = 256, kBigStep = 32, kBigThreads = 512, kBigStages = 4;
+constexpr uint32_t kBigRow = kBig * 2, kBigOperand = kBigStep * kBigRow, kBigStage = 2 * kBigOperand;    // bytes
+constexpr size_t kBigLds = (size_t)kBigStages * kBigStage;                                               // 128 KB
+
+typedef short short4v __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4s __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) unsigned char lds_byte;
+
+template <int N> __device__ inline void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+
+template <bool N8>
+__global__ __launch_bounds__(kBigThreads) void score_big_kernel(const _Float16 *__restrict__ dY, const _Float16 *__restrict__ X,
+                                                                int M, int N, int K, int tiles_n, int tiles_k, float alpha, float beta,
+                                                                float *__restrict__ score)
+{
+    extern __shared__ unsigned char big_lds[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // XCD x takes the x-th eighth of the tiles, in bands of four tile rows (see above).
+    const int per_xcd = (tiles_n * tiles_k + 7) >> 3;
+    const int lin = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (lin >= tiles_n * tiles_k) return;               // whole block, before any barrier
+    const int band = lin / (4 * tiles_k), in_band = lin - band * 4 * tiles_k;
+    const int band_rows = tiles_n - 4 * band < 4 ? tiles_n - 4 * band : 4;
+    const int n0 = (4 * band + in_band % band_rows) * kBig, k0 = (in_band / band_rows) * kBig;
+    const int wn = wave >> 2, wk = wave & 3;
+    const int steps = (M + kBigStep - 1) / kBigStep;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte *)big_lds;
+
+    // Staging: wave w brings samples 4 w .. 4 w + 3 of a step, two per 1 KB request; lane l takes the unit that belongs
+    // at position l % 32 of its row.  Columns beyond N or K read column 0 (their results are not stored), samples
+    // beyond M the last one (zeroed once they are in LDS).  A request's address is the step's first sample (scalar) plus a
+    // lane offset that changes in the last step alone.
+    const int row_in = 4 * wave + (lane >> 5);          // + 2 i: this lane's sample of the step
+    uint32_t col_a[2], col_b[2];                        // first column of the lane's unit, per request
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int u = (lane & 31) ^ (4 * ((2 * i + (lane >> 5)) & 3));
+        col_a[i] = n0 + 8 * u < N ? n0 + 8 * u : 0;
+        col_b[i] = k0 + 8 * u < K ? k0 + 8 * u : 0;
+    }
+    auto sample = [&](int t, int i) {                   // within the step
+        const int m = row_in + 2 * i, rest = M - 1 - t * kBigStep;
+        return m < rest ? m : rest;
+    };
+    uint32_t off_a[2], off_b[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        off_a[i] = ((uint32_t)(row_in + 2 * i) * N + col_a[i]) * 2;
+        off_b[i] = ((uint32_t)(row_in + 2 * i) * K + col_b[i]) * 2;
+    }
+    // (m0 holds the LDS address; nothing else in this kernel uses it, and the compiler takes it in no clobber list.)
+    auto load_lds = [&](uint32_t dst, uint32_t off, const _Float16 *base) {
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(off), "s"(base) : "memory");
+    };
+    auto slot = [&](int t, int i) { return (uint32_t)(t & (kBigStages - 1)) * kBigStage + (uint32_t)(4 * wave + 2 * i) * kBigRow; };
+    auto cut = [&](int t) { return t * kBigStep + kBigStep > M; };         // the step ends beyond M
+    auto request_a = [&](int t) {
+        const _Float16 *base = dY + (size_t)t * kBigStep * N;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) load_lds(lds0 + slot(t, i), cut(t) ? ((uint32_t)sample(t, i) * N + col_a[i]) * 2 : off_a[i], base);
+    };
+    auto request_b = [&](int t) {
+        const _Float16 *base = X + (size_t)t * kBigStep * K;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) load_lds(lds0 + slot(t, i) + kBigOperand, cut(t) ? ((uint32_t)sample(t, i) * K + col_b[i]) * 2 : off_b[i], base);
+    };
+    // N8 = false: the same pieces of dY in registers.  The asm keeps the loads out of the compiler's bookkeeping (it would
+    // wait for the requests behind them too); the registers are touched behind an explicit wait only.
+    auto piece_back = [&](int t, int i) {               // columns by which the piece would pass the end of dY
+        const int past = (int)col_a[i] + 8 - N;
+        return t * kBigStep + sample(t, i) == M - 1 && past > 0 ? past : 0;
+    };
+    auto request_piece = [&](int t, u32x4s piece[2]) {
+        const _Float16 *base = dY + (size_t)t * kBigStep * N;
+        const bool last = t == steps - 1;               // uniform
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const uint32_t off = last ? ((uint32_t)sample(t, i) * N + col_a[i] - piece_back(t, i)) * 2 : off_a[i];
+            asm volatile("global_load_dwordx4 %0, %1, %2" : "=v"(piece[i]) : "v"(off), "s"(base) : "memory");
+        }
+    };
+    auto store_piece = [&](int t, u32x4s piece[2]) {    // after the wait
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            if (t == steps - 1) {                       // nonzero at most for the last columns of the last sample
+                int back = piece_back(t, i);
+                u32x4s &v = piece[i];
+                for (; back >= 2; back -= 2) v = u32x4s{v.y, v.z, v.w, 0u};
+                if (back) v = u32x4s{v.x >> 16 | v.y << 16, v.y >> 16 | v.z << 16, v.z >> 16 | v.w << 16, v.w >> 16};
+            }
+            *reinterpret_cast<u32x4s *>(big_lds + slot(t, i) + 16 * lane) = piece[i];
+        }
+    };
+    // Samples beyond M of step t, which this wave brought, become zeros in both operands.
+    auto zero_tail = [&](int t) {
+        if (!cut(t)) return;                            // uniform: the last step alone
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            if (t * kBigStep + row_in + 2 * i >= M) {
+                *reinterpret_cast<u32x4s *>(big_lds + slot(t, i) + 16 * lane) = u32x4s{0u, 0u, 0u, 0u};
+                *reinterpret_cast<u32x4s *>(big_lds + slot(t, i) + kBigOperand + 16 * lane) = u32x4s{0u, 0u, 0u, 0u};
+            }
+    };
+
+    // Operands: lane l holds column l % 32 of a 32-column tile and samples 8 (l / 32) .. + 7 of a batch of 16, read as two
+    // times four samples.
+    const int j = (lane >> 2) & 3, c = lane & 3, half = (lane >> 4) & 1;
+    const uint32_t lane_at = (uint32_t)(8 * (lane >> 5) + j) * kBigRow + 16u * (2 * half + (c >> 1)) + 8u * (c & 1);
+    uint32_t at_a[4], at_b[2];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) at_a[s] = lane_at + 16u * (uint32_t)((16 * wn + 4 * s) ^ (4 * j));
+#pragma unroll
+    for (int s = 0; s < 2; ++s) at_b[s] = kBigOperand + lane_at + 16u * (uint32_t)((8 * wk + 4 * s) ^ (4 * j));
+    half8s fa[2][4], fb[2][2];
+    auto read_tile = [&](uint32_t at) {
+        typedef __attribute__((address_space(3))) short4v lds_short4;
+        const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4 *)(lds_byte *)(big_lds + at));
+        const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4 *)(lds_byte *)(big_lds + at + 4 * kBigRow));
+        return __builtin_bit_cast(half8s, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+    auto read_batch = [&](int t, int batch, int set) {
+        const uint32_t base = (uint32_t)(t & (kBigStages - 1)) * kBigStage + (uint32_t)batch * 16 * kBigRow;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) fa[set][s] = read_tile(base + at_a[s]);
+#pragma unroll
+        for (int s = 0; s < 2; ++s) fb[set][s] = read_tile(base + at_b[s]);
+    };
+    float16v acc[4][2];
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[s][u][v] = 0.f;
+    auto multiply = [&](int set) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int u = 0; u < 2; ++u) acc[s][u] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[set][s], fb[set][u], acc[s][u], 0, 0, 0);
+    };
+
+    // Steps 0, 1, 2 requested; step 0 (unaligned: dY of steps 0 and 1) staged.
+    for (int t = 0; t < 3 && t < steps; ++t) {
+        if constexpr (N8) {
+            request_a(t);
+        } else if (t < 2) {
+            u32x4s piece[2];
+            request_piece(t, piece);
+            asm volatile("s_waitcnt vmcnt(0)" : "+v"(piece[0]), "+v"(piece[1])::"memory");
+            store_piece(t, piece);
+        }
+        request_b(t);
+    }
+    wait_loads<0>();
+    for (int t = 0; t < 3 && t < steps; ++t) zero_tail(t);
+    __syncthreads();
+    read_batch(0, 0, 0);
+    for (int t = 0; t < steps; ++t) {
+        u32x4s piece[2];
+        const bool more = t + 3 < steps;                // uniform
+        if constexpr (N8) {
+            if (more) { request_a(t + 3); request_b(t + 3); }
+        } else {
+            request_piece(t + 2 < steps ? t + 2 : steps - 1, piece);
+            if (more) request_b(t + 3);
+        }
+        read_batch(t, 1, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(0);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (N8) {
+            // Step t + 1 has landed, the two behind it may be on their way.
+            if (more) wait_loads<8>();
+            else wait_loads<0>();
+            if (t + 1 < steps) zero_tail(t + 1);
+        } else {
+            // One statement that takes the registers over, on no branch: a copy of them made on the way to it would be made
+            // before the loads have arrived.
+            if (!more) wait_loads<0>();
+            asm volatile("s_waitcnt vmcnt(2)" : "+v"(piece[0]), "+v"(piece[1])::"memory");
+            if (t + 2 < steps) { store_piece(t + 2, piece); zero_tail(t + 2); }
+        }
+        __syncthreads();
+        read_batch(t + 1, 0, 0);                        // past the last step: stale bytes, not used
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(1);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+
+    // D layout of a 32x32 tile: column (k) = lane % 32, row (n) = 8 * (v / 4) + 4 * (lane / 32) + v % 4.
+    if (k0 + wk * 64 >= K) return;                      // K is a multiple of 128
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int k = k0 + wk * 64 + u * 32 + (lane & 31);
+            const int nb = n0 + wn * 128 + s * 32 + 4 * (lane >> 5);
+            float *p = score + (size_t)nb * K + k;
+            auto finish = [&](auto whole) {             // whole: no row of the wave's part lies beyond N
+                float old[16];
+                if (beta != 0.f)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const int dn = 8 * (v >> 2) + (v & 3);
+                        old[v] = decltype(whole)::value || nb + dn < N ? p[(size_t)dn * K] : 0.f;
+                    }
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int dn = 8 * (v >> 2) + (v & 3);
+                    float g = alpha * acc[s][u][v];
+                    if (beta != 0.f) g += beta * old[v];
+                    if (decltype(whole)::value || nb + dn < N) p[(size_t)dn * K] = g;
+                }
+            };
+            if (n0 + wn * 128 + 128 <= N) finish(std::true_type{});
+            else finish(std::false_type{});
+        }
+}
+
 }  // namespace
 
 hipError_t launch_score(const void *dY, const void *X, int M, int N, int K, float alpha, float beta, float *score,
                         hipStream_t st)
 {
+    const _Float16 *d = static_cast<const _Float16 *>(dY), *x = static_cast<const _Float16 *>(X);
+    const bool n8 = N % 8 == 0;
+    const int cus = device_cus();
+    static std::atomic<uint32_t> lds_allowed[4];        // per kernel
+    // Which tile.  A round of 256 x 256 tiles over the chip takes 1.6 to 1.9 times as long as a round of 128 x 128 ones
+    // (two blocks per CU) and does twice the work, so it is taken where it needs at most half the rounds (measured over 16
+    // shapes at M = 128, 1024, 2048: 1.16 to 1.52 times as fast there, 0.57 to 1.03 elsewhere).  Rows of dY that are not
+    // 16-byte aligned always take it (1.25 to 4.4 times as fast: the other kernel reads them element by element), except
+    // rows of fewer than the eight elements it fetches at a time.
+    const int big_k = (K + kBig - 1) / kBig, big_n = (N + kBig - 1) / kBig;
     const int tiles_k = K / kTile, tiles_n = (N + kTile - 1) / kTile;
-    static std::atomic<uint32_t> lds_allowed[2];        // per kernel
+    const int64_t rounds_big = ((int64_t)big_k * big_n + cus - 1) / cus, rounds_small = ((int64_t)tiles_k * tiles_n + 2 * cus - 1) / (2 * cus);
+    if (n8 ? rounds_small >= 2 * rounds_big : N >= 8) {
+        const void *kernel = n8 ? reinterpret_cast<const void *>(&score_big_kernel<true>) : reinterpret_cast<const void *>(&score_big_kernel<false>);
+        hipError_t e = allow_dynamic_lds(kernel, (int)kBigLds, lds_allowed[n8 ? 2 : 3]);
+        if (e != hipSuccess) return e;
+        const int blocks = (big_k * big_n + 7) / 8 * 8;
+        if (n8) score_big_kernel<true><<<blocks, kBigThreads, kBigLds, st>>>(d, x, M, N, K, big_n, big_k, alpha, beta, score);
+        else score_big_kernel<false><<<blocks, kBigThreads, kBigLds, st>>>(d, x, M, N, K, big_n, big_k, alpha, beta, score);
+        return hipGetLastError();
+    }
     {
         hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&score_kernel<true>), (int)kScoreLds, lds_allowed[0]);
         if (e == hipSuccess)
             e = allow_dynamic_lds(reinterpret_cast<const void *>(&score_kernel<false>), (int)kScoreLds, lds_allowed[1]);
         if (e != hipSuccess) return e;
     }
-    const _Float16 *d = static_cast<const _Float16 *>(dY), *x = static_cast<const _Float16 *>(X);
     const int blocks = (tiles_n * tiles_k + 7) / 8 * 8;
-    if (N % 8 == 0)
+    if (n8)
         score_kernel<true><<<blocks, kScoreThreads, kScoreLds, st>>>(d, x, M, N, K, tiles_n, tiles_k, alpha, beta, score);
     else
         score_kernel<false><<<blocks, kScoreThreads, kScoreLds, st>>>(d, x, M, N, K, tiles_n, tiles_k, alpha, beta, score);

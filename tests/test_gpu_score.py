@@ -132,3 +132,28 @@ def test_score_7b_shapes_sampled(N, K):
     want = orc.score(sub, X)
     bad = np.abs(got[rows].astype(np.float64) - want) > _bound(sub, X)
     assert not bad.any(), f"{bad.sum()} entries off, first at {np.argwhere(bad)[:3].tolist()}"
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 2056, 4224), (31, 2056, 4224), (32, 2056, 4224), (33, 2048, 4352), (97, 2056, 4224), (160, 2296, 3968),
+                                   (1, 9, 128), (32, 255, 256), (33, 257, 384), (64, 10, 128), (95, 513, 640), (129, 2049, 1408)])
+def test_score_large_tiles(M, N, K):
+    """The 256 x 256 tiles at their edges: fewer samples than the ring of steps holds, a step cut short by M, tiles cut by N
+    and by K (half a tile), and rows of dY that are not 16-byte aligned, whose last piece would pass the end of the array;
+    the samples beyond M multiply nothing even where the last one holds an infinity."""
+    dY, X = _inputs(M, N, K, seed=M * 5 + N + K)
+    got = _check(dY, X, f"M={M} N={N} K={K}", alpha=0.5)
+    _check(dY, X, f"M={M} N={N} K={K} accumulated", alpha=2.0, beta=-0.5, prev=got)
+
+
+def test_score_large_tiles_infinite_last_sample():
+    """An infinity in the last sample reaches the one column of X it multiplies and nothing else, although staging repeats
+    that sample for the rows beyond M."""
+    import paper_2411_00850_amd as gwq
+    from gpu_helpers import to_gpu
+    M, N, K = 33, 257, 384
+    dY, X = _inputs(M, N, K, seed=1)
+    X[M - 1, 5] = np.inf
+    dY[:, 3] = np.abs(dY[:, 3]) + np.float16(0.01)
+    got = gwq.score(to_gpu(dY), to_gpu(X)).cpu().numpy()
+    fin = np.isfinite(got)
+    assert np.isposinf(got[3, 5]) and fin[:, np.arange(K) != 5].all()
