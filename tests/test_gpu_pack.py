@@ -318,3 +318,14 @@ def test_pack_rows_and_index_at_the_encoders_edges(bits, N, K, group):
     if group < 128:
         at = (used + 255) // 256 * 256
         assert torch.equal(D.index[at:at + N * (K // 16) * 4], want[at:at + N * (K // 16) * 4])
+
+
+@pytest.mark.parametrize("N", [4095, 4096, 4097, 8193])
+def test_pack_row_scan_rounds(N):
+    """The scan over the rows at the ends of its rounds of 4096 rows, ties at the threshold taken across them."""
+    import paper_2411_00850_amd as gwq
+    from gpu_helpers import assert_packed_equal, to_gpu
+    rng = np.random.default_rng(N)
+    W = gs.weight(N, 128, rng, planted_cols=2)
+    S = np.round(rng.random((N, 128)) * 50).astype(np.float32)      # 51 values, 1 % in the largest: 3 % ends inside the third's ties
+    assert_packed_equal(gwq.pack(to_gpu(W), to_gpu(S), 4, 30000), orc.pack(W, S, 4, 30000))
