@@ -218,6 +218,7 @@ constexpr size_t kBigLds = (size_t)kBigStages * kBigStage;                      
 
 typedef short short4v __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4s __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(2), may_alias));     // 16 bytes at 2-byte alignment
 typedef __attribute__((address_space(3))) unsigned char lds_byte;
 
 template <int N> __device__ inline void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
@@ -279,8 +280,8 @@ __global__ __launch_bounds__(kBigThreads) void score_big_kernel(const _Float16 *
 #pragma unroll
         for (int i = 0; i < 2; ++i) load_lds(lds0 + slot(t, i) + kBigOperand, cut(t) ? ((uint32_t)sample(t, i) * K + col_b[i]) * 2 : off_b[i], base);
     };
-    // N8 = false: the same pieces of dY in registers.  The asm keeps the loads out of the compiler's bookkeeping (it would
-    // wait for the requests behind them too); the registers are touched behind an explicit wait only.
+    // N8 = false: the same pieces of dY in registers, by ordinary loads: the compiler knows that they are in flight and waits
+    // before it touches the registers, whatever it does with them.
     auto piece_back = [&](int t, int i) {               // columns by which the piece would pass the end of dY
         const int past = (int)col_a[i] + 8 - N;
         return t * kBigStep + sample(t, i) == M - 1 && past > 0 ? past : 0;
@@ -291,10 +292,10 @@ __global__ __launch_bounds__(kBigThreads) void score_big_kernel(const _Float16 *
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const uint32_t off = last ? ((uint32_t)sample(t, i) * N + col_a[i] - piece_back(t, i)) * 2 : off_a[i];
-            asm volatile("global_load_dwordx4 %0, %1, %2" : "=v"(piece[i]) : "v"(off), "s"(base) : "memory");
+            piece[i] = *reinterpret_cast<const u32x4u *>(reinterpret_cast<const char *>(base) + off);
         }
     };
-    auto store_piece = [&](int t, u32x4s piece[2]) {    // after the wait
+    auto store_piece = [&](int t, u32x4s piece[2]) {
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             if (t == steps - 1) {                       // nonzero at most for the last columns of the last sample
@@ -354,17 +355,19 @@ __global__ __launch_bounds__(kBigThreads) void score_big_kernel(const _Float16 *
             for (int u = 0; u < 2; ++u) acc[s][u] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[set][s], fb[set][u], acc[s][u], 0, 0, 0);
     };
 
-    // Steps 0, 1, 2 requested; step 0 (unaligned: dY of steps 0 and 1) staged.
+    // Steps 0, 1, 2 requested (unaligned: dY of steps 0 and 1); all of that staged.
+    u32x4s first[2], second[2];
+    if constexpr (!N8) {
+        request_piece(0, first);
+        if (steps > 1) request_piece(1, second);
+    }
     for (int t = 0; t < 3 && t < steps; ++t) {
-        if constexpr (N8) {
-            request_a(t);
-        } else if (t < 2) {
-            u32x4s piece[2];
-            request_piece(t, piece);
-            asm volatile("s_waitcnt vmcnt(0)" : "+v"(piece[0]), "+v"(piece[1])::"memory");
-            store_piece(t, piece);
-        }
+        if constexpr (N8) request_a(t);
         request_b(t);
+    }
+    if constexpr (!N8) {
+        store_piece(0, first);
+        if (steps > 1) store_piece(1, second);
     }
     wait_loads<0>();
     for (int t = 0; t < 3 && t < steps; ++t) zero_tail(t);
@@ -376,8 +379,8 @@ __global__ __launch_bounds__(kBigThreads) void score_big_kernel(const _Float16 *
         if constexpr (N8) {
             if (more) { request_a(t + 3); request_b(t + 3); }
         } else {
-            request_piece(t + 2 < steps ? t + 2 : steps - 1, piece);
             if (more) request_b(t + 3);
+            if (t + 2 < steps) request_piece(t + 2, piece);
         }
         read_batch(t, 1, 1);
         __builtin_amdgcn_sched_barrier(0);
@@ -388,18 +391,21 @@ __global__ __launch_bounds__(kBigThreads) void score_big_kernel(const _Float16 *
             if (more) wait_loads<8>();
             else wait_loads<0>();
             if (t + 1 < steps) zero_tail(t + 1);
-        } else {
-            // One statement that takes the registers over, on no branch: a copy of them made on the way to it would be made
-            // before the loads have arrived.
-            if (!more) wait_loads<0>();
-            asm volatile("s_waitcnt vmcnt(2)" : "+v"(piece[0]), "+v"(piece[1])::"memory");
-            if (t + 2 < steps) { store_piece(t + 2, piece); zero_tail(t + 2); }
         }
         __syncthreads();
         read_batch(t + 1, 0, 0);                        // past the last step: stale bytes, not used
         __builtin_amdgcn_sched_barrier(0);
         multiply(1);
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (!N8) {
+            // Step t + 2 is staged a barrier before it is read: its pieces have had this whole step to arrive, and X of the
+            // steps up to t + 3 arrives with them.
+            if (t + 2 < steps) {
+                wait_loads<0>();
+                store_piece(t + 2, piece);
+                zero_tail(t + 2);
+            }
+        }
     }
 
     // D layout of a 32x32 tile: column (k) = lane % 32, row (n) = 8 * (v / 4) + 4 * (lane / 32) + v % 4.
