@@ -73,8 +73,9 @@ __global__ __launch_bounds__(kScoreThreads, N8 ? 2 : 1) void score_kernel(const 
     const int steps = (M + kStepM - 1) / kStepM;
 
     // Requests for step t.  Rows beyond M and columns beyond N read a valid address.  Columns beyond N
-    // only reach rows of the tile that are never stored; rows beyond M are zeroed in X when the set is
-    // staged (touching a loaded value here would wait for it here), which makes their products zero.
+    // only reach rows of the tile that are never stored; rows beyond M are zeroed in both operands when the
+    // set is staged (touching a loaded value here would wait for it here): next to a zero in one of them
+    // alone, an infinity in the row that was read in their place would make a NaN.
     auto fetch = [&](int t, RowSet &r) {
         const int nn = n0 + 8 * chunk, kk = k0 + 8 * chunk;
 #pragma unroll
@@ -103,22 +104,23 @@ __global__ __launch_bounds__(kScoreThreads, N8 ? 2 : 1) void score_kernel(const 
         const int m = t * kStepM + 4 * quad;
         const uint32_t rows01 = (m < M ? 0xFFFFu : 0u) | (m + 1 < M ? 0xFFFF0000u : 0u);
         const uint32_t rows23 = (m + 2 < M ? 0xFFFFu : 0u) | (m + 3 < M ? 0xFFFF0000u : 0u);
-        auto put = [&](char *base, const uint4 *v, uint32_t mask01, uint32_t mask23) {
+        auto put = [&](char *base, const uint4 *v) {
             const uint32_t w[4][4] = {{v[0].x, v[0].y, v[0].z, v[0].w}, {v[1].x, v[1].y, v[1].z, v[1].w},
                                       {v[2].x, v[2].y, v[2].z, v[2].w}, {v[3].x, v[3].y, v[3].z, v[3].w}};
 #pragma unroll
             for (int jj = 0; jj < 2; ++jj) {
                 const int j = 2 * part + jj;            // column j ^ flip: the same word of the loaded 16 bytes
-                const uint32_t sel = ((j & 1) ^ flip) ? 0x07060302u : 0x05040100u;   // the same half of two words
+                // the same half of two words; a selector byte of 0x0C gives zero
+                const uint32_t sel = ((j & 1) ^ flip) ? 0x07060302u : 0x05040100u;
                 uint2 piece;
-                piece.x = __builtin_amdgcn_perm(w[1][j >> 1], w[0][j >> 1], sel) & mask01;
-                piece.y = __builtin_amdgcn_perm(w[3][j >> 1], w[2][j >> 1], sel) & mask23;
+                piece.x = __builtin_amdgcn_perm(w[1][j >> 1], w[0][j >> 1], (sel & rows01) | (0x0C0C0C0Cu & ~rows01));
+                piece.y = __builtin_amdgcn_perm(w[3][j >> 1], w[2][j >> 1], (sel & rows23) | (0x0C0C0C0Cu & ~rows23));
                 const int row = 8 * chunk + (j ^ flip);
                 *reinterpret_cast<uint2 *>(base + (size_t)unit_of(row, quad >> 1) * 16 + 8 * (quad & 1)) = piece;
             }
         };
-        put(a_base, r.a, 0xFFFFFFFFu, 0xFFFFFFFFu);
-        put(b_base, r.b, rows01, rows23);
+        put(a_base, r.a);
+        put(b_base, r.b);
     };
 
     float16v acc[2][2];

@@ -145,15 +145,20 @@ def test_score_large_tiles(M, N, K):
     _check(dY, X, f"M={M} N={N} K={K} accumulated", alpha=2.0, beta=-0.5, prev=got)
 
 
-def test_score_large_tiles_infinite_last_sample():
-    """An infinity in the last sample reaches the one column of X it multiplies and nothing else, although staging repeats
-    that sample for the rows beyond M."""
+# Shapes for each kernel (on 256 CUs): the 128 x 128 tiles, the same with dY read element by element (N < 8), the 256 x 256
+# tiles with unaligned rows of dY, and with aligned ones (three steps of 32 samples at M = 70).
+@pytest.mark.parametrize("M,N,K", [(33, 16, 128), (70, 264, 384), (33, 7, 128), (33, 257, 384), (70, 1001, 256), (33, 2056, 4224), (70, 2056, 4224)])
+def test_score_infinities_in_the_first_and_last_sample(M, N, K):
+    """An infinity reaches the entries it multiplies and nothing else, and makes infinities there, although staging repeats
+    the first or the last sample for the rows beyond M: those multiply nothing, whatever they hold."""
     import paper_2411_00850_amd as gwq
     from gpu_helpers import to_gpu
-    M, N, K = 33, 257, 384
-    dY, X = _inputs(M, N, K, seed=1)
-    X[M - 1, 5] = np.inf
-    dY[:, 3] = np.abs(dY[:, 3]) + np.float16(0.01)
+    dY, X = _inputs(M, N, K, seed=M + N)
+    for row in (0, M - 1):                                          # no zero and one sign, so that the infinities' sign is known
+        X[row] = np.abs(X[row]) + np.float16(0.01)
+        dY[row] = np.abs(dY[row]) + np.float16(0.01)
+    dY[0, 3] = dY[M - 1, 4] = X[0, 5] = X[M - 1, 6] = np.inf
     got = gwq.score(to_gpu(dY), to_gpu(X)).cpu().numpy()
-    fin = np.isfinite(got)
-    assert np.isposinf(got[3, 5]) and fin[:, np.arange(K) != 5].all()
+    touched = np.zeros((N, K), bool)
+    touched[[3, 4], :] = touched[:, [5, 6]] = True
+    assert np.isposinf(got[touched]).all() and np.isfinite(got[~touched]).all()
