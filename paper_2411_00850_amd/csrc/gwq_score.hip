@@ -419,24 +419,32 @@ __global__ __launch_bounds__(kBigThreads) void score_big_kernel(const _Float16 *
             const int k = k0 + wk * 64 + u * 32 + (lane & 31);
             const int nb = n0 + wn * 128 + s * 32 + 4 * (lane >> 5);
             float *p = score + (size_t)nb * K + k;
-            auto finish = [&](auto whole) {             // whole: no row of the wave's part lies beyond N
+            // Rows v0 .. v1 of the sixteen; whole: none of them lies beyond N.
+            auto finish = [&](auto whole, int v0, int v1) {
                 float old[16];
                 if (beta != 0.f)
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) {
+                    for (int v = v0; v < v1; ++v) {
                         const int dn = 8 * (v >> 2) + (v & 3);
                         old[v] = decltype(whole)::value || nb + dn < N ? p[(size_t)dn * K] : 0.f;
                     }
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
+                for (int v = v0; v < v1; ++v) {
                     const int dn = 8 * (v >> 2) + (v & 3);
                     float g = alpha * acc[s][u][v];
                     if (beta != 0.f) g += beta * old[v];
                     if (decltype(whole)::value || nb + dn < N) p[(size_t)dn * K] = g;
                 }
             };
-            if (n0 + wn * 128 + 128 <= N) finish(std::true_type{});
-            else finish(std::false_type{});
+            if (n0 + wn * 128 + 128 <= N) { finish(std::true_type{}, 0, 16); continue; }
+            // A tile cut by N: eight rows (four of each half of the wave) at a time, of which at most one lot is cut itself.
+            // (A guard on every store is code enough to be fetched at 5 us a block: 100 x 1024, M = 33, 16.0 -> 10.7 us.)
+#pragma unroll
+            for (int v = 0; v < 16; v += 4) {
+                const int rows = N - (n0 + wn * 128 + s * 32 + 2 * v);
+                if (rows >= 8) finish(std::true_type{}, v, v + 4);
+                else if (!N8 && rows > 0) finish(std::false_type{}, v, v + 4);
+            }
         }
 }
 
@@ -452,12 +460,14 @@ hipError_t launch_score(const void *dY, const void *X, int M, int N, int K, floa
     // Which tile.  A round of 256 x 256 tiles over the chip takes 1.6 to 1.9 times as long as a round of 128 x 128 ones
     // (two blocks per CU) and does twice the work, so it is taken where it needs at most half the rounds (measured over 16
     // shapes at M = 128, 1024, 2048: 1.16 to 1.52 times as fast there, 0.57 to 1.03 elsewhere).  Rows of dY that are not
-    // 16-byte aligned always take it (1.25 to 4.4 times as fast: the other kernel reads them element by element), except
-    // rows of fewer than the eight elements it fetches at a time.
+    // 16-byte aligned take it from 12 channels on: the other kernel reads them element by element, which is the faster way
+    // only while nearly all lanes of a load share one column (us at M = 33 and 2048, this kernel against that one:
+    // 9 x 4096 9.5 and 54.4 against 8.9 and 46.9; 12 x 1024 9.3 and 54.1 against 9.8 and 54.1; 100 x 1024 10.7 and 55.4
+    // against 13.3 and 82.8; 9001 x 4096 36 and 193 against 97 and 752).
     const int big_k = (K + kBig - 1) / kBig, big_n = (N + kBig - 1) / kBig;
     const int tiles_k = K / kTile, tiles_n = (N + kTile - 1) / kTile;
     const int64_t rounds_big = ((int64_t)big_k * big_n + cus - 1) / cus, rounds_small = ((int64_t)tiles_k * tiles_n + 2 * cus - 1) / (2 * cus);
-    if (n8 ? rounds_small >= 2 * rounds_big : N >= 8) {
+    if (n8 ? rounds_small >= 2 * rounds_big : N >= 12) {
         const void *kernel = n8 ? reinterpret_cast<const void *>(&score_big_kernel<true>) : reinterpret_cast<const void *>(&score_big_kernel<false>);
         hipError_t e = allow_dynamic_lds(kernel, (int)kBigLds, lds_allowed[n8 ? 2 : 3]);
         if (e != hipSuccess) return e;

@@ -135,7 +135,8 @@ def test_score_7b_shapes_sampled(N, K):
 
 
 @pytest.mark.parametrize("M,N,K", [(1, 2056, 4224), (31, 2056, 4224), (32, 2056, 4224), (33, 2048, 4352), (97, 2056, 4224), (160, 2296, 3968),
-                                   (1, 9, 128), (32, 255, 256), (33, 257, 384), (64, 10, 128), (95, 513, 640), (129, 2049, 1408)])
+                                   (1, 9, 128), (32, 255, 256), (33, 257, 384), (64, 10, 128), (95, 513, 640), (129, 2049, 1408),
+                                   (1, 13, 128), (64, 12, 128), (65, 14, 256), (70, 1003, 256), (96, 135, 128), (33, 2064, 4224)])
 def test_score_large_tiles(M, N, K):
     """The 256 x 256 tiles at their edges: fewer samples than the ring of steps holds, a step cut short by M, tiles cut by N
     and by K (half a tile), and rows of dY that are not 16-byte aligned, whose last piece would pass the end of the array;
@@ -145,7 +146,7 @@ def test_score_large_tiles(M, N, K):
     _check(dY, X, f"M={M} N={N} K={K} accumulated", alpha=2.0, beta=-0.5, prev=got)
 
 
-# Shapes for each kernel (on 256 CUs): the 128 x 128 tiles, the same with dY read element by element (N < 8), the 256 x 256
+# Shapes for each kernel (on 256 CUs): the 128 x 128 tiles, the same with dY read element by element (N < 12), the 256 x 256
 # tiles with unaligned rows of dY, and with aligned ones (three steps of 32 samples at M = 70).
 @pytest.mark.parametrize("M,N,K", [(33, 16, 128), (70, 264, 384), (33, 7, 128), (33, 257, 384), (70, 1001, 256), (33, 2056, 4224), (70, 2056, 4224)])
 def test_score_infinities_in_the_first_and_last_sample(M, N, K):
