@@ -664,9 +664,11 @@ hipError_t run_select(const void *score, int N, int K, uint32_t *ws, int32_t *ro
 template <int BITS, bool F16, int STEPS>
 hipError_t run_encode(const void *W, const void *score, const gwq_packed &P, const uint32_t *ws, hipStream_t st)
 {
-    // A wave per row fills the chip from about a thousand rows on; below, four waves share a row (and count its parts
-    // first, which reads the scores once more).
-    const int parts = P.N < 1024 ? kWaves : 1;
+    // Few rows: one wave for each leaves the chip waiting for its trips, so four share a row, at the price of reading the
+    // scores once more to count what the parts before keep.  Where that stops to pay (us of a whole gwq_pack, one wave
+    // against four; FP32 scores 1024 x 8192 75 / 65, 1300 x 65536 368 / 365, 1500 x 65536 394 / 410, 1900 x 8192 85 / 88;
+    // FP16 scores, half the bytes, 1500 x 28672 198 / 161, 2047 x 8192 88 / 84, 2047 x 2048 46.6 / 46.8).
+    const int parts = P.N < (F16 ? 2048 : 1300) ? kWaves : 1;
     const int blocks = parts == 1 ? (P.N + kWaves - 1) / kWaves : P.N;
     GroupRecord *rec = static_cast<GroupRecord *>(P.index);
     uint32_t *fine = rec ? reinterpret_cast<uint32_t *>(static_cast<char *>(P.index) + index_record_bytes(P.N, P.K)) : nullptr;

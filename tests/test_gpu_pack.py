@@ -320,6 +320,18 @@ def test_pack_rows_and_index_at_the_encoders_edges(bits, N, K, group):
         assert torch.equal(D.index[at:at + N * (K // 16) * 4], want[at:at + N * (K // 16) * 4])
 
 
+@pytest.mark.parametrize("N,f16", [(1299, False), (1300, False), (2047, True), (2048, True)])
+def test_pack_where_rows_stop_being_shared(N, f16):
+    """The last row counts for which four waves share a row and the first for which one takes it, per type of score, with
+    two trips a row (so that the parts hand positions and ties on) and the ties at the threshold spread over the rows."""
+    import paper_2411_00850_amd as gwq
+    from gpu_helpers import assert_packed_equal, to_gpu
+    rng = np.random.default_rng(N)
+    W = gs.weight(N, 640, rng, planted_cols=2)
+    S = np.round(rng.random((N, 640)) * 50).astype(np.float16 if f16 else np.float32)
+    assert_packed_equal(gwq.pack(to_gpu(W), to_gpu(S), 4, 30000), orc.pack(W, S, 4, 30000))
+
+
 @pytest.mark.parametrize("N", [4095, 4096, 4097, 8193])
 def test_pack_row_scan_rounds(N):
     """The scan over the rows at the ends of its rounds of 4096 rows, ties at the threshold taken across them."""
