@@ -143,13 +143,15 @@ def test_pack_and_quality_replay_from_a_graph():
         assert abs(got[0] - sq) <= 1e-11 * sq and got[2] == mx
 
 
-def test_score_replays_from_a_graph():
-    """gwq_score, then gwq_pack ranking what it wrote, captured together: the calibration step of one layer."""
+@pytest.mark.parametrize("N,K", [(96, 384), (135, 384), (2056, 4224)])
+def test_score_replays_from_a_graph(N, K):
+    """gwq_score (128 x 128 tiles; 256 x 256 tiles with unaligned and aligned rows of dY), then gwq_pack ranking what it
+    wrote, captured together: the calibration step of one layer."""
     import ctypes
     import torch
     import paper_2411_00850_amd as gwq
     from gpu_helpers import to_gpu, assert_packed_equal
-    M, N, K, bits = 150, 96, 384, 4
+    M, bits = 150, 4
     W, _, rng = _layer(44, N, K, bits)
     Wd = to_gpu(W)
     dYd = to_gpu((0.05 * rng.standard_normal((M, N))).astype(np.float16))

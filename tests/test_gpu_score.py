@@ -52,20 +52,33 @@ def test_score_small_shapes(M, N, K):
     _check(dY, X, f"M={M} N={N} K={K}")
 
 
-def test_score_picks_rows_and_columns_exactly():
+# For each kernel (on 256 CUs): the 128 x 128 tiles (one band of tile rows, and two of which the second is short), the same with
+# dY read element by element, the 256 x 256 tiles with unaligned rows of dY, and with aligned ones.
+@pytest.mark.parametrize("N,K", [(136, 256), (1416, 640), (11, 256), (140, 256), (2056, 4224)])
+def test_score_picks_rows_and_columns_exactly(N, K):
     """dY with a single one at (m0, n0) copies row m0 of X into row n0 of the score, bit for bit, and leaves
     every other row zero: a transposed or shifted operand cannot pass."""
     import paper_2411_00850_amd as gwq
     from gpu_helpers import to_gpu
-    M, N, K = 150, 140, 256
+    M = 150
     _, X = _inputs(M, N, K, seed=5)
-    for m0, n0 in ((0, 0), (63, 127), (64, 128), (149, 139), (77, 5)):
+    for m0, n0 in ((0, 0), (63, min(127, N - 1)), (64, min(128, N - 2)), (149, N - 1), (77, 5)):
         dY = np.zeros((M, N), np.float16)
         dY[m0, n0] = 1.0
         got = gwq.score(to_gpu(dY), to_gpu(X)).cpu().numpy()
         assert np.array_equal(got[n0], X[m0].astype(np.float32)), (m0, n0)
         got[n0] = 0
         assert not got.any(), (m0, n0)
+
+
+@pytest.mark.parametrize("M,N,K", [(65, 1416, 640), (100, 1560, 384), (70, 2040, 4096), (33, 8192, 1024)])
+def test_score_small_tiles_in_several_bands(M, N, K):
+    """The 128 x 128 tiles with more than the eight tile rows of one band: whole and short last bands, tile counts that the
+    eight XCDs do not share evenly, rows cut by N, steps cut by M."""
+    dY, X = _inputs(M, N, K, seed=M + N + K)
+    got = _check(dY, X, f"M={M} N={N} K={K}", alpha=0.5)
+    if N * K < 1 << 20:
+        _check(dY, X, f"M={M} N={N} K={K} accumulated", alpha=2.0, beta=-0.5, prev=got)
 
 
 def test_score_mean_over_samples_and_scaling():
@@ -117,12 +130,12 @@ def test_score_feeds_pack():
     assert len(keep_gpu ^ keep_ref) <= 2
 
 
-@pytest.mark.parametrize("N,K", [(4096, 4096), (4096, 11008)])
-def test_score_7b_shapes_sampled(N, K):
-    """Full 7B shapes at M = 2048, as bench.py times them; the oracle computes sampled output rows."""
+@pytest.mark.parametrize("N,K,M", [(4096, 4096, 2048), (4096, 11008, 2048), (6144, 4096, 2000)])
+def test_score_7b_shapes_sampled(N, K, M):
+    """Full 7B shapes at M = 2048, as bench.py times them, and a layer that fills the chip with 128 x 128 tiles; the oracle
+    computes sampled output rows."""
     import paper_2411_00850_amd as gwq
     from gpu_helpers import to_gpu
-    M = 2048
     dY, X = _inputs(M, N, K, seed=N + K, hot=0.001)
     got = gwq.score(to_gpu(dY), to_gpu(X)).cpu().numpy()
     assert np.isfinite(got).all()
