@@ -1,26 +1,28 @@
 #!/usr/bin/env python3
 """Benchmark of the GWQ linear-layer path on one MI355X.
 
-Workload (benchmark configs[1]): one LLaMA-2-7B-shaped decoder layer, 7 matrices, 4-bit codes,
+Workload: one LLaMA-2-7B-shaped decoder layer, 7 matrices, 4-bit codes,
 group 128, 1 % FP16 outliers, synthetic weights with planted outlier columns.  A step is one decode
 pass (M = 1) over the 7 matrices, launched the way the layer's data flow allows: q, k and v in one
 grouped launch (gwq_linear_batch), o alone, gate and up in one, down alone - 4 launches.  The packed
 layer exists in several copies and the steps rotate over them, so every step streams its weights
 from HBM rather than from the 256 MB last-level cache, as a decode pass over a whole model does.
 
-One JSON line is printed.  `value` is the algorithmic GB/s of the K timed steps (packed bytes + X + Y
-per step over wall time, inputs resident in HBM).  `roofline` is the decode kernel alone: algorithmic
-bytes per launch over the launch duration, from HIP events on the launch stream around each of at least
-200 further steps (median over the replays, whatever --steps says: 20 steps are 0.7 ms, too short to
-settle).  `roofline.kernel` is what the library's dispatcher reports for the launches that ran
-(gwq_linear_plan), `roofline.achievable` a plain streaming read of the same bytes launched the same way
-(gwq_probe_stream: the ceiling a kernel with no arithmetic reaches on this machine), and
-`roofline.traffic` the counter-measured HBM bytes, taken from profiles/ only when that summary was made
-from the decode sources as they are now.  Further objects report the same pass at M = 4 and 16, the
-prefill GEMM (M = 2048) in TFLOP/s against the MFMA peak and against MFMAs issued from registers
-(gwq_probe_mfma), the 3-bit layer, the 70B shapes, gwq_pack / gwq_quality / gwq_score, one row per
-(configuration, shape, bits, M) with the oracle timed beside the kernel (`extras.rows`), a 512-step
-decoder-layer loop against FP16 weights, and the CPU oracle on a bounded sample (`cpu_baseline`).
+One JSON line is printed, the last of stdout and short enough to be read whole from the end of a log;
+the further measurements come before it, a line `extras.NAME {...}` each.  `value` is the algorithmic
+GB/s of the K timed steps (packed bytes + X + Y per step over wall time, inputs resident in HBM).
+`roofline` is the decode kernel alone: algorithmic bytes per launch over the launch duration, from HIP
+events on the launch stream around each of at least 200 further steps (median over the replays, whatever
+--steps says: 20 steps are 0.7 ms, too short to settle).  `roofline.kernel` is what the library's
+dispatcher reports for the launches that ran (gwq_linear_plan; `extras.launches` has them in full),
+`roofline.achievable` a plain streaming read of the same bytes launched the same way (gwq_probe_stream:
+the ceiling a kernel with no arithmetic reaches on this machine), and `roofline.traffic` the
+counter-measured HBM bytes, taken from profiles/ only when that summary was made from the decode sources
+as they are now.  `prefill_M2048` is the prefill GEMM's part of the metric.  The extras: the same pass at
+M = 4 and 16, the prefill GEMM (M = 2048) in TFLOP/s against the MFMA peak and against MFMAs issued from
+registers (gwq_probe_mfma), the 3-bit layer, the 70B shapes, gwq_pack / gwq_quality / gwq_score, one row
+per (configuration, shape, bits, M) with the oracle timed beside the kernel (`extras.rows`), a 512-step
+decoder-layer loop against FP16 weights.  `cpu_baseline` is the CPU oracle on a bounded sample.
 """
 import argparse
 import json
@@ -484,6 +486,7 @@ def main():
     plans = decode_leg.plans
     kernels = sorted({p.split(" ")[0] for p in plans})
     ceiling = stream_read_leg(1, args.group, layers) if args.launch == "graph" else None
+    print(f"extras.launches {json.dumps(plans)}")
     out = {
         "metric": "gwq_linear decode GB/s (% HBM peak) & prefill TFLOP/s (% MFMA peak), 7B shapes",
         "value": round(value, 1), "unit": "GB/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
@@ -495,8 +498,7 @@ def main():
                                                                "all": "one call over the 7 matrices (one launch per distinct K)"}[args.group],
                    "copies_rotated": args.copies, "bytes_per_step": bytes_step, "launch": args.launch},
         "pct_hbm_peak": round(100 * value / HBM_PEAK_GBS, 2),
-        "roofline": {"bound": "hbm", "kernel": kernels[0] if len(kernels) == 1 else kernels, "launches": plans,
-                     "achieved": round(achieved, 1),
+        "roofline": {"bound": "hbm", "kernel": kernels[0] if len(kernels) == 1 else kernels, "achieved": round(achieved, 1),
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": read_traffic(), "bytes_per_launch": round(bytes_launch),
                      "avg_launch_us": round(launch_ms * 1e3, 3),
@@ -931,7 +933,11 @@ def main():
         # oracle on the host cores (all cores and one), with the parity errors of exactly that row.
         if "rows" in legs:
             extra["rows"] = result_rows(gwq, gs, dev, torch)
-        out["extras"] = extra
+        if "prefill_M2048" in extra:
+            out["prefill_M2048"] = {k: extra["prefill_M2048"][k] for k in ("TFLOP/s", "ms_per_pass", "pct_mfma_f16_peak")}
+        for name, value in extra.items():
+            for item in value if isinstance(value, list) else [value]:
+                print(f"extras.{name} {json.dumps(item)}")
 
     if not args.no_cpu_baseline:
         from oracle import gwq_oracle as orc
