@@ -294,10 +294,10 @@ __global__ __launch_bounds__(kThreads) void candidates_kernel(const void *score,
 
 // Ties at the threshold are kept in flat-index order until `remaining` of them are taken;
 // row_ptr is the running count of kept entries.  One block, since every row needs the sum of those before it; a chain of
-// two block scans and their barriers per round bounds it, so a round is as long as LDS allows (4096 rows, 1024 threads
-// with kRowsPerThread consecutive rows each) and the next round's counts are requested before this round's scans.
-// Rounds of 2048 rows, 256 threads, without the early requests: 8.6 us at 4096 rows, 22.8 at 11008; this way 3.9 and 8.3.  The counts go
-// through LDS: read from memory with consecutive threads on consecutive rows, handed to the thread that owns them.
+// two block scans and their barriers per round bounds it, so a round takes many rows (4096: four consecutive rows for each
+// of the 1024 threads that a block can have) and the next round's counts are requested before this round's scans.
+// 4.0 us at 4096 rows, one round, and 8.2 at 11008 (256 threads, rounds of 2048 rows, no early requests: 8.6 and 22.8).  The
+// counts go through LDS: read from memory with consecutive threads on consecutive rows, handed to the thread that owns them.
 constexpr int kScanThreads = 1024;
 constexpr int kRowsPerThread = 4;
 __global__ __launch_bounds__(kScanThreads) void row_scan_kernel(uint32_t *ws, int N, int32_t *row_ptr)
@@ -368,21 +368,21 @@ __global__ __launch_bounds__(kScanThreads) void row_scan_kernel(uint32_t *ws, in
 //
 // One wave walks a row (or, where there are few rows, one of four consecutive parts of it) in flat-index order, 512
 // weights per trip, eight per lane: it marks the kept entries, appends them to the CSR arrays, and quantises and packs the
-// rest.  No barrier and no LDS: positions come from the compare masks (mbcnt), a group's 2 to 16 lanes meet by DPP, the
-// 3-bit words are put together across a quad of lanes.  The next trip's weights and scores are requested before this
-// trip's are worked on.
+// rest.  The trips need no barrier and no LDS: positions come from the compare masks (mbcnt), a group's 2 to 16 lanes meet
+// by DPP, the 3-bit words are put together across a quad of lanes.  (The four waves of a shared row exchange once, before
+// their trips, what each part keeps.)  The next trip's weights and scores are requested before this trip's are worked on.
 //
 // Bound by HBM (6.56 bytes per weight at FP32 scores), which needs the instruction stream short: about 300 vector
 // instructions per trip and wave.  A kept weight is replaced by 0: a group's range always contains 0 and 0 gets the code
 // z, so masking it once serves the range and the code.  The quotient w / s is one reciprocal per group and three
 // instructions per weight (see quotient).
 //
-// Measured, 11008 x 4096 and 4096 x 11008, 4 bits, FP32 scores, with the layer's index: 53 us = 5.7 TB/s (a block of four
-// waves per row with a barrier per 2048 weights, IEEE divisions and fp64 scales took 88 .. 92 us, and 7 .. 12 us more for a
-// kernel that wrote the index).
+// Measured, 11008 x 4096 and 4096 x 11008, 4 bits, FP32 scores, with the layer's index: 51 .. 56 us = 5.3 .. 5.8 TB/s (a
+// block of four waves per row with a barrier per 2048 weights, IEEE divisions and fp64 scales took 88 .. 92 us, and 7 .. 12 us
+// more for a kernel that wrote the index).
 
-// w / s for an FP16 number w and the FP16 scale s (r: its reciprocal to 1 ulp): the product with r is within 2^-22 of the
-// quotient, its residual w - t s has at most 13 significant bits and is exact, and the correction leaves an error below
+// w / s for an FP16 number w and the FP16 scale s (r: its reciprocal to 1 ulp), by one step of Markstein's correction with
+// fused multiply-adds: the product with r is within 2^-22 of the quotient, its residual w - t s has at most 13 significant bits and is exact, and the correction leaves an error below
 // 2^-44 before the last rounding.  What follows rounds to an integer, half to even: a quotient that is exactly a
 // half-integer is representable and comes out exactly; any other (mw 2^a / ms 2^b with 11-bit mw, ms) is at least
 // 1 / (4 ms) >= 2^-13 away from one while below 2^6 in magnitude, and larger ones are clamped to the same end whatever
@@ -396,7 +396,7 @@ __device__ inline float quotient(float w, float s, float r)
 __device__ inline float half_bits_to_float(uint32_t h) { return (float)__builtin_bit_cast(_Float16, (uint16_t)h); }
 
 // Eq. 6 / Eq. 7 for one group from its masked min and max (both already widened to contain 0): the smallest FP16 s with
-// s * maxq >= mx - mn, and z = clamp(rint(-mn / s), 0, maxq).  The range is held exactly as d + err (two-sum), products
+// s * maxq >= mx - mn, and z = clamp(rint(-mn / s), 0, maxq).  The range is held exactly as d + err (Knuth's two-sum), products
 // s * maxq are exact in FP32, so comparing them is exact.  The guess RN(d / maxq) is the wanted s or its neighbour.
 template <int BITS> __device__ inline void scale_and_zero(float mn, float mx, uint32_t &s_bits, float &s, float &r, float &z)
 {

@@ -206,13 +206,15 @@ __global__ __launch_bounds__(kScoreThreads, N8 ? 2 : 1) void score_kernel(const 
 // are permuted by sample (unit u of sample m at u ^ 4 (m % 4)): the four samples of a read fall into different banks.
 // One barrier per step, in its middle: behind it the next step is staged and this one's operands are in registers.
 //
-// Measured at M = 2048 (128 x 128 tiles before): 4096 x 4096, one round of tiles, 72.6 us = 946 TFLOP/s (101.9 us);
-// 4096 x 11008 238 us (343), accumulating 262 us (381); with 3333 or 9001 channels 3.4 to 3.6 times as fast.  What is left at
-// 4096 x 11008: 688 tiles on 256 CUs are three rounds at 2.69 rounds' work, and 180 MB of FP32 scores (36 us at HBM speed)
-// are written at the rounds' ends.  Four waves of 128 x 128 (a third less LDS traffic, one wave per SIMD): 10 % slower.
+// Measured at M = 2048 (128 x 128 tiles in brackets), calls replayed from a graph on normally distributed inputs:
+// 4096 x 4096, one round of tiles, 73.7 us = 932 TFLOP/s (104.9); 4096 x 11008 192 us (262), accumulating 210 us (318);
+// unaligned 3333 x 4096 75 us (336), 9001 x 4096 193 us (753).  The matrix cores work 43 to 45 % of the time, the LDS sees
+// no bank conflict.  What is left at 4096 x 11008: 688 tiles on 256 CUs are three rounds at 2.69 rounds' work, and 180 MB
+// of FP32 scores (36 us at HBM speed) are written at the rounds' ends.  Four waves of 128 x 128 (a third less LDS traffic,
+// one wave per SIMD): 10 % slower.
 //
 // N8 = false: rows of dY are not 16-byte aligned.  Their pieces come through registers (loads at 2-byte alignment, requested
-// a step before they are stored); only the piece that would reach beyond the end of dY is read from 16 bytes before
+// at the start of a step and stored at its end); only the piece that would reach beyond the end of dY is read from 16 bytes before
 // the end and shifted (N >= 8).
 constexpr int kBig = 256, kBigStep = 32, kBigThreads = 512, kBigStages = 4;
 constexpr uint32_t kBigRow = kBig * 2, kBigOperand = kBigStep * kBigRow, kBigStage = 2 * kBigOperand;    // bytes
@@ -457,13 +459,15 @@ hipError_t launch_score(const void *dY, const void *X, int M, int N, int K, floa
     const bool n8 = N % 8 == 0;
     const int cus = device_cus();
     static std::atomic<uint32_t> lds_allowed[4];        // per kernel
-    // Which tile.  A round of 256 x 256 tiles over the chip takes 1.6 to 1.9 times as long as a round of 128 x 128 ones
-    // (two blocks per CU) and does twice the work, so it is taken where it needs at most half the rounds (measured over 16
-    // shapes at M = 128, 1024, 2048: 1.16 to 1.52 times as fast there, 0.57 to 1.03 elsewhere).  Rows of dY that are not
-    // 16-byte aligned take it from 12 channels on: the other kernel reads them element by element, which is the faster way
-    // only while nearly all lanes of a load share one column (us at M = 33 and 2048, this kernel against that one:
-    // 9 x 4096 9.5 and 54.4 against 8.9 and 46.9; 12 x 1024 9.3 and 54.1 against 9.8 and 54.1; 100 x 1024 10.7 and 55.4
-    // against 13.3 and 82.8; 9001 x 4096 36 and 193 against 97 and 752).
+    // Which tile.  A round of 256 x 256 tiles over the chip does twice the work of a round of 128 x 128 ones (two blocks per
+    // CU), so it is taken where it needs at most half the rounds (us at M = 33 and 2048, 128 against 256: one round
+    // against one, 2048 x 4096 13.2 and 56.8 against 13.5 and 57.8; two against one, 4096 x 4096 20.7 and 104.9 against 17.6
+    // and 73.7; six against three, 4096 x 11008 44.9 and 262 against 37.8 and 192).  In between (three against two,
+    // 6144 x 4096 27.2 and 148 against 24.9 and 120) the large tiles win as well, which this rule forgoes.
+    // Rows of dY that are not 16-byte aligned take the large tiles from 12 channels on: the other kernel reads them element
+    // by element, which is the faster way only while nearly all lanes of a load share one column (us at M = 33 and 2048,
+    // 128 against 256: 9 x 4096 8.9 and 46.9 against 9.5 and 54.4; 12 x 1024 9.8 and 54.1 against 9.3 and 54.1;
+    // 100 x 1024 13.3 and 82.8 against 10.8 and 55.4; 9001 x 4096 97 and 753 against 36 and 193).
     const int big_k = (K + kBig - 1) / kBig, big_n = (N + kBig - 1) / kBig;
     const int tiles_k = K / kTile, tiles_n = (N + kTile - 1) / kTile;
     const int64_t rounds_big = ((int64_t)big_k * big_n + cus - 1) / cus, rounds_small = ((int64_t)tiles_k * tiles_n + 2 * cus - 1) / (2 * cus);
