@@ -127,7 +127,10 @@ gwq_status gwq_pack(const void *W_f16, const void *score, int32_t score_dtype,
  * builds the layer's index there, unless P->index holds it already (then that part stays
  * untouched).  The rest holds FP32 partial sums when a launch also splits K, which it does where
  * rows and channels alone give too few tiles to fill the chip; with less than that the call
- * still works, without the split.
+ * still works, without the split.  Where it is expected to be faster the call also keeps a copy
+ * of X there, in the order its MFMAs take it: 2 * K * (M rounded up to 16) bytes, taken from
+ * linear_scratch where twice that fits in it, else from as many bytes more than linear_workspace
+ * (or, in gwq_linear_indexed, than linear_scratch); without them the call works without the copy.
  * For M > 16, and for every M when group < 128, the weights enter the MFMA as FP16 numbers s*(q-z), with s capped
  * at the largest FP16 value for which s*(2^bits-1) is finite (4364 at 4 bits, 9352 at 3; only groups whose range
  * exceeds 65460 reach the cap, which moves such a weight by < 0.1 %); for M <= 16 and group = 128 the scale
@@ -235,7 +238,7 @@ gwq_status gwq_linear_gate_up(const gwq_packed *P_gate, const gwq_packed *P_up, 
  * kernel name with its template arguments, grid, block, LDS bytes, written as text (NUL-terminated, truncated
  * to text_bytes).  Pure host call: reads the structs' scalars (and the tuning hooks), launches nothing, so a
  * benchmark can label its numbers with the kernel that actually ran.  with_scratch: for M > 16, whether the
- * call has the scratch for a K-split launch.  Errors as gwq_linear_batch; M > 16 needs count = 1. */
+ * call has the scratch gwq_layout reports (1), or that and room for a copy of X behind it (2).  Errors as gwq_linear_batch; M > 16 needs count = 1. */
 gwq_status gwq_linear_plan(int32_t count, const gwq_packed *const *P, int32_t M, int32_t with_scratch, char *text,
                            size_t text_bytes);
 
@@ -260,8 +263,10 @@ gwq_status gwq_probe_mfma(int32_t blocks, int32_t iters, void *sink, void *strea
  * where it fits), "decode_pairs" (that kernel with two neighbouring 16-channel tiles per block, which share one copy of X
  * in LDS, for 5 <= M <= 8: 1 never, 2 wherever it fits; by default where the launch has at least four tiles per compute
  * unit), "pack_full_passes" (1: gwq_pack finds the threshold and the per-row counts by passes over all
- * scores even where the short list of candidate keys would do), "gemm_rows" (rows of Y per block of the GEMM: 32, 64, 128 or 256; by default 256 beyond
- * M = 512 and below that the shape a cost model of the launch expects to be fastest).  Unknown keys or
+ * scores even where the short list of candidate keys would do), "gemm_rows" (rows of Y per block of the GEMM: 32, 64, 96, 128, 160, 192 or
+ * 256; by default the shape a cost model of the launch expects to be fastest), "gemm_staged" (1: the GEMM that passes X
+ * through the LDS, 2: the one that reads a copy of X in fragment order, wherever the scratch allows it; by default whichever
+ * the models expect to be faster).  Unknown keys or
  * out-of-range values return GWQ_ERR_UNSUPPORTED. */
 gwq_status gwq_tuning_set(const char *key, int32_t value);
 

@@ -162,7 +162,7 @@ def linear_plan(layers, M, with_scratch=True):
     structs = [P.c_struct() for P in layers]
     parr = (ctypes.POINTER(_Packed) * len(structs))(*[ctypes.pointer(c) for c in structs])
     buf = ctypes.create_string_buffer(256)
-    rc = lib().gwq_linear_plan(len(structs), parr, int(M), int(bool(with_scratch)), buf, 256)
+    rc = lib().gwq_linear_plan(len(structs), parr, int(M), 2 if with_scratch else 0, buf, 256)
     if rc != GWQ_OK:
         raise GwqError(rc, "gwq_linear_plan")
     return buf.value.decode()
@@ -302,10 +302,17 @@ def score(dY, X, out=None, alpha=1.0, beta=0.0, stream=None):
     return out
 
 
+def _room_for_x(P, M, scratch):
+    """Bytes to add to the linear_scratch of gwq_layout so that a call with M > 16 rows can keep a copy of X there."""
+    copy = (M + 15) // 16 * 16 * P.K * 2
+    return copy if M > 16 and 2 * copy > scratch else 0
+
+
 def linear_workspace(P, M, device="cuda"):
     """Scratch tensor gwq_linear needs for this layer at M rows (None for the decode path)."""
     import torch
-    nbytes = layout(P.N, P.K, P.bits, P.group, P.ppm, M)["linear_workspace"]
+    sz = layout(P.N, P.K, P.bits, P.group, P.ppm, M)
+    nbytes = sz["linear_workspace"] + _room_for_x(P, M, sz["linear_scratch"])
     return torch.empty(nbytes, dtype=torch.uint8, device=device) if nbytes else None
 
 
@@ -313,6 +320,7 @@ def linear_scratch(P, M, device="cuda"):
     """Scratch tensor gwq_linear_indexed may use for this layer at M rows (None for the decode path)."""
     import torch
     nbytes = layout(P.N, P.K, P.bits, P.group, P.ppm, M)["linear_scratch"]
+    nbytes += _room_for_x(P, M, nbytes)
     return torch.empty(nbytes, dtype=torch.uint8, device=device) if nbytes else None
 
 

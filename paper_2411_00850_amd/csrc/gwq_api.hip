@@ -37,6 +37,7 @@ hipError_t static_scratch(unsigned char **out)
 // Measurement hooks of gwq_tuning_set: process-wide, read once per call.
 std::atomic<int> g_decode_waves{0};   // 0 = heuristic
 std::atomic<int> g_gemm_ms{0};        // rows of Y per GEMM block; 0 = heuristic
+std::atomic<int> g_gemm_staged{0};    // 1: X through the LDS, 2: never where the scratch allows it; 0 = heuristic
 std::atomic<int> g_decode_stream{0};  // 0 = heuristic, 1 = never the streaming kernel, 2 = wherever it can run
 std::atomic<int> g_decode_tiles{0};   // tiles per block of the streaming kernel; 0 = heuristic
 std::atomic<int> g_decode_lean{0};    // largest M of the kernel that keeps X[M][K] in LDS; 0 = built-in
@@ -44,6 +45,8 @@ std::atomic<int> g_decode_pairs{0};   // two tiles per block in that kernel for 
 std::atomic<int> g_pack_full{0};      // 1: gwq_pack always runs its passes over all scores (never the candidate list)
 
 gwq::DecodeTuning decode_tuning() { return gwq::DecodeTuning{g_decode_waves, g_decode_stream, g_decode_tiles, g_decode_lean, g_decode_pairs}; }
+
+gwq::GemmTuning gemm_tuning() { return gwq::GemmTuning{g_gemm_ms, g_gemm_staged}; }
 
 gwq_status check_shape(int64_t N, int64_t K, int bits, int group, uint32_t ppm)
 {
@@ -211,7 +214,7 @@ gwq_status gwq_linear(const gwq_packed *P, const void *X_f16, int32_t M, void *Y
         e = P->index ? hipSuccess : gwq::launch_gemm_index(*P, workspace, st);
         if (e == hipSuccess)
             e = gwq::launch_gemm(*P, X_f16, M, Y_f16, P->index ? P->index : workspace,
-                                 static_cast<char *>(workspace) + ib, workspace_bytes - ib, g_gemm_ms, st);
+                                 static_cast<char *>(workspace) + ib, workspace_bytes - ib, gemm_tuning(), st);
     }
     return e == hipSuccess ? GWQ_OK : GWQ_ERR_DEVICE;
 }
@@ -233,7 +236,7 @@ gwq_status gwq_linear_bf16(const gwq_packed *P, const void *X_bf16, int32_t M, v
         e = P->index ? hipSuccess : gwq::launch_gemm_index(*P, workspace, st);
         if (e == hipSuccess)
             e = gwq::launch_gemm(*P, X_bf16, M, Y_bf16, P->index ? P->index : workspace,
-                                 static_cast<char *>(workspace) + ib, workspace_bytes - ib, g_gemm_ms, st, nullptr, true);
+                                 static_cast<char *>(workspace) + ib, workspace_bytes - ib, gemm_tuning(), st, nullptr, true);
     }
     return e == hipSuccess ? GWQ_OK : GWQ_ERR_DEVICE;
 }
@@ -257,7 +260,7 @@ gwq_status gwq_linear_indexed(const gwq_packed *P, const void *X_f16, int32_t M,
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipError_t e = M <= 16 ? gwq::launch_decode(1, &P, &X_f16, M, &Y_f16, decode_tuning(), st)
                            : gwq::launch_gemm(*P, X_f16, M, Y_f16, index, scratch, scratch ? scratch_bytes : 0,
-                                              g_gemm_ms, st);
+                                              gemm_tuning(), st);
     return e == hipSuccess ? GWQ_OK : GWQ_ERR_DEVICE;
 }
 
@@ -277,7 +280,7 @@ gwq_status gwq_linear_static(const gwq_packed *P, const void *X_f16, int32_t M, 
     // Same layout as gwq_linear's workspace: the index (when the layer carries none), then the partial sums.
     hipError_t e = P->index ? hipSuccess : gwq::launch_gemm_index(*P, base, st);
     if (e == hipSuccess)
-        e = gwq::launch_gemm(*P, X_f16, M, Y_f16, P->index ? P->index : base, base + ib, sb, g_gemm_ms, st);
+        e = gwq::launch_gemm(*P, X_f16, M, Y_f16, P->index ? P->index : base, base + ib, sb, gemm_tuning(), st);
     return e == hipSuccess ? GWQ_OK : GWQ_ERR_DEVICE;
 }
 
@@ -367,7 +370,7 @@ gwq_status gwq_linear_plan(int32_t count, const gwq_packed *const *P, int32_t M,
     } else {
         // the pointer only says whether partial sums may be used; nothing is launched
         e = gwq::launch_gemm(*P[0], nullptr, M, nullptr, nullptr, with_scratch ? &plan : nullptr,
-                             with_scratch ? gwq::gemm_scratch_bytes(P[0]->N, M) : 0, g_gemm_ms, nullptr, &plan);
+                             with_scratch ? gwq::gemm_scratch_bytes(P[0]->N, M) + (with_scratch == 2 ? gwq::frag_bytes(M, P[0]->K) : 0) : 0, gemm_tuning(), nullptr, &plan);
     }
     if (e != hipSuccess) return GWQ_ERR_DEVICE;
     strncpy(text, plan.text, text_bytes - 1);
@@ -423,8 +426,13 @@ gwq_status gwq_tuning_set(const char *key, int32_t value)
         return GWQ_OK;
     }
     if (!strcmp(key, "gemm_rows")) {
-        if (value != 0 && value != 32 && value != 64 && value != 128 && value != 256) return GWQ_ERR_UNSUPPORTED;
+        if (value != 0 && value != 32 && value != 64 && value != 96 && value != 128 && value != 160 && value != 192 && value != 256) return GWQ_ERR_UNSUPPORTED;
         g_gemm_ms = value;
+        return GWQ_OK;
+    }
+    if (!strcmp(key, "gemm_staged")) {
+        if (value < 0 || value > 2) return GWQ_ERR_UNSUPPORTED;
+        g_gemm_staged = value;
         return GWQ_OK;
     }
     return GWQ_ERR_UNSUPPORTED;

@@ -1,4 +1,6 @@
-// gwq_linear for M > 16 on gfx950: an MFMA GEMM that dequantises the packed weights on the fly.
+// gwq_linear for M > 16 on gfx950: an MFMA GEMM that dequantises the packed weights on the fly.  This kernel needs no scratch
+// and is the faster one for few rows and small matrices; larger calls whose scratch has room for a copy of X take the kernel
+// of gwq_gemm_frag.hip (plan_frag below has the line between them).
 //
 //   Y[m][n] = sum_k X[m][k] * What[n][k],  What = s*(q - z) (Sec. 3.2, Eq. 10) with the FP16
 //   outliers written over their (zero-decoding) codes.
@@ -32,10 +34,10 @@
 // partial sums go to scratch and splitk_reduce_kernel adds them in a fixed order.
 #include <stdio.h>
 
+#include <algorithm>
 #include <type_traits>
 
-#include "gwq_dequant.h"
-#include "gwq_internal.h"
+#include "gwq_gemm_parts.h"
 
 namespace gwq {
 namespace {
@@ -113,37 +115,6 @@ __global__ __launch_bounds__(256) void fine_index_kernel(const uint16_t *__restr
     fine[i] = (sc < scale_cap ? sc : scale_cap) | (uint32_t)zeros[g] << 16;
 }
 
-// ------------------------------------------------------------------------------------------------
-template <int BITS> struct SlotRegs;
-template <> struct SlotRegs<4> { uint32_t w[4]; };
-template <> struct SlotRegs<3> { uint32_t w[3], fourth; };    // fourth: the word after the slot's three (slot 3: the tail word)
-
-template <int BITS> __device__ inline void load_slot(SlotRegs<BITS> &r, const uint32_t *group, int slot);
-template <> __device__ inline void load_slot<4>(SlotRegs<4> &r, const uint32_t *group, int slot)
-{
-    const uint4 v = *reinterpret_cast<const uint4 *>(group + 4 * slot);
-    r.w[0] = v.x; r.w[1] = v.y; r.w[2] = v.z; r.w[3] = v.w;
-}
-template <> __device__ inline void load_slot<3>(SlotRegs<3> &r, const uint32_t *group, int slot)
-{
-    // one 16-byte load at 4-byte alignment; it stays inside the group's 13 words for every slot
-    const U128a4 v = *reinterpret_cast<const U128a4 *>(group + 3 * slot);
-    r.w[0] = v.x; r.w[1] = v.y; r.w[2] = v.z; r.fourth = v.w;
-}
-
-// A 16-bit load that is complete when it returns, invisible to the compiler's bookkeeping of
-// outstanding loads: for the rare path inside the staging loop, whose loads would otherwise make
-// the compiler wait for every prefetch in flight at each trip of the loop.
-__device__ inline uint32_t load_u16_now(const uint16_t *p)
-{
-    uint32_t v;
-    asm volatile("global_load_ushort %0, %1, off\n\ts_waitcnt vmcnt(0)" : "=v"(v) : "v"(p) : "memory");
-    return v;
-}
-
-// A load of 8 bytes at 2-byte alignment (gfx950 global memory takes unaligned addresses).
-struct __attribute__((packed, aligned(2))) U64a2 { uint32_t lo, hi; };
-
 // What producer thread (n, h) fetches for one group of channel n: its two slots (h and 2 + h: columns
 // 32h .. 32h+31 of the group's two steps), entries 4h .. 4h+3 of the group's first eight outliers
 // as packed 16-bit pairs, and the record of the group after it.
@@ -154,43 +125,6 @@ template <int BITS> struct GroupRegs {
     uint32_t next_scale_zero;
     uint32_t sub[4];                                    // small groups only: scale | zero << 16 of the halves of the two slots
 };
-
-// Fragment j (8 codes -> 8 FP16 values s*(q - z)) of a slot.
-__device__ inline u32x4 dequant_frag(const SlotRegs<4> &r, int j, uint32_t z, uint32_t s2, const DecodeConsts &d)
-{
-    const ZeroConsts<4> c(z);
-    u32x4 f = decode_word4(r.w[j], c, d);
-    f.x = pk_mul(f.x, s2); f.y = pk_mul(f.y, s2); f.z = pk_mul(f.z, s2); f.w = pk_mul(f.w, s2);
-    return f;
-}
-__device__ inline void dequant_all(const SlotRegs<3> &r, uint32_t tail_pair, uint32_t z, uint32_t s2, const DecodeConsts &d,
-                                   u32x4 f[4])
-{
-    decode_slot3(r.w, tail_pair, z, d, f);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        f[j].x = pk_mul(f[j].x, s2); f[j].y = pk_mul(f[j].y, s2);
-        f[j].z = pk_mul(f[j].z, s2); f[j].w = pk_mul(f[j].w, s2);
-    }
-}
-
-// bfloat16 operands: the eight exact FP16 integers q - z of a fragment times the scale in FP32, rounded once to
-// bfloat16 (round to nearest even).
-__device__ inline uint32_t scale_pair_bf16(uint32_t h2, float s)
-{
-    const half2v h = __builtin_bit_cast(half2v, h2);
-    const __bf16 lo = (__bf16)((float)h.x * s), hi = (__bf16)((float)h.y * s);
-    return (uint32_t)__builtin_bit_cast(uint16_t, lo) | (uint32_t)__builtin_bit_cast(uint16_t, hi) << 16;
-}
-__device__ inline u32x4 scale_frag_bf16(u32x4 f, float s)
-{
-    return u32x4{scale_pair_bf16(f.x, s), scale_pair_bf16(f.y, s), scale_pair_bf16(f.z, s), scale_pair_bf16(f.w, s)};
-}
-// An FP16 bit pattern as the nearest bfloat16's (the stored outliers, for bfloat16 MFMA operands).
-__device__ inline uint16_t half_bits_to_bf16_bits(uint32_t h)
-{
-    return __builtin_bit_cast(uint16_t, (__bf16)(float)__builtin_bit_cast(_Float16, (uint16_t)h));
-}
 
 // X rows lie in LDS 128 bytes apart, so the 16-byte chunk c of row r is kept at position
 // c ^ x_swizzle(r): the 16 rows a fragment read touches per cycle then hit 16 different bank groups,
@@ -215,7 +149,7 @@ template <int N> __device__ inline void wait_vm() { asm volatile("s_waitcnt vmcn
 // BF16: X and Y are bfloat16 and the MFMAs take bfloat16 operands: the producers round s * (q - z), formed in FP32, and
 // the stored outliers to bfloat16 (groups of 128 only).
 template <int BITS, int MSW, int WN, int WM, bool FINE, bool BF16>
-__global__ __launch_bounds__(kThreads) void gemm_kernel(const uint32_t *__restrict__ qweight,
+__global__ __launch_bounds__(kThreads) void gemm_kernel_staged(const uint32_t *__restrict__ qweight,
                                                         const uint16_t *__restrict__ col_idx,
                                                         const uint16_t *__restrict__ out_val,
                                                         const GroupRecord *__restrict__ rec,
@@ -578,6 +512,13 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restr
     Y[i] = (act_t)sum;
 }
 
+hipError_t launch_splitk_reduce(const float *partial, void *Y, size_t count, int splits, bool bf16, hipStream_t st)
+{
+    if (bf16) splitk_reduce_kernel<__bf16><<<(unsigned)((count + 255) / 256), 256, 0, st>>>(partial, static_cast<__bf16 *>(Y), count, splits);
+    else splitk_reduce_kernel<_Float16><<<(unsigned)((count + 255) / 256), 256, 0, st>>>(partial, static_cast<_Float16 *>(Y), count, splits);
+    return hipGetLastError();
+}
+
 // How many ways K is split for a launch of `tiles` tiles over rows of `gpr` groups: as many as keep
 // the block count within the CU count, at least two groups each, at most kMaxSplits.
 // kCUs is the compute-unit count of the MI355X, which the scratch size reported by gwq_layout (a pure host
@@ -641,6 +582,61 @@ int choose_rows(int M, int N, int K, bool have_scratch)
     return best;
 }
 
+// Whether the GEMM with X in fragment order (gwq_gemm_frag.hip) takes a call, with which tiles, and where its scratch lies.
+struct FragPlan {
+    int rows, splits, split_groups;                     // rows == 0: the kernel above
+    size_t frag_at, partial_at;
+};
+// Both kernels by models fitted to the same 1922 launches (340 matrices with N = 257 .. 30000, K = 1024 .. 28672, M = 17 .. 3000,
+// 3 and 4 bits, all group sizes and both types; rms error 7 %): rounds of blocks over the chip, each a start and its
+// groups, the sums of a K split, and for this kernel the copy of X, a launch of its own, for the other one what a full
+// chip adds.  The copy and the longer start make it lose on small matrices and few rows (us, the other kernel first:
+// 4096 x 4096, M = 64: 14.2, 16.6; 4096 x 11008, M = 64: 22.3, 24.1); it wins where blocks walk many groups or the tile
+// fits M better (28672 x 8192, M = 64: 79, 61; M = 301: 247, 166; M = 1024: 500, 429; 11008 x 4096, M = 301: 57, 43; M = 2048:
+// 199, 175).  The 5 % asked for keep the models' errors from choosing it where it loses: over the 340 matrices the choice is
+// 5.1 % faster than the other kernel alone, the best one 5.4 %.  Tiles of 96 rows and less only up to four along m: beyond,
+// their X no longer stays in the L2 between blocks and arrives late (803 x 2560, M = 1695: 39 us with 64 rows, 27 with the
+// other kernel).
+constexpr float kBf16StagedUs = 0.1f, kBf16FragUs = 0.2f;      // per step, per group: what rounding weights to bfloat16 adds
+constexpr ShapeCost kFragCost[7] = {{32, 0.66f, 5.3f}, {64, 0.75f, 5.3f}, {96, 0.85f, 5.3f}, {128, 0.96f, 5.3f},
+                                    {160, 1.11f, 5.3f}, {192, 1.28f, 5.3f}, {256, 1.45f, 5.3f}};  // per group
+FragPlan plan_frag(int M, int N, int K, bool fine, bool bf16, size_t scratch_bytes, const GemmTuning &tune, int staged_rows)
+{
+    const int gpr = K / kGroup, tiles_n = (N + kBN - 1) / kBN, cus = launch_cus();
+    FragPlan plan{0, 1, gpr, 0, 0};
+    const size_t usual = gemm_scratch_bytes(N, M), frag = frag_bytes(M, K);
+    if (scratch_bytes < usual) return plan;
+    size_t room = usual;                                // for partial sums
+    if (2 * frag <= usual) plan.partial_at = frag, room -= frag;
+    else if (scratch_bytes >= usual + frag) plan.frag_at = usual;
+    else return plan;
+    float best_us = 1e30f;
+    if (tune.staged != 2 && !tune.rows) {
+        const int tiles = (M + staged_rows - 1) / staged_rows * tiles_n;
+        const SplitPlan sp = plan_split(tiles, gpr, true, cus);
+        const int blocks = tiles * sp.splits, rounds = (blocks + cus - 1) / cus, steps = 2 * sp.split_groups;
+        float step_us = staged_rows <= 64 ? 0.445f : staged_rows == 128 ? 0.50f : 0.60f;
+        step_us += (fine && staged_rows <= 64 ? 0.126f : 0.f) + (bf16 ? kBf16StagedUs : 0.f) + 0.0002f * std::min(steps, 128);
+        float us = rounds * (7.f + steps * step_us) - 2.3f + 0.0017f * (float)blocks / cus * steps * staged_rows;
+        if (sp.splits > 1) us += 2.7f + 0.44f * (4e-6f * sp.splits * M * N);
+        best_us = 0.95f * us;
+    }
+    const int most = (int)std::min<size_t>(kMaxSplits, room / ((size_t)M * N * sizeof(float)));
+    for (const ShapeCost &c : kFragCost) {
+        if (tune.rows ? c.rows != tune.rows : (c.rows > 32 && c.rows >= 2 * M) || (c.rows < 128 && M > 4 * c.rows)) continue;
+        const int tiles = (M + c.rows - 1) / c.rows * tiles_n;
+        int splits = tiles >= kSplitBelowTiles ? 1 : std::max(1, std::min({most, cus / tiles, gpr / 2}));
+        const int split_groups = (gpr + splits - 1) / splits;
+        splits = (gpr + split_groups - 1) / split_groups;               // no empty split
+        const int rounds = (tiles * splits + cus - 1) / cus;
+        const float group_us = c.step_us + (fine ? 0.07f : 0.f) + (bf16 ? kBf16FragUs : 0.f);
+        float us = 4.1f + 0.58e-6f * M * K + rounds * (c.block_us + split_groups * group_us);
+        if (splits > 1) us += 2.3f + 0.6f * (4e-6f * splits * M * N);
+        if (us < best_us) best_us = us, plan.rows = c.rows, plan.splits = splits, plan.split_groups = split_groups;
+    }
+    return plan;
+}
+
 template <int BITS, int MSW, int WN, int WM, bool FINE, bool BF16>
 hipError_t launch_ms(const gwq_packed &P, const void *X, int M, void *Y, const GroupRecord *rec, float *partial,
                      size_t partial_bytes, hipStream_t st, PlanText *describe)
@@ -654,27 +650,24 @@ hipError_t launch_ms(const gwq_packed &P, const void *X, int M, void *Y, const G
     if (splits == 1) partial = nullptr;
     const size_t lds = ((size_t)3 * BM * kBK + (size_t)3 * kBN * kLd) * sizeof(_Float16);
     if (describe) {
-        snprintf(describe->text, sizeof(describe->text), "gemm_kernel<%d,%d,%d,%d,%s,%s> tile %dx%d grid %d block %d lds %zu k_splits %d",
+        snprintf(describe->text, sizeof(describe->text), "gemm_kernel_staged<%d,%d,%d,%d,%s,%s> tile %dx%d grid %d block %d lds %zu k_splits %d",
                  BITS, MSW, WN, WM, FINE ? "true" : "false", BF16 ? "true" : "false", BM, kBN, tiles_m * tiles_n * splits, kThreads, lds, splits);
         return hipSuccess;
     }
     static std::atomic<uint32_t> lds_allowed{0};        // per instantiation
     {
-        hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_kernel<BITS, MSW, WN, WM, FINE, BF16>), (int)lds, lds_allowed);
+        hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_kernel_staged<BITS, MSW, WN, WM, FINE, BF16>), (int)lds, lds_allowed);
         if (e != hipSuccess) return e;
     }
     // The half-slot pairs of a layer with small groups follow the records.
     const uint32_t *fine = reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(rec) + index_record_bytes(P.N, P.K));
-    gemm_kernel<BITS, MSW, WN, WM, FINE, BF16><<<tiles_m * tiles_n * splits, kThreads, lds, st>>>(
+    gemm_kernel_staged<BITS, MSW, WN, WM, FINE, BF16><<<tiles_m * tiles_n * splits, kThreads, lds, st>>>(
         P.qweight, P.col_idx, P.out_val, rec, fine, static_cast<const _Float16 *>(X),
         static_cast<_Float16 *>(Y), partial, split_groups, P.N, P.K, M, tiles_m, tiles_n,
         P.n_outliers > 0 ? (int)P.n_outliers - 1 : 0);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || splits == 1) return e;
-    const size_t count = (size_t)M * P.N;
-    if (BF16) splitk_reduce_kernel<__bf16><<<(unsigned)((count + 255) / 256), 256, 0, st>>>(partial, static_cast<__bf16 *>(Y), count, splits);
-    else splitk_reduce_kernel<_Float16><<<(unsigned)((count + 255) / 256), 256, 0, st>>>(partial, static_cast<_Float16 *>(Y), count, splits);
-    return hipGetLastError();
+    return launch_splitk_reduce(partial, Y, (size_t)M * P.N, splits, BF16, st);
 }
 
 }  // namespace
@@ -713,16 +706,28 @@ hipError_t launch_gemm_index(const gwq_packed &P, void *workspace, hipStream_t s
 }
 
 hipError_t launch_gemm(const gwq_packed &P, const void *X, int M, void *Y, const void *index, void *scratch,
-                       size_t scratch_bytes, int ms_override, hipStream_t st, PlanText *describe, bool bf16)
+                       size_t scratch_bytes, const GemmTuning &tune, hipStream_t st, PlanText *describe, bool bf16)
 {
     if (bf16 && P.group != kGroup) return hipErrorNotSupported;
     const GroupRecord *rec = static_cast<const GroupRecord *>(index);
     float *part = static_cast<float *>(scratch);
-    // Rows per tile (the override is in rows): 256 (consumer waves 4 x 2, 64 x 64 each), 128 (4 x 2, 32 x 64
+    // Rows per tile of the kernel that stages X in the LDS: 256 (consumer waves 4 x 2, 64 x 64 each), 128 (4 x 2, 32 x 64
     // each), 64 (2 x 4, 32 x 32 each) or 32 (1 x 4, four consumer waves idle).  In the small shapes the
     // weights a block stages are read from LDS by two rows of waves, or one, instead of four, and the
     // LDS is what bounds a step.
-    const int rows = ms_override ? ms_override : choose_rows(M, (int)P.N, (int)P.K, part != nullptr);
+    const int wanted = tune.rows > 128 ? 256 : tune.rows == 96 ? 128 : tune.rows;
+    const int rows = wanted ? wanted : choose_rows(M, (int)P.N, (int)P.K, part != nullptr);
+    if (tune.staged != 1 && part) {
+        const FragPlan plan = plan_frag(M, (int)P.N, (int)P.K, P.group != kGroup, bf16, scratch_bytes, tune, rows);
+        if (plan.rows) {
+            char *base = static_cast<char *>(scratch);
+            float *sums = reinterpret_cast<float *>(base + plan.partial_at);
+            hipError_t e = launch_gemm_frag(P, X, M, Y, index, base + plan.frag_at, sums, plan.rows, plan.splits, plan.split_groups, st,
+                                            describe, bf16);
+            if (e != hipSuccess || plan.splits == 1 || describe) return e;
+            return launch_splitk_reduce(sums, Y, (size_t)M * P.N, plan.splits, bf16, st);
+        }
+    }
     const int shape = rows == 256 ? 2 : rows == 128 ? 1 : rows == 64 ? 0 : 3;
 #define GWQ_GEMM(B, F, A) \
     return shape == 2   ? launch_ms<B, 2, 2, 4, F, A>(P, X, M, Y, rec, part, scratch_bytes, st, describe) \

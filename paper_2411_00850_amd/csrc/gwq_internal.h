@@ -83,15 +83,25 @@ struct PlanText {
 };
 hipError_t launch_decode(int count, const gwq_packed *const *P, const void *const *X, int M, void *const *Y,
                          const DecodeTuning &tune, hipStream_t stream, PlanText *describe = nullptr);
+// Measurement overrides of the GEMM launch (0 = built-in choice): rows of Y per block; X through the LDS (1: always, 2: never
+// where the scratch allows it).
+struct GemmTuning {
+    int rows, staged;
+};
 // index: gemm_index_bytes(N, K, group) bytes, 16-byte aligned (one record per channel and block of 128 codes:
 // index of the block's first outlier, scale, zero point; for groups below 128 also a scale / zero-point pair
 // per 16 columns; a multiple of 256 bytes).  scratch: gemm_scratch_bytes(N, M_max)
-// bytes for the partial sums of launches that also split K (may be NULL: then K is never split).
+// bytes for the partial sums of launches that also split K and, where it fits, a copy of X (may be NULL: then neither).
 size_t gemm_index_bytes(int64_t N, int64_t K, int group);
 size_t gemm_scratch_bytes(int64_t N, int64_t M_max);
 hipError_t launch_gemm_index(const gwq_packed &P, void *index, hipStream_t stream);        // fills the records
+// The GEMM whose X operands come from memory in fragment order (gwq_gemm_frag.hip): frag = frag_bytes(M, K) bytes for that
+// copy of X, 16-byte aligned; rows = 32, 64, 96, 128, 160, 192 or 256 rows of Y per block; partial for splits > 1.
+size_t frag_bytes(int64_t M, int64_t K);
+hipError_t launch_gemm_frag(const gwq_packed &P, const void *X, int M, void *Y, const void *index, void *frag, float *partial,
+                            int rows, int splits, int split_groups, hipStream_t stream, PlanText *describe, bool bf16);
 hipError_t launch_gemm(const gwq_packed &P, const void *X, int M, void *Y, const void *index, void *scratch,
-                       size_t scratch_bytes, int ms_override, hipStream_t stream,
+                       size_t scratch_bytes, const GemmTuning &tune, hipStream_t stream,
                        PlanText *describe = nullptr, bool bf16 = false);                   // reads them; bf16: X, Y bfloat16
 
 // workspace: quality_workspace_bytes(N) bytes, 8-byte aligned (one partial result per channel); out: 3 doubles.

@@ -1,0 +1,133 @@
+"""The GEMM with X in fragment order (csrc/gwq_gemm_frag.hip) at its edges, and the rule that chooses between it and the GEMM
+that stages X in the LDS.  Reference: the oracle's fp64 product, at the tolerance of every linear test (gpu_helpers); the two
+kernels multiply the same FP16 operands with FP32 sums, so where K is not split they may differ by the order of those sums
+alone: by 2 * K * 2^-24 of the sum of magnitudes, which one FP16 rounding of the result (2^-11) then covers."""
+import numpy as np
+import pytest
+
+import gwq_synth as gs
+from oracle import gwq_oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+ROWS = [32, 64, 96, 128, 160, 192, 256]
+
+
+def _pack(seed, N, K, bits, ppm=10000, group=128, clustered=False):
+    rng = np.random.default_rng(seed)
+    W = gs.weight(N, K, rng, planted_cols=2)
+    S = gs.score_from_weight(W, rng)
+    if clustered:                                        # nine in ten outliers in one eighth of the rows and columns
+        S[: max(1, N // 8), : K // 8] += np.float32(10.0)
+    return orc.pack(W, S, bits, ppm, group), rng
+
+
+def _with(rows, staged, call):
+    import paper_2411_00850_amd as gwq
+    gwq.tuning_set("gemm_rows", rows)
+    gwq.tuning_set("gemm_staged", staged)
+    try:
+        return call()
+    finally:
+        gwq.tuning_set("gemm_rows", 0)
+        gwq.tuning_set("gemm_staged", 0)
+
+
+@pytest.mark.parametrize("bits,group", [(4, 128), (3, 128), (4, 16), (3, 32)])
+@pytest.mark.parametrize("rows", ROWS)
+def test_tiles_at_their_edges(bits, group, rows):
+    """Every tile height with ragged M (one row over a tile, one short of one, a multiple of 16 and not) and N (odd, one
+    channel over a tile), and K of one group, of one window of eight groups and one more, and of several, split and not."""
+    import paper_2411_00850_amd as gwq
+    from gpu_helpers import assert_close, to_gpu, upload_packed
+    for N, K, M in ((129, 128, rows + 1), (131, 1152, max(17, rows - 1)), (200, 2176, 48), (1601, 1024, 17), (64, 3200, 2 * rows + 33)):
+        P, rng = _pack(rows + N + bits, N, K, bits, group=group)
+        X = gs.activations(M, K, rng, hot_frac=0.01)
+        D, Xd = upload_packed(P), to_gpu(X)
+        plan = _with(rows, 2, lambda: gwq.linear_plan(D, M))
+        assert plan.startswith(("gemm_kernel<", "gemm_kernel_rows<")) and f" tile {rows}x128 " in plan
+        Y = _with(rows, 2, lambda: gwq.linear(D, Xd)).cpu().numpy()
+        assert_close(Y, orc.linear_f64(P, X), f"frag rows={rows} N={N} K={K} M={M} bits={bits} group={group}")
+
+
+@pytest.mark.parametrize("bits", [4, 3])
+@pytest.mark.parametrize("rows", ROWS)
+def test_bf16_tiles(bits, rows):
+    import torch
+    import paper_2411_00850_amd as gwq
+    from gpu_helpers import upload_packed
+    N, K, M = 260, 1280, rows + 7
+    P, rng = _pack(rows + bits, N, K, bits)
+    x = torch.from_numpy(gs.activations(M, K, rng)).to(torch.bfloat16)
+    Y = _with(rows, 2, lambda: gwq.linear_bf16(upload_packed(P), x.cuda())).cpu().double().numpy()
+    ref = orc.linear_f64_x(P, x.double().numpy())
+    # weights rounded to bfloat16 (relative 2^-9, rms 2^-9 / sqrt(3), over a sum of many) and the result's own rounding
+    assert np.linalg.norm(Y - ref) <= (2e-3 + 2.0 ** -8 / 3 ** 0.5) * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("rows", [32, 160, 256])
+@pytest.mark.parametrize("ppm,clustered", [(0, False), (10000, True), (200000, False), (1000000, False)])
+def test_outliers_beyond_a_group_or_a_window(rows, ppm, clustered):
+    """No outliers; more than eight in a group and more than 32 in eight groups, everywhere or in some rows only; nothing else."""
+    from gpu_helpers import assert_close, to_gpu, upload_packed
+    import paper_2411_00850_amd as gwq
+    N, K, M = 150, 2304, 40
+    P, rng = _pack(ppm + rows, N, K, 4, ppm=ppm, clustered=clustered)
+    X = gs.activations(M, K, rng)
+    Y = _with(rows, 2, lambda: gwq.linear(upload_packed(P), to_gpu(X))).cpu().numpy()
+    assert_close(Y, orc.linear_f64(P, X), f"frag rows={rows} ppm={ppm} clustered={clustered}")
+
+
+@pytest.mark.parametrize("rows", [32, 64, 128, 256])
+@pytest.mark.parametrize("bits,group", [(4, 128), (3, 16)])
+def test_staged_kernel_still_takes_every_shape(rows, bits, group):
+    """The kernel that stages X in the LDS, which calls without scratch take, against the oracle and the other kernel."""
+    import paper_2411_00850_amd as gwq
+    from gpu_helpers import assert_close, to_gpu, upload_packed
+    for N, K, M in ((200, 1408, 100), (131, 512, 300), (72, 2048, 17)):
+        P, rng = _pack(rows + N + M + bits, N, K, bits, group=group)
+        X = gs.activations(M, K, rng, hot_frac=0.01)
+        D, Xd = upload_packed(P), to_gpu(X)
+        a = _with(rows, 1, lambda: gwq.linear(D, Xd)).cpu().numpy()
+        assert_close(a, orc.linear_f64(P, X), f"staged rows={rows} N={N} K={K} M={M} bits={bits}")
+        index = gwq.linear_index(D)
+        whole = _with(rows, 0, lambda: gwq.linear(D, Xd, index=index, scratch=None)).cpu().numpy().astype(np.float64)
+        b = _with(rows, 2, lambda: gwq.linear(D, Xd)).cpu().numpy().astype(np.float64)
+        assert np.abs(whole - b).max() <= 2.0 ** -10 * np.abs(b).max() + 1e-6
+
+
+@pytest.mark.parametrize("short", [0, 16, "copy"])
+def test_scratch_limits(short):
+    """Scratch of exactly what gwq_layout reports, 16 bytes less, and so little that X has no room: always accepted, always
+    right; the copy of X stays inside what was passed."""
+    import torch
+    import paper_2411_00850_amd as gwq
+    from gpu_helpers import assert_close, to_gpu, upload_packed
+    for N, K, M in ((600, 2048, 200), (40, 16384, 520)):                # the copy of X within half of linear_scratch; beyond it
+        P, rng = _pack(N, N, K, 4)
+        X = gs.activations(M, K, rng)
+        D, Xd = upload_packed(P), to_gpu(X)
+        usual = gwq.layout(N, K, 4, M_max=M)["linear_scratch"]
+        copy = (M + 15) // 16 * 16 * K * 2
+        assert (2 * copy <= usual) == (N == 600)
+        size = usual - short if short != "copy" else usual + copy
+        buf = torch.full((size + 4096,), 0x3C, dtype=torch.uint8, device="cuda")
+        Y = _with(0, 2, lambda: gwq.linear(D, Xd, index=gwq.linear_index(D), scratch=buf[:size])).cpu().numpy()
+        assert_close(Y, orc.linear_f64(P, X), f"scratch {size} N={N} K={K} M={M}")
+        assert bool((buf[size:] == 0x3C).all())
+
+
+def test_nonfinite_activations_stay_in_their_rows():
+    import torch
+    import paper_2411_00850_amd as gwq
+    from gpu_helpers import to_gpu, upload_packed
+    N, K, M = 140, 640, 50
+    P, rng = _pack(5, N, K, 4)
+    X = gs.activations(M, K, rng)
+    D = upload_packed(P)
+    good = _with(64, 2, lambda: gwq.linear(D, to_gpu(X)))
+    bad = X.copy()
+    bad[7, 3], bad[M - 1, K - 1] = np.inf, np.nan
+    got = _with(64, 2, lambda: gwq.linear(D, to_gpu(bad)))
+    keep = [m for m in range(M) if m not in (7, M - 1)]
+    assert torch.equal(got[keep], good[keep]) and not torch.isfinite(got[M - 1]).any() and not torch.isfinite(got[7]).all()
