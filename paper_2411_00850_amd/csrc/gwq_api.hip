@@ -332,7 +332,10 @@ gwq_status gwq_linear_gate_up(const gwq_packed *P_gate, const gwq_packed *P_up, 
     hipStream_t st = static_cast<hipStream_t>(stream);
     const gwq_packed *p[2] = {P_gate, P_up};
     const void *x[2] = {X_f16, X_f16};
-    if (M <= 4) {                                       // one launch: the second run of each block writes H
+    const size_t each = (size_t)M * P_gate->N * 2;
+    const bool room = workspace && workspace_bytes >= 2 * each;
+    if ((M > 4 || P_gate->group != gwq::kGroup) && !room) return GWQ_ERR_WORKSPACE;
+    {                                                   // one launch that writes H, where a kernel has it
         void *y[2] = {H_f16, H_f16};
         gwq::DecodeTuning t = decode_tuning();
         t.gated_pairs = true;
@@ -340,9 +343,8 @@ gwq_status gwq_linear_gate_up(const gwq_packed *P_gate, const gwq_packed *P_up, 
         if (e == hipSuccess) return GWQ_OK;
         if (e != hipErrorNotSupported) return GWQ_ERR_DEVICE;
     }
-    // Larger batches (and rows too long for the kernel above): the two products into the workspace, then H.
-    const size_t each = (size_t)M * P_gate->N * 2;
-    if (!workspace || workspace_bytes < 2 * each) return GWQ_ERR_WORKSPACE;
+    // Rows too long for those kernels, and more than four rows with groups below 128: the two products, then H.
+    if (!room) return GWQ_ERR_WORKSPACE;
     void *y[2] = {workspace, static_cast<char *>(workspace) + each};
     hipError_t e = gwq::launch_decode(2, p, x, M, y, decode_tuning(), st);
     if (e == hipSuccess) e = gwq::launch_silu_mul(y[0], y[1], H_f16, (size_t)M * P_gate->N, st);

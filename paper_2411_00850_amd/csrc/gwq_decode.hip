@@ -223,7 +223,8 @@ struct DecodeBatch {
 //
 // MODE 0 stores Y.  MODE 1 and 2 are the two halves of the gated pair H = silu(X Wg^T) * (X Wu^T): the
 // first run keeps its FP32 sums in LDS (behind the partial sums), the second combines them with its own
-// and stores H, so the pair costs one launch and never writes the two products.
+// and stores H, so the pair costs one launch and never writes the two products.  MODE 3 (with PAIR) is the gated pair
+// beyond four rows: the block's two sets of waves take the same tile of gate and of up, and the partial sums of both meet.
 __device__ inline float silu(float x)
 {
     // x * sigmoid(x); exp2 and the reciprocal are the hardware's approximations (about 1 ulp each)
@@ -241,12 +242,17 @@ __device__ inline float silu(float x)
 template <int BITS, int U, int MS, int MODE, bool FINE = false, bool BF16 = false, bool PAIR = false>
 __device__ __forceinline__ void decode_small_body(const DecodeBatch &batch, const int layer)
 {
-    static_assert(!PAIR || (MODE == 0 && !FINE && !BF16 && MS > 4), "paired tiles: plain products of more than four rows");
+    constexpr bool GATED = MODE == 3;
+    static_assert(!PAIR || ((MODE == 0 || GATED) && !FINE && !BF16 && MS > 4), "paired tiles: FP16 products of more than four rows");
+    static_assert(PAIR || !GATED, "the two sets of a gated block");
     static_assert(!FINE || MODE == 0, "gated pairs: groups of 128 only");
     static_assert(!BF16 || (MODE == 0 && !FINE), "bfloat16 activations: plain products with groups of 128 only");
     typedef std::conditional_t<BF16, __bf16, _Float16> act_t;          // X and Y; both 16 bits wide
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-    const DecodeProblem &pr = batch.p[layer];
+    const int block_wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int nwaves = PAIR ? batch.nwaves / 2 : batch.nwaves, nthreads = nwaves * 64;
+    const int set = PAIR ? (int)(block_wave >= nwaves) : 0;
+    const DecodeProblem &pr = batch.p[layer + (GATED ? set : 0)];
     const int N = pr.N, K = pr.K;
     const uint32_t *__restrict__ qweight = pr.qweight;
     const uint16_t *__restrict__ scales = pr.scales;
@@ -262,20 +268,17 @@ __device__ __forceinline__ void decode_small_body(const DecodeBatch &batch, cons
     // keeps the compiler from moving the other loads behind the branch on N).
     asm volatile("" ::"s"(qweight), "s"(scales), "s"(zeros), "s"(row_ptr), "s"(col_idx), "s"(out_val), "s"(X), "s"(Y),
                  "s"(K), "s"(sc_last_vec), "s"(zp_last_vec), "s"(csr_last_vec), "s"(shift));
-    if ((int)blockIdx.x * (PAIR ? 32 : 16) >= N) return;    // the grid is as wide as the largest layer
+    if ((int)blockIdx.x * (PAIR && !GATED ? 32 : 16) >= N) return;      // the grid is as wide as the largest layer
 
     // PAIR: the block's waves form two sets that work on two neighbouring 16-channel tiles with one copy of X
     // between them (each set stages every second row of it): half the reads of X per tile, which is what rows
     // five to eight cost over fewer.  Below, tid, wave, nwaves and nthreads are those of the set; everything
     // per tile in LDS exists once per set.  A set whose tile lies beyond N works on the last tile and stores nothing.
     const int lane = threadIdx.x & 63;
-    const int block_wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int nwaves = PAIR ? batch.nwaves / 2 : batch.nwaves, nthreads = nwaves * 64;
-    const int set = PAIR ? block_wave / nwaves : 0;
     const int wave = block_wave - set * nwaves;
     const int tid = (int)threadIdx.x - set * nthreads;
-    const int tile = PAIR ? 2 * (int)blockIdx.x + set : (int)blockIdx.x;
-    const bool tile_live = !PAIR || tile * 16 < N;
+    const int tile = PAIR && !GATED ? 2 * (int)blockIdx.x + set : (int)blockIdx.x;
+    const bool tile_live = !PAIR || GATED || tile * 16 < N;
     const int block = tile_live ? tile : (N - 1) / 16;
     GWQ_TS_DECL;
     GWQ_TS(0);                                          // descriptor has arrived
@@ -552,6 +555,22 @@ __device__ __forceinline__ void decode_small_body(const DecodeBatch &batch, cons
         }
         __syncthreads();
         GWQ_TS(5);
+        if constexpr (GATED) {
+            const float *gate = reinterpret_cast<const float *>(lds_raw + red_off - (uint32_t)set * set_bytes);
+            const float *up = reinterpret_cast<const float *>(lds_raw + red_off + (uint32_t)(1 - set) * set_bytes);
+            for (int idx = threadIdx.x; idx < MS * 16; idx += 2 * nthreads) {
+                const int e = idx >> 4, c = idx & 15;
+                float g = 0.f, u = 0.f;
+                for (int w = 0; w < nwaves; ++w) {
+                    g += gate[(w * MS + e) * 16 + c];
+                    u += up[(w * MS + e) * 16 + c];
+                }
+                if (row0 + c < N) Y[(size_t)e * N + row0 + c] = (act_t)(silu(g) * u);   // both layers' Y is H
+            }
+            GWQ_TS(6);
+            GWQ_TS_FLUSH(wave == 0, wave == nwaves - 1);
+            return;
+        }
         for (int idx = tid; idx < MS * 16; idx += nthreads) {
             const int e = idx >> 4, c = idx & 15;
             float sum = 0.f;
@@ -608,6 +627,14 @@ __global__ __launch_bounds__(1024) void decode_small_gate_up_kernel(const Decode
     decode_small_body<BITS, U, MS, 1>(batch, 2 * blockIdx.y);
     __syncthreads();
     decode_small_body<BITS, U, MS, 2>(batch, 2 * blockIdx.y + 1);
+}
+
+// Beyond four rows: one set of waves for gate, one for up, on one copy of X (MODE 3).  us, against two products and a kernel
+// that combines them, 4 bits, M = 8: 11008 x 4096 16.0 and 17.8, 4096 x 2048 5.9 and 7.9, 28672 x 1024 11.9 and 13.9.
+template <int BITS, int U, int MS>
+__global__ __launch_bounds__(1024) void decode_small_gate_up_pair_kernel(const DecodeBatch batch)
+{
+    decode_small_body<BITS, U, MS, 3, false, false, true>(batch, 2 * blockIdx.y);
 }
 
 // ---- any M <= 16, X staged through LDS in chunks of K: the wide kernel ---------------------------
@@ -1052,29 +1079,37 @@ template <int BITS> struct TileRegs {
     u32x4 seg_col, seg_val;                             // this thread's eight entries of the tile's segment
 };
 
-template <int BITS, int MR>
+// GATED: layers 2y and 2y + 1 of the batch are gate and up of a gated pair (one N, one K, one X).  A block takes the tiles of
+// both in turn, `tiles_per_block` of each; the threads that add a gate tile's partial sums keep them in a register, add the
+// up tile's one step later and store H = silu(gate) * up.
+template <int BITS, int MR, bool GATED = false>
 __global__ __launch_bounds__(512) void decode_stream_kernel(const DecodeBatch batch, const int tiles_per_block,
                                                             const int ent_cap)
 {
     constexpr int U = kStreamU, RB = MR / 4, SPLIT = 4 / RB;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-    const DecodeProblem &pr = batch.p[blockIdx.y];
+    const DecodeProblem &pr = batch.p[GATED ? 2 * blockIdx.y : blockIdx.y];
     const int N = pr.N, K = pr.K;
-    const uint32_t *__restrict__ qweight = pr.qweight;
-    const uint16_t *__restrict__ scales = pr.scales;
-    const uint8_t *__restrict__ zeros = pr.zeros;
-    const int32_t *__restrict__ row_ptr = pr.row_ptr;
-    const uint16_t *__restrict__ col_idx = pr.col_idx;
-    const uint16_t *__restrict__ out_val = pr.out_val;
+    const uint32_t *__restrict__ const qweight0 = pr.qweight;
+    const uint16_t *__restrict__ const scales0 = pr.scales;
+    const uint8_t *__restrict__ const zeros0 = pr.zeros;
+    const int32_t *__restrict__ const row_ptr0 = pr.row_ptr;
+    const uint16_t *__restrict__ const col_idx0 = pr.col_idx;
+    const uint16_t *__restrict__ const out_val0 = pr.out_val;
     const _Float16 *__restrict__ X = pr.X;
-    _Float16 *__restrict__ Y = pr.Y;
-    const int csr_last_vec = pr.csr_last_vec, sc_last_vec = pr.sc_last_vec, zp_last_vec = pr.zp_last_vec;
-    asm volatile("" ::"s"(qweight), "s"(scales), "s"(zeros), "s"(row_ptr), "s"(col_idx), "s"(out_val), "s"(X), "s"(Y),
-                 "s"(K), "s"(csr_last_vec), "s"(sc_last_vec), "s"(zp_last_vec));
+    _Float16 *__restrict__ Y = pr.Y;                    // of a gated pair both layers' Y is H
+    const int csr_last_vec0 = pr.csr_last_vec, sc_last_vec = pr.sc_last_vec, zp_last_vec = pr.zp_last_vec;
+    asm volatile("" ::"s"(qweight0), "s"(scales0), "s"(zeros0), "s"(row_ptr0), "s"(col_idx0), "s"(out_val0), "s"(X), "s"(Y),
+                 "s"(K), "s"(csr_last_vec0), "s"(sc_last_vec), "s"(zp_last_vec));
+    // Tile number `it` of a gated block belongs to layer it & 1.  Its pointers are read from the argument segment where they
+    // are used, through the scalar cache: both layers' would not fit the scalar registers.
+    auto layer_of = [&](int it) -> const DecodeProblem & { return batch.p[2 * blockIdx.y + (it & 1)]; };
     const int tiles = (N + 15) >> 4;
     const int tile0 = (int)blockIdx.x * tiles_per_block;
     if (tile0 >= tiles) return;                         // the grid is as wide as the largest layer needs
-    const int nt = tiles - tile0 < tiles_per_block ? tiles - tile0 : tiles_per_block;
+    const int own = tiles - tile0 < tiles_per_block ? tiles - tile0 : tiles_per_block;
+    const int nt = GATED ? 2 * own : own;
+    auto tile_of = [&](int it) { return tile0 + (GATED ? it >> 1 : it); };
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1099,18 +1134,22 @@ __global__ __launch_bounds__(512) void decode_stream_kernel(const DecodeBatch ba
 
     // row_ptr again as a pointer to constant memory (nothing in this launch writes it): a load through it with a
     // wave-uniform index is a scalar load, which does not queue behind the vector loads in flight.
-    const __attribute__((address_space(4))) int32_t *row_ptr_k =
-        (const __attribute__((address_space(4))) int32_t *)(uintptr_t)row_ptr;
+    typedef const __attribute__((address_space(4))) int32_t *row_ptr_const;
+    auto row_ptr_k = [&](int it) { return (row_ptr_const)(uintptr_t)(GATED ? layer_of(it).row_ptr : row_ptr0); };
     // Requests for tile number `it` of this block (clamped: past the last one it is the last again): the
     // CSR bounds of the tile (scalar loads), then everything the lanes need.
     auto issue_bounds = [&](TileRegs<BITS> &T, int it) {
-        const int row0 = (tile0 + (it < nt ? it : nt - 1)) * 16;
+        it = it < nt ? it : nt - 1;
+        const int row0 = tile_of(it) * 16;
         const int last_row = row0 + 16 < N ? row0 + 16 : N;
-        T.e_begin = row_ptr_k[row0];                    // uniform addresses in the constant address space: scalar loads
-        T.e_end = row_ptr_k[last_row];
+        T.e_begin = row_ptr_k(it)[row0];                // uniform addresses in the constant address space: scalar loads
+        T.e_end = row_ptr_k(it)[last_row];
     };
     auto issue_tile = [&](TileRegs<BITS> &T, int it) {
-        const int n = (tile0 + (it < nt ? it : nt - 1)) * 16 + r;
+        it = it < nt ? it : nt - 1;
+        const uint32_t *qweight = (GATED ? layer_of(it).qweight : qweight0);
+        const int32_t *row_ptr = (GATED ? layer_of(it).row_ptr : row_ptr0);
+        const int n = tile_of(it) * 16 + r;
         const int n_c = n < N ? n : N - 1;
         const uint32_t first_group = (uint32_t)n_c * gpr + g0;
 #pragma unroll
@@ -1123,7 +1162,10 @@ __global__ __launch_bounds__(512) void decode_stream_kernel(const DecodeBatch ba
     // lane of its own four scales and zero points costs the CU's address unit four times as long); the
     // other threads repeat vector 0.
     auto issue_meta = [&](TileRegs<BITS> &T, int it) {
-        const int tile = tile0 + (it < nt ? it : nt - 1);
+        it = it < nt ? it : nt - 1;
+        const uint16_t *scales = (GATED ? layer_of(it).scales : scales0);
+        const uint8_t *zeros = (GATED ? layer_of(it).zeros : zeros0);
+        const int tile = tile_of(it);
         const bool is_sc = tid < 2 * gpr, is_zp = !is_sc && tid < 3 * gpr;
         const int v_sc = tile * 2 * gpr + tid < sc_last_vec ? tile * 2 * gpr + tid : sc_last_vec;
         const int v_zp = tile * gpr + (tid - 2 * gpr) < zp_last_vec ? tile * gpr + (tid - 2 * gpr) : zp_last_vec;
@@ -1135,14 +1177,16 @@ __global__ __launch_bounds__(512) void decode_stream_kernel(const DecodeBatch ba
     };
     // The tile's CSR segment [e_begin, e_end) from the 16-byte boundary below e_begin: thread t brings
     // entries e0 + 8t .. e0 + 8t + 7 (idle threads repeat the last vector: no extra traffic).
-    auto issue_seg = [&](TileRegs<BITS> &T) {
+    auto issue_seg = [&](TileRegs<BITS> &T, int it) {
+        it = it < nt ? it : nt - 1;
         const int e0 = T.e_begin & ~7;
         const int v_end = T.e_end > e0 ? (T.e_end - 1) / 8 : e0 / 8;
         int v = e0 / 8 + tid;
         v = v < v_end ? v : v_end;
+        const int csr_last_vec = GATED ? layer_of(it).csr_last_vec : csr_last_vec0;
         v = v < csr_last_vec ? v : csr_last_vec;
-        T.seg_col = reinterpret_cast<const u32x4 *>(col_idx)[v];
-        T.seg_val = reinterpret_cast<const u32x4 *>(out_val)[v];
+        T.seg_col = reinterpret_cast<const u32x4 *>((GATED ? layer_of(it).col_idx : col_idx0))[v];
+        T.seg_val = reinterpret_cast<const u32x4 *>((GATED ? layer_of(it).out_val : out_val0))[v];
     };
 
     // Order of the first requests: the first tile's scales and zero points, X, tiles 0, 1 and 2 - none of which
@@ -1173,8 +1217,8 @@ __global__ __launch_bounds__(512) void decode_stream_kernel(const DecodeBatch ba
     issue_meta(C, 2);
     issue_tile(C, 2);
     __builtin_amdgcn_sched_barrier(0);
-    issue_seg(A);
-    issue_seg(B);
+    issue_seg(A, 0);
+    issue_seg(B, 1);
     __builtin_amdgcn_sched_barrier(0);
     GWQ_STAMP_AT(2);                                    // everything requested
 
@@ -1262,9 +1306,10 @@ __global__ __launch_bounds__(512) void decode_stream_kernel(const DecodeBatch ba
     const int red_groups = nthreads >= 512 ? 2 : 1;     // sets of 256 threads that take turns adding partial sums
 
     // Adds the partial sums of tile number `it` (written before the last barrier) and stores its outputs.
+    float gate_sum = 0.f;
     auto reduce_tile = [&](int it) {
         const float *src = red + (it & 1) * (nwaves * 256);
-        const int row0 = (tile0 + it) * 16;
+        const int row0 = tile_of(it) * 16;
         auto one = [&](int idx) {
             const int e = idx >> 6, l = idx & 63, bq = l >> 4;
             if (bq >= RB) return;
@@ -1273,10 +1318,11 @@ __global__ __launch_bounds__(512) void decode_stream_kernel(const DecodeBatch ba
 #pragma unroll
                 for (int sp = 0; sp < SPLIT; ++sp) sum += src[(w * 4 + e) * 64 + (l & 15) + 16 * (bq + RB * sp)];
             const int nn = row0 + (l & 15), m = 4 * bq + e;
-            if (nn < N && m < M) Y[(size_t)m * N + nn] = (_Float16)sum;
+            if (GATED && !(it & 1)) gate_sum = sum;     // this thread adds the same entry of the up tile next (at least 256 threads)
+            else if (nn < N && m < M) Y[(size_t)m * N + nn] = (_Float16)(GATED ? silu(gate_sum) * sum : sum);
         };
         if (nthreads >= 256) {
-            const int grp = it % red_groups;
+            const int grp = (GATED ? it >> 1 : it) % red_groups;
             if ((tid >> 8) == grp) one(tid & 255);
         } else {
             for (int idx = tid; idx < 256; idx += nthreads) one(idx);
@@ -1319,7 +1365,7 @@ __global__ __launch_bounds__(512) void decode_stream_kernel(const DecodeBatch ba
         __builtin_amdgcn_sched_barrier(0);
         if (it == 0) GWQ_STAMP_AT(6);                   // multiplied
         u32x4 seg_col = T.seg_col, seg_val = T.seg_val;
-        issue_seg(T2);
+        issue_seg(T2, it + 2);
         issue_bounds(T, it + 3);
         issue_meta(T, it + 3);
         issue_tile(T, it + 3);
@@ -1332,7 +1378,7 @@ __global__ __launch_bounds__(512) void decode_stream_kernel(const DecodeBatch ba
         if (it > 0) reduce_tile(it - 1);
 
         // Outliers: entry j of the channel sits at LDS index j - e0 while j < staged_end.
-        const int n = (tile0 + it) * 16 + r;
+        const int n = tile_of(it) * 16 + r;
         const int j_end = n < N ? rp1 : rp0;
         const int j_staged = j_end < staged_end ? j_end : staged_end;
         for (int j = rp0 + sub; j < j_staged; j += 4 * stride) {
@@ -1362,8 +1408,8 @@ __global__ __launch_bounds__(512) void decode_stream_kernel(const DecodeBatch ba
             int j = rp0 + sub;
             if (j < staged_end) j += (staged_end - j + stride - 1) / stride * stride;
             for (; j < j_end; j += stride) {
-                const uint32_t col = load_u16_now(col_idx + j);
-                const float v = (float)__builtin_bit_cast(_Float16, (uint16_t)load_u16_now(out_val + j));
+                const uint32_t col = load_u16_now((GATED ? layer_of(it).col_idx : col_idx0) + j);
+                const float v = (float)__builtin_bit_cast(_Float16, (uint16_t)load_u16_now((GATED ? layer_of(it).out_val : out_val0) + j));
                 const uint2 x = *reinterpret_cast<const uint2 *>(xt + xt_offset<MR>(col, xq));
                 const half2v x01 = __builtin_bit_cast(half2v, x.x), x23 = __builtin_bit_cast(half2v, x.y);
                 acc[0] = __builtin_fmaf(v, (float)x01[0], acc[0]);
@@ -1424,8 +1470,9 @@ hipError_t launch_small(const DecodeBatch &batch, int count, int blocks, int nwa
 {
     if (pair) {                                         // nwaves: both sets of waves
 #define GWQ_SMALL_PAIR(UU, MM) \
-    if (u == UU && ms == MM && !gated_pairs && !fine && !bf16) \
-        return launch_kernel<&decode_small_kernel<BITS, UU, MM, false, false, true>>(batch, count, blocks, nwaves, lds, st)
+    if (u == UU && ms == MM && !fine && !bf16) \
+        return gated_pairs ? launch_kernel<&decode_small_gate_up_pair_kernel<BITS, UU, MM>>(batch, count / 2, blocks, nwaves, lds, st) \
+                           : launch_kernel<&decode_small_kernel<BITS, UU, MM, false, false, true>>(batch, count, blocks, nwaves, lds, st)
         GWQ_SMALL_PAIR(4, 5); GWQ_SMALL_PAIR(4, 6); GWQ_SMALL_PAIR(4, 7); GWQ_SMALL_PAIR(4, 8);
         GWQ_SMALL_PAIR(8, 5); GWQ_SMALL_PAIR(8, 6); GWQ_SMALL_PAIR(8, 7); GWQ_SMALL_PAIR(8, 8);
 #undef GWQ_SMALL_PAIR
@@ -1510,7 +1557,7 @@ hipError_t launch_decode(int count, const gwq_packed *const *P, const void *cons
     // The lean kernel: M <= 4, every wave owning exactly U groups, at most 16 waves, X in LDS.
     if (tune.bf16 && fine) return hipErrorNotSupported;
     const int lean_rows = tune.lean_rows > 0 ? tune.lean_rows : kLeanRows;
-    if (M <= lean_rows && (M <= 4 || !tune.gated_pairs) && !(fine && tune.gated_pairs) && !(tune.bf16 && tune.gated_pairs) &&
+    if (M <= lean_rows && !((fine || tune.bf16) && tune.gated_pairs) &&
         !(tune.stream == 2 && !fine && max_gpr <= 8 * kStreamU)) {
         int u = max_gpr > 128 ? 16 : max_gpr > 16 ? 8 : 4;
         if (waves_override > 0) {                       // the most waves that do not exceed the request
@@ -1533,21 +1580,22 @@ hipError_t launch_decode(int count, const gwq_packed *const *P, const void *cons
         // per tile) where the launch still has two blocks for every CU and two such blocks share a CU's LDS.
         const size_t set_bytes = meta + (size_t)16 * nwaves * 64 + 32 + (size_t)nwaves * M * 64;
         const size_t lds_pair = x_bytes + 2 * set_bytes;
-        const bool pair = M > 4 && !fine && !tune.bf16 && !tune.gated_pairs && u <= 8 && 2 * nwaves <= 16 &&
-                          x_bytes <= kXLdsBudget && 2 * lds_pair <= kMaxLds && tune.pairs != 1 &&
-                          (tune.pairs == 2 || total_blocks >= 4 * device_cus());
+        // (A gated pair beyond four rows needs the two sets whatever the size of the launch.)
+        const bool pair = M > 4 && !fine && !tune.bf16 && u <= 8 && 2 * nwaves <= 16 && x_bytes <= kXLdsBudget && 2 * lds_pair <= kMaxLds &&
+                          (tune.gated_pairs || (tune.pairs != 1 && (tune.pairs == 2 || total_blocks >= 4 * device_cus())));
         if (pair) {
             batch.nwaves = 2 * nwaves;
-            const int grid = (blocks + 1) / 2;
+            const int grid = tune.gated_pairs ? blocks : (blocks + 1) / 2;
             if (describe) {
                 snprintf(describe->text, sizeof(describe->text), "decode_small_kernel<%d,%d,%d,false,false,true> grid %dx%d block %d lds %zu",
                          bits, u, M, grid, count, 128 * nwaves, lds_pair);
                 return hipSuccess;
             }
-            return bits == 4 ? launch_small<4>(batch, count, grid, 2 * nwaves, u, M, lds_pair, false, false, false, true, st)
-                             : launch_small<3>(batch, count, grid, 2 * nwaves, u, M, lds_pair, false, false, false, true, st);
+            return bits == 4 ? launch_small<4>(batch, count, grid, 2 * nwaves, u, M, lds_pair, tune.gated_pairs, false, false, true, st)
+                             : launch_small<3>(batch, count, grid, 2 * nwaves, u, M, lds_pair, tune.gated_pairs, false, false, true, st);
         }
-        if (nwaves <= 16 && (u < 16 || M <= (tune.bf16 ? 1 : 2)) && x_bytes <= kXLdsBudget && lds <= kMaxLds && (M <= 4 || u <= 8) && roomy && fine_ok) {
+        if (nwaves <= 16 && (u < 16 || M <= (tune.bf16 ? 1 : 2)) && x_bytes <= kXLdsBudget && lds <= kMaxLds && (M <= 4 || u <= 8) && roomy && fine_ok &&
+            (M <= 4 || !tune.gated_pairs)) {
             batch.nwaves = nwaves;
             if (describe) {
                 snprintf(describe->text, sizeof(describe->text), "%s<%d,%d,%d%s> grid %dx%d block %d lds %zu",
@@ -1560,11 +1608,9 @@ hipError_t launch_decode(int count, const gwq_packed *const *P, const void *cons
                              : launch_small<3>(batch, count, blocks, nwaves, u, M, lds, tune.gated_pairs, fine, tune.bf16, false, st);
         }
     }
-    if (tune.gated_pairs) return hipErrorNotSupported;  // only the kernel above multiplies gated pairs
-
     // The streaming kernel: rows of at most 32 groups (8 waves of 4), XT[K][rows] in LDS.  By default for
     // the batches the lean kernel does not take.
-    if (!fine && !tune.bf16 && tune.stream != 1 && (M > 4 || tune.stream == 2) && max_gpr <= 8 * kStreamU) {
+    if (!fine && !tune.bf16 && tune.stream != 1 && (M > 4 || (tune.stream == 2 && !tune.gated_pairs)) && max_gpr <= 8 * kStreamU) {
         const int nwaves = (max_gpr + kStreamU - 1) / kStreamU, nthreads = 64 * nwaves;
         const int mr = M <= 4 ? 4 : M <= 8 ? 8 : 16;
         const size_t xt = (size_t)max_gpr * kGroup * 2 * mr, red = (size_t)2 * nwaves * 1024;
@@ -1580,16 +1626,22 @@ hipError_t launch_decode(int count, const gwq_packed *const *P, const void *cons
             if (bpc < 1) bpc = 1;
             const int slots = device_cus() * bpc;
             // The fewest tiles per block with which all layers' blocks are resident at once.
+            // (A gated pair: tiles of gate, each with its tile of up.)
+            const int step = tune.gated_pairs ? 2 : 1;
             int tpb = tune.tiles;
             if (tpb <= 0)
                 for (tpb = 1;; ++tpb) {
                     int total = 0;
-                    for (int i = 0; i < count; ++i) total += ((P[i]->N + 15) / 16 + tpb - 1) / tpb;
+                    for (int i = 0; i < count; i += step) total += ((P[i]->N + 15) / 16 + tpb - 1) / tpb;
                     if (total <= slots) break;
                 }
             // A block that gets a single tile has nothing to pipeline and pays the set-up of XT for it: the wide
-            // kernel is faster there (4096 channels on 256 CUs).
-            const bool take = tune.stream == 2 || tune.tiles > 0 || tpb >= 2;
+            // kernel is faster there (4096 channels on 256 CUs).  A gated block has two tiles at least: it loses to two
+            // products and silu_mul_kernel with one pair and long rows (us, 2048 x 4096, M = 16: 11.3 against 9.3), not with
+            // rows of 2048 (1000 x 2048: 8.3 against 9.3) or several pairs (11008 x 4096: 20.8 against 22.2).  The threads that add
+            // up a tile must be there for both: four waves.
+            const bool take = tune.gated_pairs ? nthreads >= 256 && (tpb >= 2 || max_gpr <= 16 || tune.tiles > 0)
+                                               : tune.stream == 2 || tune.tiles > 0 || tpb >= 2;
             batch.nwaves = nwaves;
             const int grid = (blocks + tpb - 1) / tpb;
             if (take && describe) {
@@ -1599,19 +1651,23 @@ hipError_t launch_decode(int count, const gwq_packed *const *P, const void *cons
                 return hipSuccess;
             }
             hipError_t e = hipErrorInvalidValue;
-#define GWQ_STREAM(B, RR) \
-    if (take && bits == B && mr == RR) { \
+#define GWQ_STREAM(B, RR, G) \
+    if (take && bits == B && mr == RR && tune.gated_pairs == G) { \
         static std::atomic<uint32_t> lds_allowed{0}; \
-        e = allow_dynamic_lds(reinterpret_cast<const void *>(&decode_stream_kernel<B, RR>), (int)kMaxLds, lds_allowed); \
+        e = allow_dynamic_lds(reinterpret_cast<const void *>(&decode_stream_kernel<B, RR, G>), (int)kMaxLds, lds_allowed); \
         if (e != hipSuccess) return e; \
-        decode_stream_kernel<B, RR><<<dim3(grid, count), nthreads, lds, st>>>(batch, tpb, ent_cap); \
+        decode_stream_kernel<B, RR, G><<<dim3(grid, count / step), nthreads, lds, st>>>(batch, tpb, ent_cap); \
         return hipGetLastError(); \
     }
-            GWQ_STREAM(4, 4) GWQ_STREAM(4, 8) GWQ_STREAM(4, 16) GWQ_STREAM(3, 4) GWQ_STREAM(3, 8) GWQ_STREAM(3, 16)
+            GWQ_STREAM(4, 4, false) GWQ_STREAM(4, 8, false) GWQ_STREAM(4, 16, false)
+            GWQ_STREAM(3, 4, false) GWQ_STREAM(3, 8, false) GWQ_STREAM(3, 16, false)
+            GWQ_STREAM(4, 8, true) GWQ_STREAM(4, 16, true) GWQ_STREAM(3, 8, true) GWQ_STREAM(3, 16, true)
 #undef GWQ_STREAM
             if (take) return e;
         }
     }
+
+    if (tune.gated_pairs) return hipErrorNotSupported;  // only the kernels above multiply gated pairs
 
     // The wide kernel.  Among the shapes (U, waves <= 8) whose LDS footprint fits, the one with the
     // fewest phases, then the most waves, then the shorter waves.

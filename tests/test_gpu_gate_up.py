@@ -1,0 +1,83 @@
+"""The gated pair in one launch beyond four rows and for groups below 128, against the oracle's fp64 products, at the
+tolerance of every linear test (gpu_helpers); H comes from FP32 sums, so only its own rounding is new."""
+import numpy as np
+import pytest
+
+import gwq_synth as gs
+from oracle import gwq_oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+
+def _pair(seed, N, K, bits, group=128, ppm=(10000, 10000)):
+    layers = []
+    for i in range(2):
+        rng = np.random.default_rng([seed, i])
+        W = gs.weight(N, K, rng, planted_cols=2)
+        layers.append(orc.pack(W, gs.score_from_weight(W, rng), bits, ppm[i], group))
+    return layers, np.random.default_rng([seed, 2])
+
+
+def _check(layers, rng, M, what):
+    import paper_2411_00850_amd as gwq
+    from gpu_helpers import assert_close, to_gpu, upload_packed
+    X = gs.activations(M, layers[0].K, rng)
+    H = gwq.linear_gate_up(upload_packed(layers[0]), upload_packed(layers[1]), to_gpu(X)).cpu().numpy()
+    assert_close(H, orc.gate_up(orc.linear_f64(layers[0], X), orc.linear_f64(layers[1], X)), what)
+
+
+@pytest.mark.parametrize("bits", [4, 3])
+@pytest.mark.parametrize("M", [5, 6, 7, 8, 9, 13, 16])
+@pytest.mark.parametrize("N,K", [(16, 128), (1, 512), (50, 1152), (333, 2048), (130, 4096), (40, 5120)])
+def test_every_row_count(bits, M, N, K):
+    """Ragged last tiles, one wave to eight per layer, rows too long for the kernels (the product path), and different
+    numbers of outliers in gate and up."""
+    layers, rng = _pair(N + K + bits, N, K, bits, ppm=(10000, 30000))
+    _check(layers, rng, M, f"gate_up N={N} K={K} M={M} bits={bits}")
+
+
+@pytest.mark.parametrize("bits", [4, 3])
+@pytest.mark.parametrize("tiles", [1, 2, 3, 7])
+def test_streaming_pairs_of_tiles(bits, tiles):
+    """The streaming kernel with one to seven tiles of each layer per block, the last block cut short."""
+    import paper_2411_00850_amd as gwq
+    layers, rng = _pair(77 + bits, 16 * 16 + 5, 2048, bits, ppm=(0, 20000))
+    gwq.tuning_set("decode_tiles", tiles)
+    try:
+        for M in (9, 16):
+            _check(layers, rng, M, f"gate_up tiles={tiles} M={M} bits={bits}")
+    finally:
+        gwq.tuning_set("decode_tiles", 0)
+
+
+@pytest.mark.parametrize("bits", [4, 3])
+@pytest.mark.parametrize("group", [16, 32, 64])
+@pytest.mark.parametrize("N,K", [(50, 1152), (130, 4096), (20, 128)])
+def test_small_groups(bits, group, N, K):
+    layers, rng = _pair(group + N + bits, N, K, bits, group)
+    for M in (1, 2, 3, 4, 7):
+        _check(layers, rng, M, f"gate_up group={group} N={N} K={K} M={M} bits={bits}")
+
+
+@pytest.mark.parametrize("M,group", [(4, 16), (8, 128), (16, 128)])
+def test_replayed_from_a_graph(M, group):
+    import torch
+    import paper_2411_00850_amd as gwq
+    from gpu_helpers import to_gpu, upload_packed
+    layers, rng = _pair(9 * M, 200, 2048, 4, group)
+    D = [upload_packed(P) for P in layers]
+    X = to_gpu(gs.activations(M, 2048, rng))
+    H = torch.empty((M, 200), dtype=torch.float16, device="cuda")
+    call = gwq.prepare_linear_gate_up(D[0], D[1], X, H)
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    for trial in range(3):
+        X.copy_(to_gpu(gs.activations(M, 2048, rng)))
+        want = gwq.linear_gate_up(D[0], D[1], X)
+        H.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(H, want), trial
