@@ -108,12 +108,17 @@ def version():
     return lib().gwq_version().decode()
 
 
-def layout(N, K, bits, group=128, ppm=10000, M_max=0):
-    """Buffer sizes in bytes for one layer, as a dict (pure host call)."""
+def _sizes(N, K, bits, group, ppm, M_max):
     s = _Sizes()
     rc = lib().gwq_layout(N, K, bits, group, ppm, M_max, ctypes.byref(s))
     if rc != GWQ_OK:
         raise GwqError(rc, "gwq_layout")
+    return s
+
+
+def layout(N, K, bits, group=128, ppm=10000, M_max=0):
+    """Buffer sizes in bytes for one layer, as a dict (pure host call)."""
+    s = _sizes(N, K, bits, group, ppm, M_max)
     return {n: getattr(s, n) for n, _ in _Sizes._fields_}
 
 
@@ -136,10 +141,9 @@ def prepare_linear_gate_up(Pg, Pu, X, out):
     xp, hp = ctypes.c_void_p(X.data_ptr()), ctypes.c_void_p(out.data_ptr())
     wp, wl = (ctypes.c_void_p(ws.data_ptr()), ws.numel()) if ws is not None else (None, 0)
     fn = lib().gwq_linear_gate_up
-    current_stream = torch.cuda.current_stream
 
     def call(_keep=(cg, cu, Pg, Pu, X, out, ws)):
-        rc = fn(rg, ru, xp, M, hp, wp, wl, ctypes.c_void_p(current_stream().cuda_stream))
+        rc = fn(rg, ru, xp, M, hp, wp, wl, _current_stream_ptr())
         if rc != GWQ_OK:
             raise GwqError(rc, "gwq_linear_gate_up")
     return call
@@ -183,10 +187,21 @@ def probe_mfma(blocks, iters, sink, stream=None):
     return 2.0 * 32 * 32 * 16 * 8 * iters * 4 * blocks
 
 
-def _stream_ptr(stream):
+_raw_stream = None
+
+
+def _current_stream_ptr():
+    """torch.cuda.current_stream().cuda_stream without the Stream object around it, which takes 2.7 us to make - half as
+    long as a decode launch of one 4096 x 4096 layer - against 0.2."""
+    global _raw_stream
     import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    if _raw_stream is None:
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda device: torch.cuda.current_stream(device).cuda_stream)
+    return _raw_stream(torch.cuda.current_device())
+
+
+def _stream_ptr(stream):
+    return _current_stream_ptr() if stream is None else stream.cuda_stream
 
 
 @dataclass
@@ -274,7 +289,7 @@ def quality(P, W, score, out=None, stream=None, workspace=None):
     if out is None:
         out = torch.empty(3, dtype=torch.float64, device=W.device)
     if workspace is None:
-        nbytes = layout(P.N, P.K, P.bits, P.group, P.ppm, 0)["quality_workspace"]
+        nbytes = _sizes(P.N, P.K, P.bits, P.group, P.ppm, 0).quality_workspace
         workspace = torch.empty(nbytes, dtype=torch.uint8, device=W.device)
     cs = P.c_struct()
     rc = lib().gwq_quality(ctypes.byref(cs), W.data_ptr(), score.data_ptr(), st, out.data_ptr(), workspace.data_ptr(),
@@ -311,15 +326,15 @@ def _room_for_x(P, M, scratch):
 def linear_workspace(P, M, device="cuda"):
     """Scratch tensor gwq_linear needs for this layer at M rows (None for the decode path)."""
     import torch
-    sz = layout(P.N, P.K, P.bits, P.group, P.ppm, M)
-    nbytes = sz["linear_workspace"] + _room_for_x(P, M, sz["linear_scratch"])
+    sz = _sizes(P.N, P.K, P.bits, P.group, P.ppm, M)
+    nbytes = sz.linear_workspace + _room_for_x(P, M, sz.linear_scratch)
     return torch.empty(nbytes, dtype=torch.uint8, device=device) if nbytes else None
 
 
 def linear_scratch(P, M, device="cuda"):
     """Scratch tensor gwq_linear_indexed may use for this layer at M rows (None for the decode path)."""
     import torch
-    nbytes = layout(P.N, P.K, P.bits, P.group, P.ppm, M)["linear_scratch"]
+    nbytes = _sizes(P.N, P.K, P.bits, P.group, P.ppm, M).linear_scratch
     nbytes += _room_for_x(P, M, nbytes)
     return torch.empty(nbytes, dtype=torch.uint8, device=device) if nbytes else None
 
@@ -355,7 +370,7 @@ def linear(P, X, out=None, stream=None, workspace=None, index=None, scratch="aut
         if rc != GWQ_OK:
             raise GwqError(rc, "gwq_linear_indexed")
         return out
-    if workspace is None:
+    if workspace is None and M > 16:                   # the decode path has none
         workspace = linear_workspace(P, M, X.device)
     ws_ptr = workspace.data_ptr() if workspace is not None else None
     ws_len = workspace.numel() if workspace is not None else 0
@@ -374,7 +389,7 @@ def linear_bf16(P, X, out=None, stream=None, workspace=None):
     if out is None:
         out = torch.empty((M, P.N), dtype=torch.bfloat16, device=X.device)
     assert out.is_cuda and out.dtype == torch.bfloat16 and out.is_contiguous() and tuple(out.shape) == (M, P.N)
-    if workspace is None:
+    if workspace is None and M > 16:
         workspace = linear_workspace(P, M, X.device)
     cs = P.c_struct()
     rc = lib().gwq_linear_bf16(ctypes.byref(cs), X.data_ptr(), M, out.data_ptr(),
@@ -412,7 +427,6 @@ def prepare_linear(P, X, out, index=None):
     cs = P.c_struct()
     ref = ctypes.byref(cs)
     xp, yp, M = ctypes.c_void_p(X.data_ptr()), ctypes.c_void_p(out.data_ptr()), X.shape[0]
-    current_stream = torch.cuda.current_stream
 
     def ptr_len(t):
         return (ctypes.c_void_p(t.data_ptr()), t.numel()) if t is not None else (None, 0)
@@ -423,7 +437,7 @@ def prepare_linear(P, X, out, index=None):
         wp, wl = ptr_len(ws)
 
         def call(_keep=(cs, P, X, out, ws)):
-            rc = fn(ref, xp, M, yp, wp, wl, ctypes.c_void_p(current_stream().cuda_stream))
+            rc = fn(ref, xp, M, yp, wp, wl, _current_stream_ptr())
             if rc != GWQ_OK:
                 raise GwqError(rc, "gwq_linear")
         return call
@@ -432,7 +446,7 @@ def prepare_linear(P, X, out, index=None):
     (ip, il), (sp, sl) = ptr_len(index), ptr_len(sc)
 
     def call_indexed(_keep=(cs, P, X, out, index, sc)):
-        rc = fn(ref, xp, M, yp, ip, il, sp, sl, ctypes.c_void_p(current_stream().cuda_stream))
+        rc = fn(ref, xp, M, yp, ip, il, sp, sl, _current_stream_ptr())
         if rc != GWQ_OK:
             raise GwqError(rc, "gwq_linear_indexed")
     return call_indexed
@@ -454,10 +468,9 @@ def prepare_linear_batch(layers, Xs, outs):
     xarr = (ctypes.c_void_p * n)(*[X.data_ptr() for X in Xs])
     yarr = (ctypes.c_void_p * n)(*[Y.data_ptr() for Y in outs])
     fn = lib().gwq_linear_batch
-    current_stream = torch.cuda.current_stream
 
     def call(_keep=(structs, layers, Xs, outs)):
-        rc = fn(n, parr, xarr, M, yarr, ctypes.c_void_p(current_stream().cuda_stream))
+        rc = fn(n, parr, xarr, M, yarr, _current_stream_ptr())
         if rc != GWQ_OK:
             raise GwqError(rc, "gwq_linear_batch")
     return call
