@@ -38,29 +38,34 @@ inline size_t index_record_bytes(int64_t N, int64_t K) { return ((size_t)(N * (K
 __host__ __device__ constexpr uint32_t index_scale_cap(int bits) { return bits == 4 ? 0x6C43u : 0x7091u; }
 
 // ---- gwq_pack workspace: uint32 words -------------------------------------------------------
-// [0, 3*kSelBins)        histograms of the three radix-select passes
-// kWsPrefix              key bits fixed by the passes done so far
-// kWsRemaining           how many entries are still to be taken among keys matching the prefix
+// [0, 3*kSelBins)        histograms of the selection's later digits (gwq_pack.hip)
+// kWsPrefix              the threshold: key of the smallest kept entry
+// kWsRemaining           how many of the keys equal to it are kept
+// kWsCandOverflow        nonzero when some row had more candidates than its share of the list holds
+// kWsBandLo, kWsBandHi   the band of keys that the sample puts the threshold in, both ends included
+// kWsWanted, kWsWay      entries to select; by list, by scores or a single key
+// kWsStep + 2 i, + 1     after digit i: what is known of the threshold, and how many entries are still wanted from there
 // kWsRows + 0*N ..       per row: count of keys above the threshold
 // kWsRows + 1*N ..       per row: count of keys equal to the threshold
 // kWsRows + 2*N ..       per row: how many of its threshold ties are kept
-// kWsRows + 3*N ..       kSelBins words: histogram of the second digit over the candidates (below)
+// kWsRows + 3*N ..       kSelBins words: three times kSpread whose sums are the keys above the band, where it is a single key
+//                        the keys equal to it, and the candidates
 // then                   per row: number of candidates; then the candidates' keys, [N][pack_candidates_per_row(K)]
-// kWsCandOverflow        nonzero when some row had more candidates than its share of the list holds
-// Candidates are the keys whose first digit equals the threshold's: after the first pass over the scores only
-// they can still decide the threshold, so the second and third digit and the per-row counts are worked out on
-// that short list instead of in three more passes over all scores.  Every row has its own part of the list (no
-// counter shared between blocks).  When a row's part does not hold its candidates (scores with very many equal or
-// nearly equal magnitudes) the full passes run instead; both ways give the same result.
+// Every row has its own part of the list (no counter shared between blocks).
 constexpr int kWsPrefix = 3 * kSelBins;
 constexpr int kWsRemaining = kWsPrefix + 1;
 constexpr int kWsCandOverflow = kWsPrefix + 3;
+constexpr int kWsBandLo = kWsPrefix + 4, kWsBandHi = kWsPrefix + 5, kWsWanted = kWsPrefix + 6, kWsWay = kWsPrefix + 7;
+constexpr int kWsStep = kWsPrefix + 8;                 // three pairs
 constexpr int kWsRows = kWsPrefix + 16;
+constexpr int kSpread = 512;
+static_assert(3 * kSpread <= kSelBins, "the place of one histogram");
 
 inline int pack_candidates_per_row(int64_t K) { return K / 32 < 32 ? 32 : (int)(K / 32); }
+__host__ __device__ constexpr int64_t pack_keys_at(int64_t N) { return kWsRows + 3 * N + kSelBins + N; }   // a multiple of four
 inline size_t pack_workspace_bytes(int64_t N, int64_t K)
 {
-    return (size_t)(kWsRows + 3 * N + kSelBins + N + N * pack_candidates_per_row(K)) * 4 + 256;
+    return (size_t)(pack_keys_at(N) + N * pack_candidates_per_row(K)) * 4 + 256;
 }
 
 // Launchers (defined in the .hip files).  Each enqueues on `stream` and returns the last HIP error.

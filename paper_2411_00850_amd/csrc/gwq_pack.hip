@@ -1,10 +1,13 @@
-// gwq_pack on gfx950: outlier selection (Sec. 3.2, Eq. 8) as a three-pass (FP16 scores: two-pass) radix select over the
-// bit patterns of |score|, CSR build in flat-index order, then per (row, group of 16 to 128) the scale,
+// gwq_pack on gfx950: outlier selection (Sec. 3.2, Eq. 8) by the bit patterns of |score|, from a sampled band of them or by a
+// radix select over all, CSR build in flat-index order, then per (row, group of 16 to 128) the scale,
 // zero point and codes of Eq. 6, 7 and 9 and the word layout documented in gwq.h.
 //
 // Everything is integer work or arithmetic whose result is that of exact arithmetic rounded once (see the encoder),
 // so the output is a function of the inputs alone.  Integer atomics are used for the
 // histograms (order-independent); there are no floating-point atomics.
+#include <algorithm>
+#include <type_traits>
+
 #include "gwq_internal.h"
 
 #pragma clang fp contract(off)
@@ -58,110 +61,6 @@ template <bool F16> __device__ inline void load_keys8(const void *score, size_t 
     }
 }
 
-__global__ void init_ws_kernel(uint32_t *ws, uint32_t k_out, int N)
-{
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < kWsRows; i += gridDim.x * blockDim.x)
-        ws[i] = 0;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < kSelBins; i += gridDim.x * blockDim.x)
-        ws[kWsRows + 3 * N + i] = 0;                    // the candidates' histogram
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        // With nothing to select the threshold sits above every key, so no entry qualifies.
-        ws[kWsPrefix] = k_out ? 0u : 0xFFFFFFFFu;
-        ws[kWsRemaining] = k_out;
-    }
-}
-
-// One radix-select pass: histogram of this pass's digit over the keys that match the prefix.
-// `total` is a multiple of 8 (K is a multiple of 128).  The grid is kept small (two blocks per CU):
-// every block flushes its non-empty bins with global atomics, in the first pass a few hundred bins
-// per block and all blocks on the same addresses, which with 2048 blocks took longer than the pass
-// over the keys.
-// Which way a launch belongs to: both ways are enqueued (the choice is made on the device, by the pass that
-// collects the candidates) and the kernels of the way not taken return at once.
-enum When { kAlways = 0, kWithCandidates = 1, kWithoutCandidates = 2 };
-__device__ inline bool not_my_turn(const uint32_t *ws, int when)
-{
-    const bool overflow = ws[kWsCandOverflow] != 0;
-    return (when == kWithCandidates && overflow) || (when == kWithoutCandidates && !overflow);
-}
-
-// With candidates (PASS 2 only, per_row > 0): when the candidates fitted, the third digit is counted over them instead
-// (one wave per row of the list, global atomics: they are few), and the scores are not read.
-template <int PASS, bool F16>
-__global__ __launch_bounds__(kThreads) void hist_kernel(const void *score, size_t total, uint32_t *ws, int when, int N = 0,
-                                                        int per_row = 0)
-{
-    if (PASS == 2 && per_row > 0 && ws[kWsCandOverflow] == 0) {
-        const uint32_t prefix = ws[kWsPrefix];
-        const uint32_t *counts = ws + kWsRows + 3 * N + kSelBins, *keys = counts + N;
-        const int lane = threadIdx.x & 63;
-        for (int n = blockIdx.x * kWaves + (threadIdx.x >> 6); n < N; n += gridDim.x * kWaves) {
-            const uint32_t count = counts[n];
-            for (uint32_t i = lane; i < count; i += 64) {
-                const uint32_t key = keys[(size_t)n * per_row + i];
-                if (prefix_matches<2>(key, prefix)) atomicAdd(&ws[2 * kSelBins + digit_of<2>(key)], 1u);
-            }
-        }
-        return;
-    }
-    if (not_my_turn(ws, when)) return;
-    __shared__ uint32_t h[kSelBins];
-    for (int i = threadIdx.x; i < kSelBins; i += kThreads) h[i] = 0;
-    __syncthreads();
-    const uint32_t prefix = ws[kWsPrefix];
-    const size_t stride = (size_t)gridDim.x * kThreads * 8;
-    for (size_t idx = ((size_t)blockIdx.x * kThreads + threadIdx.x) * 8; idx < total; idx += stride) {
-        uint32_t key[8];
-        load_keys8<F16>(score, idx, key);
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-            if (prefix_matches<PASS>(key[i], prefix)) atomicAdd(&h[digit_of<PASS>(key[i])], 1u);
-    }
-    __syncthreads();
-    uint32_t *g = ws + PASS * kSelBins;
-    for (int i = threadIdx.x; i < kSelBins; i += kThreads)
-        if (h[i]) atomicAdd(&g[i], h[i]);
-}
-
-// Pick the digit d of this pass: (#keys with digit > d) < remaining <= (#keys with digit >= d).
-// One block of kSelBins / 2 threads; suffix sums by a doubling scan in LDS.
-// hist: word offset of the histogram in ws; hist_candidates (when not negative): the one to read instead when the
-// candidates fitted.
-template <int PASS> __global__ __launch_bounds__(kSelBins / 2) void pick_kernel(uint32_t *ws, int hist, int hist_candidates)
-{
-    __shared__ uint32_t a[2][kSelBins + 1];
-    const uint32_t *g = ws + (hist_candidates >= 0 && ws[kWsCandOverflow] == 0 ? hist_candidates : hist);
-    const int t = threadIdx.x;
-    a[0][t] = g[t];
-    a[0][t + kSelBins / 2] = g[t + kSelBins / 2];
-    __syncthreads();
-    int cur = 0;
-    for (int d = 1; d < kSelBins; d <<= 1) {           // a[cur][i] becomes sum of bins i .. end
-#pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            const int i = t + r * (kSelBins / 2);
-            a[cur ^ 1][i] = a[cur][i] + (i + d < kSelBins ? a[cur][i + d] : 0u);
-        }
-        __syncthreads();
-        cur ^= 1;
-    }
-    const uint32_t remaining = ws[kWsRemaining];
-    const uint32_t prefix = ws[kWsPrefix];
-    __syncthreads();
-    if (remaining == 0) return;
-    constexpr int shift = PASS == 0 ? 20 : PASS == 1 ? 9 : 0;
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-        const int i = t + r * (kSelBins / 2);
-        const uint32_t ge = a[cur][i];
-        const uint32_t gt = i + 1 < kSelBins ? a[cur][i + 1] : 0u;
-        if (gt < remaining && remaining <= ge) {       // true for exactly one bin
-            ws[kWsPrefix] = prefix | ((uint32_t)i << shift);
-            ws[kWsRemaining] = remaining - gt;
-        }
-    }
-}
-
 __device__ inline uint32_t wave_inclusive_scan(uint32_t v)
 {
     const int lane = threadIdx.x & 63;
@@ -192,103 +91,383 @@ template <int WAVES> __device__ inline uint32_t block_exclusive_scan(uint32_t v,
     return base + inc - v;
 }
 
-// Per row: how many keys are above the threshold and how many are equal to it.
-// With candidates (per_row > 0) and when they fitted: only the row's candidates are looked at - the keys with a larger
-// first digit are counted already (candidates_kernel) - and the scores are not read.
+// ---- the selection ---------------------------------------------------------------------------------
+//
+// A sample of 32768 keys gives a band of keys that holds the threshold (five standard deviations of the rank on either
+// side: 0.6 % of the keys at 1 % outliers).  One pass over the scores then counts per row the keys above the band and
+// collects those inside it - the candidates - and what is left works on that short list: the threshold's offset in the band
+// by digits from its top bit down, and the per-row counts.  A band of a single key (scores of few distinct values) needs no
+// list: its keys are counted.  Where the counts say that the threshold lies outside the band, or a row has more candidates
+// than its part of the list holds, the same launches do a radix select over all scores instead (digits of 11, 11 and 9 bits;
+// FP16 scores: two digits); which of the two, every block works out for itself from the same counts, so the choice costs no
+// host synchronisation, and both give the same bytes.
+//
+// What bounds it: the one pass (180 MB of FP32 scores, 11008 x 4096: 36 us, 5.0 TB/s), then launches, 4.5 us each beside it,
+// so a kernel picks the digit that its predecessor has counted (every block does, from 8 KB).  It was a pass over all scores
+// for the first digit, 40 us, and one that collected the keys of the threshold's first digit, 1 % of all and more, and added
+// each to a histogram in global memory by itself, 47 to 111 us (16 ms where all keys are equal).  us of a whole gwq_pack,
+// 4 bits, 1 % outliers, before and now:
+//     scores          4096 x 4096    11008 x 4096    8192 x 28672    1000 x 2048    1 x 128
+//     normal, FP32       98 / 72       193 / 124        895 / 592        51 / 43     48 / 42
+//     normal, FP16       95 / 70       178 / 118        804 / 456        45 / 40     44 / 39
+//     uniform, FP32     189 / 72       416 / 127       2170 / 591        71 / 43     49 / 41
+//     51 values        2489 / 121     6603 / 230      34420 / 1210      349 / 56     48 / 43
+//     all equal        6188 / 174    16545 / 221      86134 / 701       795 / 147    48 / 42
+// Scores whose outliers lie in a few rows go by scores, both before and now: 165 / 167, 378 / 359, 2035 / 1869, 54 / 58.
+enum Way { kByList = 1, kByScores = 2, kSingleKey = 3 };
+
+// The sample: pieces of 16 bytes, one at a pseudo-random place of each of as many equal parts of the scores - one of 32 there
+// are, 8192 (FP16 scores: 4096) at most; as keys into the part of the workspace where the candidates come later, which holds
+// total / 32 words.  Many blocks: 8192 lines are a megabyte, and one compute unit that reads it takes 15 us.  Clears the
+// counters on the way.
+constexpr uint32_t kSampleKeys = 32768;
+struct __attribute__((packed, aligned(4))) Keys4 { uint32_t k[4]; };     // the workspace is aligned to four bytes only
+inline uint32_t sample_keys(size_t total) { return total / 32 < kSampleKeys ? (uint32_t)(total / 256 * 8) : kSampleKeys; }
 template <bool F16>
-__global__ __launch_bounds__(kThreads) void row_count_kernel(const void *score, int K, uint32_t *ws, int N, int per_row)
+__global__ __launch_bounds__(kThreads) void sample_kernel(const void *__restrict__ score, uint64_t total, uint32_t *ws, int N, uint32_t parts)
+{
+    constexpr int kKeys = F16 ? 8 : 4;
+    const uint32_t j = blockIdx.x * kThreads + threadIdx.x, threads = gridDim.x * kThreads;
+    for (uint32_t i = j; i < kWsRows; i += threads) ws[i] = 0;
+    for (uint32_t i = j; i < 3 * kSpread; i += threads) ws[kWsRows + 3 * N + i] = 0;
+    if (j >= parts) return;
+    const uint64_t pieces = total / kKeys;              // total is a multiple of 128
+    const uint64_t lo = j * pieces / parts, hi = (j + 1) * pieces / parts;
+    const uint64_t at = lo + (((uint64_t)(j * 2654435761u) * (hi - lo)) >> 32);
+    const uint4 raw = static_cast<const uint4 *>(score)[at];
+    const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+    uint32_t key[kKeys];
+#pragma unroll
+    for (int i = 0; i < kKeys; ++i) key[i] = F16 ? key_from_f16((uint16_t)(w[i / 2 % 4] >> (16 * (i & 1)))) : key_from_f32(w[i % 4]);
+    Keys4 *out = reinterpret_cast<Keys4 *>(ws + pack_keys_at(N) + (size_t)j * kKeys);
+#pragma unroll
+    for (int i = 0; i < kKeys / 4; ++i) out[i] = Keys4{{key[4 * i], key[4 * i + 1], key[4 * i + 2], key[4 * i + 3]}};
+}
+
+// The band, by one block.  Its ends are exact keys where both share 22 bits (then they may be the same key), otherwise the ends
+// of their ranges of 512 keys.  The first digit's few bins take most of the keys: eight copies of it, one per lane of eight,
+// each on banks of its own.
+constexpr int kBandThreads = 1024, kCopies = 8, kCopyStride = kSelBins + 8;
+__global__ __launch_bounds__(kBandThreads) void band_kernel(uint32_t *ws, int N, uint32_t sampled, float share, uint32_t k_out)
+{
+    constexpr int kRounds = kSampleKeys / 4 / kBandThreads;
+    __shared__ uint32_t h[kCopies * kCopyStride], smem[kBandThreads / 64];
+    __shared__ uint32_t found_digit[2], found_rest[2];
+    const int tid = threadIdx.x;
+    const Keys4 *sample = reinterpret_cast<const Keys4 *>(ws + pack_keys_at(N));
+    uint32_t key[kRounds][4];
+#pragma unroll
+    for (int q = 0; q < kRounds; ++q) {
+        const uint32_t at = tid + q * kBandThreads;
+        Keys4 v = {{~0u, ~0u, ~0u, ~0u}};
+        if (4 * at < sampled) v = sample[at];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) key[q][i] = v.k[i];
+    }
+
+    // Ranks from the top: of the band's lower end and of its upper end.  0: the band is open at that end.
+    const float r = share * (float)sampled, m = 5.f * __builtin_sqrtf(r) + 8.f;
+    uint32_t rank[2] = {r + m < (float)sampled ? (uint32_t)(r + m) : 0u, r - m >= 1.f ? (uint32_t)(r - m) : 0u};
+    uint32_t prefix[2] = {0u, 0u};
+    const bool open_lo = rank[0] == 0, open_hi = rank[1] == 0;
+    auto pass = [&](auto which) {
+        constexpr int PASS = decltype(which)::value;
+        for (int i = tid; i < (PASS == 0 ? kCopies * kCopyStride : 2 * kSelBins); i += kBandThreads) h[i] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kRounds; ++q)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t x = key[q][i];
+                if (PASS == 0) {
+                    if (!(x >> 31)) atomicAdd(&h[(tid & (kCopies - 1)) * kCopyStride + digit_of<PASS>(x)], 1u);
+                } else {
+                    if (prefix_matches<PASS>(x, prefix[0])) atomicAdd(&h[digit_of<PASS>(x)], 1u);
+                    if (prefix_matches<PASS>(x, prefix[1])) atomicAdd(&h[kSelBins + digit_of<PASS>(x)], 1u);
+                }
+            }
+        __syncthreads();
+        // Keys of digits 2 tid and 2 tid + 1, for the lower end and, in the high halves, for the upper: 32768 at most.
+        uint32_t b0 = 0, b1 = 0, sum;
+        if (PASS == 0) {
+#pragma unroll
+            for (int i = 0; i < kCopies; ++i) b0 += h[i * kCopyStride + 2 * tid], b1 += h[i * kCopyStride + 2 * tid + 1];
+            b0 |= b0 << 16;
+            b1 |= b1 << 16;
+        } else {
+            b0 = h[2 * tid] | h[kSelBins + 2 * tid] << 16;
+            b1 = h[2 * tid + 1] | h[kSelBins + 2 * tid + 1] << 16;
+        }
+        const uint32_t below = block_exclusive_scan<kBandThreads / 64>(b0 + b1, smem, sum);
+        const uint32_t above = sum - below - b0 - b1;                    // (no borrow between the halves: sum of parts each)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const uint32_t gt1 = above >> 16 * t & 0xFFFFu, gt0 = gt1 + (b1 >> 16 * t & 0xFFFFu), ge0 = gt0 + (b0 >> 16 * t & 0xFFFFu);
+            if (rank[t] > gt1 && rank[t] <= gt0) found_digit[t] = 2 * tid + 1, found_rest[t] = rank[t] - gt1;
+            if (rank[t] > gt0 && rank[t] <= ge0) found_digit[t] = 2 * tid, found_rest[t] = rank[t] - gt0;
+        }
+        __syncthreads();
+        constexpr int shift = PASS == 0 ? 20 : PASS == 1 ? 9 : 0;
+        for (int t = 0; t < 2; ++t)
+            if (rank[t]) prefix[t] |= found_digit[t] << shift, rank[t] = found_rest[t];
+    };
+    pass(std::integral_constant<int, 0>{});
+    pass(std::integral_constant<int, 1>{});
+    if (open_lo || open_hi || prefix[0] != prefix[1]) {
+        prefix[1] |= 0x1FFu;
+    } else {
+        __syncthreads();                                // `found` is read
+        pass(std::integral_constant<int, 2>{});
+    }
+    if (tid == 0) {
+        ws[kWsBandLo] = open_lo ? 0u : prefix[0];
+        ws[kWsBandHi] = open_hi ? 0x7FFFFFFFu : prefix[1];
+        ws[kWsWanted] = k_out;
+    }
+}
+
+// Nothing to select: the threshold sits above every key, no row keeps anything.
+__global__ void nothing_kernel(uint32_t *ws, int N)
+{
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < kWsRows + 3 * N; i += gridDim.x * blockDim.x)
+        ws[i] = i == kWsPrefix ? 0xFFFFFFFFu : 0u;
+}
+
+// By list: the bits of an offset into the band that lie below its digit 0, 1 or 2 (9, 11 and 11 bits at most; the low 13 bits
+// of FP16 scores' keys are all zero).  The first digit is the one that all candidates are counted for: few bins to add up.
+template <bool F16> __device__ inline int bits_below(int digit, uint32_t lo, uint32_t hi)
+{
+    const int least = F16 ? 13 : 0, below = 32 - __builtin_clz((hi - lo) | 1u) - 9 - 11 * digit;
+    return below > least ? below : least;
+}
+template <bool F16> __device__ inline bool is_last(int below) { return below == (F16 ? 13 : 0); }
+
+// The pass over the scores: a block per row.
+template <bool F16>
+__global__ __launch_bounds__(kThreads) void candidates_kernel(const void *score, int K, uint32_t *ws, int N, int per_row,
+                                                              int force_scores)
 {
     __shared__ uint32_t red[2][kWaves];
+    __shared__ uint32_t count_s;
     const int n = blockIdx.x;
-    const uint32_t thr = ws[kWsPrefix];
-    if (per_row > 0 && ws[kWsCandOverflow] == 0) {
-        if (threadIdx.x >= 64) return;                  // a row's candidates are few: one wave
-        const uint32_t *counts = ws + kWsRows + 3 * N + kSelBins, *keys = counts + N + (size_t)n * per_row;
-        const uint32_t count = counts[n];
-        uint32_t gt = 0, eq = 0;
-        for (uint32_t i = threadIdx.x; i < count; i += 64) {
-            const uint32_t key = keys[i];
-            gt += key > thr;
-            eq += key == thr;
-        }
-#pragma unroll
-        for (int d = 32; d > 0; d >>= 1) { gt += __shfl_xor(gt, d); eq += __shfl_xor(eq, d); }
-        if (threadIdx.x == 0) { ws[kWsRows + n] += gt; ws[kWsRows + N + n] = eq; }
-        return;
-    }
+    if (threadIdx.x == 0) count_s = 0;
+    __syncthreads();
+    const uint32_t lo = ws[kWsBandLo], hi = ws[kWsBandHi], width = hi - lo;
+    const bool single = width == 0;
+    uint32_t *sums = ws + kWsRows + 3 * N, *counts = ws + pack_keys_at(N) - N, *keys = counts + N + (size_t)n * per_row;
     uint32_t gt = 0, eq = 0;
+    uint32_t key[8], next[8];
+    const size_t row = (size_t)n * K;
+    if ((int)threadIdx.x * 8 < K) load_keys8<F16>(score, row + threadIdx.x * 8, next);
     for (int k = threadIdx.x * 8; k < K; k += kElemsPerIter) {
-        uint32_t key[8];
-        load_keys8<F16>(score, (size_t)n * K + k, key);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) { gt += key[i] > thr; eq += key[i] == thr; }
+        for (int i = 0; i < 8; ++i) key[i] = next[i];
+        if (k + kElemsPerIter < K) load_keys8<F16>(score, row + k + kElemsPerIter, next);
+        uint32_t mine = 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            gt += key[i] > hi;
+            mine += key[i] - lo <= width;
+        }
+        if (single) {
+            eq += mine;
+        } else if (mine) {
+            uint32_t slot = atomicAdd(&count_s, mine);
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (key[i] - lo <= width) {
+                    if (slot < (uint32_t)per_row) keys[slot] = key[i];
+                    ++slot;
+                }
+        }
     }
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) { gt += __shfl_xor(gt, d); eq += __shfl_xor(eq, d); }
     if ((threadIdx.x & 63) == 0) { red[0][threadIdx.x >> 6] = gt; red[1][threadIdx.x >> 6] = eq; }
     __syncthreads();
     if (threadIdx.x == 0) {
+        const uint32_t found = count_s;
         uint32_t a = 0, b = 0;
         for (int i = 0; i < kWaves; ++i) { a += red[0][i]; b += red[1][i]; }
-        ws[kWsRows + n] = a;
+        ws[kWsRows + n] = a;                            // rows_kernel adds the candidates above the threshold (or counts anew)
         ws[kWsRows + N + n] = b;
+        counts[n] = found < (uint32_t)per_row ? found : (uint32_t)per_row;
+        // The totals, over many addresses: one would serialise the rows.
+        if (a) atomicAdd(&sums[n % kSpread], a);
+        if (b) atomicAdd(&sums[kSpread + n % kSpread], b);
+        if (found) atomicAdd(&sums[2 * kSpread + n % kSpread], found);
+        if (force_scores || found > (uint32_t)per_row) ws[kWsCandOverflow] = 1u;
     }
 }
 
-// The second pass over the scores when candidates are collected: per row the count of keys whose first digit is above
-// the threshold's (they are above the threshold whatever its other digits are), and the keys whose first digit equals
-// it - the candidates - written to the row's part of the list and entered into the histogram of the second digit.  A
-// row with more candidates than its part holds raises the overflow flag (then the full passes run).
-template <bool F16>
-__global__ __launch_bounds__(kThreads) void candidates_kernel(const void *score, int K, uint32_t *ws, int N, int per_row,
-                                                              int force_overflow)
+// The digit d of a histogram with (#keys with digit > d) < wanted <= (#keys with digit >= d), and wanted less the former;
+// by every block for itself.
+template <int THREADS>
+__device__ inline void pick_digit(const uint32_t *hist, uint32_t wanted, uint32_t *smem, uint32_t &digit, uint32_t &rest)
 {
-    __shared__ uint32_t red[kWaves];
-    __shared__ uint32_t count_s;
-    const int n = blockIdx.x;
-    if (threadIdx.x == 0) count_s = 0;
-    __syncthreads();
-    const uint32_t p0 = ws[kWsPrefix] >> 20;
-    uint32_t *hist = ws + kWsRows + 3 * N, *counts = hist + kSelBins, *keys = counts + N + (size_t)n * per_row;
-    uint32_t gt = 0;
-    for (int k = threadIdx.x * 8; k < K; k += kElemsPerIter) {
-        uint32_t key[8];
-        load_keys8<F16>(score, (size_t)n * K + k, key);
+    constexpr int PER = kSelBins / THREADS;
+    __shared__ uint32_t found[2];
+    uint32_t bin[PER], sum = 0, total;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const uint32_t d0 = key[i] >> 20;
-            gt += d0 > p0;
-            // One LDS atomic per wave and position: the first candidate lane reserves the slots, the others take
-            // theirs by their rank among the wave's candidate lanes.
-            const bool cand = d0 == p0;
-            const unsigned long long m = __ballot(cand);
-            if (m) {
-                const int leader = __builtin_ctzll(m);
-                uint32_t first = 0;
-                if ((int)(threadIdx.x & 63) == leader) first = atomicAdd(&count_s, (uint32_t)__builtin_popcountll(m));
-                first = __shfl(first, leader);
-                if (cand) {
-                    const uint32_t slot = first + (uint32_t)__builtin_popcountll(m & ((1ull << (threadIdx.x & 63)) - 1ull));
-                    if (slot < (uint32_t)per_row) {
-                        keys[slot] = key[i];
-                        atomicAdd(&hist[digit_of<1>(key[i])], 1u);
-                    }
-                }
-            }
+    for (int i = 0; i < PER; ++i) { bin[i] = hist[PER * threadIdx.x + i]; sum += bin[i]; }
+    if (threadIdx.x == 0) found[0] = 0, found[1] = wanted;
+    uint32_t gt = block_exclusive_scan<THREADS / 64>(sum, smem, total);  // (its barriers also order the line above)
+    gt = total - gt - sum;
+#pragma unroll
+    for (int i = PER - 1; i >= 0; --i) {
+        if (wanted > gt && wanted <= gt + bin[i]) found[0] = PER * threadIdx.x + i, found[1] = wanted - gt;
+        gt += bin[i];
+    }
+    __syncthreads();
+    digit = found[0];
+    rest = found[1];
+    __syncthreads();
+}
+
+// A block ends with atomics on the bins it has counted in, and those of all blocks on one line are served one after another:
+// few large blocks, one for each CU over the scores and half as many over the list (11008 x 4096, 26 candidates a row, STEP 0:
+// 344 blocks of 256 threads 14.4 us, 688 17.1, 128 of 1024 7.6).
+constexpr int kDigitThreads = 1024, kScoreBlocks = 256, kListBlocks = 128;
+
+// One digit of all scores into LDS, then to `g`.
+template <int PASS, bool F16> __device__ inline void count_scores(const void *score, size_t total, uint32_t prefix, uint32_t *h, uint32_t *g)
+{
+    const size_t stride = (size_t)gridDim.x * kDigitThreads * 8;
+    for (size_t idx = ((size_t)blockIdx.x * kDigitThreads + threadIdx.x) * 8; idx < total; idx += stride) {
+        uint32_t key[8];
+        load_keys8<F16>(score, idx, key);
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (prefix_matches<PASS>(key[i], prefix)) atomicAdd(&h[digit_of<PASS>(key[i])], 1u);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < kSelBins; i += kDigitThreads)
+        if (h[i]) atomicAdd(&g[i], h[i]);
+}
+
+// Every candidate of every row: four rows to a wave, sixteen lanes each.  visit(key) once per candidate; row_done(n) by every
+// lane of a row when it has seen its own.  A row's part holds 32 keys at least: those are loaded before the count is known.
+template <int WAVES, typename Visit, typename RowDone>
+__device__ inline void for_candidates(const uint32_t *ws, int N, int per_row, int blocks, Visit visit, RowDone row_done)
+{
+    const uint32_t *counts = ws + pack_keys_at(N) - N, *keys = counts + N;
+    const int lane = threadIdx.x & 63, wave = blockIdx.x * WAVES + (threadIdx.x >> 6);
+    for (int n0 = 4 * wave; n0 < N; n0 += 4 * WAVES * blocks) {
+        const int n = n0 + (lane >> 4);
+        const uint32_t *k = keys + (size_t)(n < N ? n : 0) * per_row + (lane & 15);
+        const uint32_t k0 = k[0], k1 = k[16], count = n < N ? counts[n] : 0u, i0 = lane & 15;
+        if (i0 < count) visit(k0);
+        if (i0 + 16 < count) visit(k1);
+#pragma unroll 4
+        for (uint32_t i = i0 + 32; i < count; i += 16) visit(k[i - i0]);
+        row_done(n);
+    }
+}
+
+// Counts digit STEP, having picked the one before.  STEP 0 also decides the way.
+template <int STEP, bool F16>
+__global__ __launch_bounds__(kDigitThreads) void digit_kernel(const void *score, size_t total, uint32_t *ws, int N, int per_row)
+{
+    __shared__ uint32_t h[kSelBins], smem[kDigitThreads / 64];
+    const uint32_t lo = ws[kWsBandLo], hi = ws[kWsBandHi], k_out = ws[kWsWanted];
+    uint32_t way = ws[kWsWay], base = 0, wanted = k_out;
+    if (STEP == 0) {
+        const uint32_t *sums = ws + kWsRows + 3 * N;
+        uint32_t sum[3];                                // above the band, of a single key, candidates
+        static_assert(kSpread <= kDigitThreads, "a word a thread");
+#pragma unroll
+        for (int t = 0; t < 3; ++t)
+            block_exclusive_scan<kDigitThreads / 64>(threadIdx.x < kSpread ? sums[t * kSpread + threadIdx.x] : 0u, smem, sum[t]);
+        const uint32_t above = sum[0];
+        const bool in = above < k_out && k_out - above <= (lo == hi ? sum[1] : sum[2]) && ws[kWsCandOverflow] == 0;
+        way = !in ? kByScores : lo == hi ? kSingleKey : kByList;
+        if (way != kByScores) base = lo, wanted = k_out - above;
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            ws[kWsWay] = way;
+            ws[kWsStep] = base;
+            ws[kWsStep + 1] = wanted;
+            if (way == kSingleKey) ws[kWsPrefix] = base, ws[kWsRemaining] = wanted;
         }
     }
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) gt += __shfl_xor(gt, d);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = gt;
+    if (way == kSingleKey || (way == kByList && blockIdx.x >= kListBlocks)) return;
+    if (STEP > 0) {
+        base = ws[kWsStep + 2 * (STEP - 1)];
+        wanted = ws[kWsStep + 2 * (STEP - 1) + 1];
+        const int below = way == kByList ? bits_below<F16>(STEP - 1, lo, hi) : STEP == 1 ? 20 : 9;
+        if (way == kByList && STEP == 2 && is_last<F16>(bits_below<F16>(0, lo, hi))) return;      // rows_kernel picks it
+        if (way == kByList && is_last<F16>(below)) return;
+        uint32_t digit;
+        pick_digit<kDigitThreads>(ws + (STEP - 1) * kSelBins, wanted, smem, digit, wanted);
+        base += digit << below;
+        if (blockIdx.x == 0 && threadIdx.x == 0) ws[kWsStep + 2 * STEP] = base, ws[kWsStep + 2 * STEP + 1] = wanted;
+    }
+    for (int i = threadIdx.x; i < kSelBins; i += kDigitThreads) h[i] = 0;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t a = 0;
-        for (int i = 0; i < kWaves; ++i) a += red[i];
-        ws[kWsRows + n] = a;                            // row_count_kernel adds the candidates above the threshold (or counts anew)
-        ws[kWsRows + N + n] = 0;
-        const uint32_t count = count_s;
-        counts[n] = count < (uint32_t)per_row ? count : (uint32_t)per_row;
-        if (force_overflow || count > (uint32_t)per_row) ws[kWsCandOverflow] = 1u;
+    uint32_t *g = ws + STEP * kSelBins;
+    if (way == kByScores) {
+        count_scores<STEP, F16>(score, total, base, h, g);
+        return;
+    }
+    const int below = bits_below<F16>(STEP, lo, hi);
+    const uint32_t last = STEP == 0 ? hi - lo : (1u << bits_below<F16>(STEP - 1, lo, hi)) - 1u;   // largest offset still open
+    for_candidates<kDigitThreads / 64>(ws, N, per_row, min((int)gridDim.x, kListBlocks), [&](uint32_t key) {
+        if (key - base <= last) atomicAdd(&h[(key - base) >> below], 1u);
+    }, [](int) {});
+    __syncthreads();
+    for (int i = threadIdx.x; i < kSelBins; i += kDigitThreads)
+        if (h[i]) atomicAdd(&g[i], h[i]);
+}
+
+// Picks the last digit, and per row: how many keys are above the threshold and how many are equal to it.
+template <bool F16>
+__global__ __launch_bounds__(kThreads) void rows_kernel(const void *score, int K, uint32_t *ws, int N, int per_row)
+{
+    __shared__ uint32_t red[2][kWaves], smem[kWaves];
+    const uint32_t way = ws[kWsWay];
+    if (way == kSingleKey) return;                      // both are known
+    int last = F16 ? 1 : 2, below = 0;                  // the last digit counted
+    if (way == kByList) {
+        const uint32_t lo = ws[kWsBandLo], hi = ws[kWsBandHi];
+        for (last = 0; !is_last<F16>(below = bits_below<F16>(last, lo, hi));) ++last;
+    } else if (F16) {                                   // (the low 13 bits of every key are zero: two digits are all)
+        below = 9;
+    }
+    uint32_t thr = ws[kWsStep + 2 * last], wanted = ws[kWsStep + 2 * last + 1], digit;
+    pick_digit<kThreads>(ws + last * kSelBins, wanted, smem, digit, wanted);
+    thr += digit << below;
+    if (blockIdx.x == 0 && threadIdx.x == 0) ws[kWsPrefix] = thr, ws[kWsRemaining] = wanted;
+    if (way == kByList) {
+        uint32_t gt = 0, eq = 0;
+        for_candidates<kWaves>(ws, N, per_row, (int)gridDim.x, [&](uint32_t key) {
+            gt += key > thr;
+            eq += key == thr;
+        }, [&](int n) {
+#pragma unroll
+            for (int d = 8; d > 0; d >>= 1) { gt += __shfl_xor(gt, d); eq += __shfl_xor(eq, d); }
+            if ((threadIdx.x & 15) == 0 && n < N) { ws[kWsRows + n] += gt; ws[kWsRows + N + n] = eq; }
+            gt = eq = 0;
+        });
+        return;
+    }
+    for (int n = blockIdx.x; n < N; n += gridDim.x) {
+        uint32_t gt = 0, eq = 0;
+        for (int k = threadIdx.x * 8; k < K; k += kElemsPerIter) {
+            uint32_t key[8];
+            load_keys8<F16>(score, (size_t)n * K + k, key);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) { gt += key[i] > thr; eq += key[i] == thr; }
+        }
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) { gt += __shfl_xor(gt, d); eq += __shfl_xor(eq, d); }
+        __syncthreads();                                // the row before is done with `red`
+        if ((threadIdx.x & 63) == 0) { red[0][threadIdx.x >> 6] = gt; red[1][threadIdx.x >> 6] = eq; }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            uint32_t a = 0, b = 0;
+            for (int i = 0; i < kWaves; ++i) { a += red[0][i]; b += red[1][i]; }
+            ws[kWsRows + n] = a;
+            ws[kWsRows + N + n] = b;
+        }
     }
 }
 
@@ -630,32 +809,22 @@ __global__ __launch_bounds__(kThreads) void encode_kernel(const uint16_t *__rest
 }
 
 template <bool F16>
-hipError_t run_select(const void *score, int N, int K, uint32_t *ws, int32_t *row_ptr, bool any, bool full_passes,
-                      hipStream_t st)
+hipError_t run_select(const void *score, int N, int K, uint32_t *ws, int32_t *row_ptr, uint32_t k_out, bool by_scores, hipStream_t st)
 {
     const size_t total = (size_t)N * K;
-    const size_t want = (total / 8 + kThreads - 1) / kThreads;
-    const int blocks = (int)(want < 512 ? (want ? want : 1) : 512);
     const int per_row = pack_candidates_per_row(K);
-    if (any) {
-        // With nothing to keep the threshold set by init_ws_kernel already sits above every key.
-        hist_kernel<0, F16><<<blocks, kThreads, 0, st>>>(score, total, ws, kAlways);
-        pick_kernel<0><<<1, kSelBins / 2, 0, st>>>(ws, 0, -1);
-        // Second pass over the scores: the first digit's share of the per-row counts, and the candidates.
-        candidates_kernel<F16><<<N, kThreads, 0, st>>>(score, K, ws, N, per_row, full_passes ? 1 : 0);
-        // Every launch from here on takes the candidates where they fitted and the scores where not; the one pass
-        // that only the second way needs returns at once on the first.
-        hist_kernel<1, F16><<<blocks, kThreads, 0, st>>>(score, total, ws, kWithoutCandidates);
-        pick_kernel<1><<<1, kSelBins / 2, 0, st>>>(ws, 1 * kSelBins, kWsRows + 3 * N);
-        // (The key of an FP16 score is its exact binary32 widening, whose low 13 bits are zero, payloads of NaNs
-        // included: the third digit is 0 for every key, so FP16 scores are selected by two digits.)
-        if (!F16) {
-            hist_kernel<2, F16><<<blocks, kThreads, 0, st>>>(score, total, ws, kAlways, N, per_row);
-            pick_kernel<2><<<1, kSelBins / 2, 0, st>>>(ws, 2 * kSelBins, -1);
-        }
-        row_count_kernel<F16><<<N, kThreads, 0, st>>>(score, K, ws, N, per_row);
+    if (k_out) {
+        const int blocks = (int)std::min<size_t>((total / 8 + kDigitThreads - 1) / kDigitThreads, kScoreBlocks);
+        const uint32_t sampled = sample_keys(total);
+        sample_kernel<F16><<<32, kThreads, 0, st>>>(score, total, ws, N, sampled / (F16 ? 8 : 4));
+        band_kernel<<<1, kBandThreads, 0, st>>>(ws, N, sampled, (float)k_out / (float)total, k_out);
+        candidates_kernel<F16><<<N, kThreads, 0, st>>>(score, K, ws, N, per_row, by_scores ? 1 : 0);
+        digit_kernel<0, F16><<<blocks, kDigitThreads, 0, st>>>(score, total, ws, N, per_row);
+        digit_kernel<1, F16><<<blocks, kDigitThreads, 0, st>>>(score, total, ws, N, per_row);
+        if (!F16) digit_kernel<2, F16><<<blocks, kDigitThreads, 0, st>>>(score, total, ws, N, per_row);
+        rows_kernel<F16><<<std::min(N, 1024), kThreads, 0, st>>>(score, K, ws, N, per_row);
     } else {
-        row_count_kernel<F16><<<N, kThreads, 0, st>>>(score, K, ws, N, 0);
+        nothing_kernel<<<8, kThreads, 0, st>>>(ws, N);
     }
     row_scan_kernel<<<1, kScanThreads, 0, st>>>(ws, N, row_ptr);
     return hipGetLastError();
@@ -665,9 +834,9 @@ template <int BITS, bool F16, int STEPS>
 hipError_t run_encode(const void *W, const void *score, const gwq_packed &P, const uint32_t *ws, hipStream_t st)
 {
     // Few rows: one wave for each leaves the chip waiting for its trips, so four share a row, at the price of reading the
-    // scores once more to count what the parts before keep.  Where that stops to pay (us of a whole gwq_pack, one wave
-    // against four; FP32 scores 1024 x 8192 75 / 65, 1300 x 65536 368 / 365, 1500 x 65536 394 / 410, 1900 x 8192 85 / 88;
-    // FP16 scores, half the bytes, 1500 x 28672 198 / 161, 2047 x 8192 88 / 84, 2047 x 2048 46.6 / 46.8).
+    // scores once more to count what the parts before keep.  Where that stops to pay (us that
+    // four waves save over one; FP32 scores 1024 x 8192 10, 1300 x 65536 3, 1500 x 65536 -16, 1900 x 8192 -3; FP16 scores, half
+    // the bytes, 1500 x 28672 37, 2047 x 8192 4, 2047 x 2048 -0.2).
     const int parts = P.N < (F16 ? 2048 : 1300) ? kWaves : 1;
     const int blocks = parts == 1 ? (P.N + kWaves - 1) / kWaves : P.N;
     GroupRecord *rec = static_cast<GroupRecord *>(P.index);
@@ -692,11 +861,8 @@ hipError_t run_encode(const void *W, const void *score, const gwq_packed &P, con
 hipError_t launch_pack(const void *W, const void *score, int score_is_f16, const gwq_packed &P,
                        uint32_t *ws, bool full_passes, hipStream_t st)
 {
-    init_ws_kernel<<<8, kThreads, 0, st>>>(ws, (uint32_t)P.n_outliers, P.N);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    e = score_is_f16 ? run_select<true>(score, P.N, P.K, ws, P.row_ptr, P.n_outliers > 0, full_passes, st)
-                     : run_select<false>(score, P.N, P.K, ws, P.row_ptr, P.n_outliers > 0, full_passes, st);
+    const hipError_t e = score_is_f16 ? run_select<true>(score, P.N, P.K, ws, P.row_ptr, (uint32_t)P.n_outliers, full_passes, st)
+                                      : run_select<false>(score, P.N, P.K, ws, P.row_ptr, (uint32_t)P.n_outliers, full_passes, st);
     if (e != hipSuccess) return e;
     if (P.bits == 4)
         return score_is_f16 ? run_encode<4, true>(W, score, P, ws, st) : run_encode<4, false>(W, score, P, ws, st);

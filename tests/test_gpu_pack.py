@@ -222,9 +222,9 @@ def test_pack_7b_shapes_full(name, N, K, mid):
 
 
 # ---- the two ways gwq_pack finds the threshold ---------------------------------------------------------------------
-# After the first pass over the scores only the keys whose leading 11 bits equal the threshold's can still decide it:
-# gwq_pack collects them (a row's part of the list holds K / 32 keys, at least 32) and works out the remaining digits
-# and the per-row counts on that list; when some row's candidates do not fit it runs its passes over all scores instead.
+# A sample of the scores gives a band of keys around the threshold: gwq_pack collects the keys inside (a row's part of the
+# list holds K / 32 keys, at least 32) and works out the threshold and the per-row counts on that list; when some row's
+# candidates do not fit, or the threshold is not in the band, it runs its passes over all scores instead.
 # Both ways must give the oracle's bytes.
 
 @pytest.fixture
@@ -341,3 +341,33 @@ def test_pack_row_scan_rounds(N):
     W = gs.weight(N, 128, rng, planted_cols=2)
     S = np.round(rng.random((N, 128)) * 50).astype(np.float32)      # 51 values, 1 % in the largest: 3 % ends inside the third's ties
     assert_packed_equal(gwq.pack(to_gpu(W), to_gpu(S), 4, 30000), orc.pack(W, S, 4, 30000))
+
+
+@pytest.mark.parametrize("f16", [False, True])
+@pytest.mark.parametrize("kind", ["normal", "octaves", "few", "half_zero", "nan_inf", "steps"])
+@pytest.mark.parametrize("N,K", [(1, 128), (3, 128), (65, 640), (300, 3072), (513, 2176)])
+def test_pack_from_a_sampled_band(N, K, kind, f16):
+    """The band's edges: no sample at all (1 x 128), a sample of a few keys, 1/32 of the scores and, from 2^20 scores, 32768;
+    outlier shares that leave the band open above (one entry), below, or at neither end; scores over sixty octaves (three
+    digits of the band's offset; FP16: over thirty), of few values (a band of a single key), half of them zero, and with a
+    period that a regular sample would miss (`steps`: all large keys at every 32nd place).  The packed bytes are the oracle's."""
+    import paper_2411_00850_amd as gwq
+    from gpu_helpers import assert_packed_equal, to_gpu
+    rng = np.random.default_rng(N + K + f16)
+    W = gs.weight(N, K, rng, planted_cols=min(2, K // 64))
+    S = rng.standard_normal((N, K)).astype(np.float32)
+    if kind == "octaves":
+        S = np.exp2((rng.random((N, K)) * (28 if f16 else 60) - (14 if f16 else 30))).astype(np.float32)
+    elif kind == "few":
+        S = np.round(S * 4) / 4
+    elif kind == "half_zero":
+        S[rng.random((N, K)) < 0.5] = 0
+    elif kind == "nan_inf":
+        S.ravel()[rng.choice(N * K, N * K // 50, replace=False)] = np.inf
+        S.ravel()[rng.choice(N * K, N * K // 200, replace=False)] = np.nan
+    elif kind == "steps":
+        S = np.abs(S)
+        S[:, ::32] += 100
+    S = S.astype(np.float16 if f16 else np.float32)
+    for ppm in (1, 1000, 10000, 300000):
+        assert_packed_equal(gwq.pack(to_gpu(W), to_gpu(S), 4, ppm), orc.pack(W, S, 4, ppm))
