@@ -1082,11 +1082,13 @@ template <int BITS> struct TileRegs {
 // GATED: layers 2y and 2y + 1 of the batch are gate and up of a gated pair (one N, one K, one X).  A block takes the tiles of
 // both in turn, `tiles_per_block` of each; the threads that add a gate tile's partial sums keep them in a register, add the
 // up tile's one step later and store H = silu(gate) * up.
-template <int BITS, int MR, bool GATED = false>
+template <int BITS, int MR, bool GATED = false, bool BF16 = false>
 __global__ __launch_bounds__(512) void decode_stream_kernel(const DecodeBatch batch, const int tiles_per_block,
                                                             const int ent_cap)
 {
     constexpr int U = kStreamU, RB = MR / 4, SPLIT = 4 / RB;
+    static_assert(!BF16 || !GATED, "bfloat16 activations: plain products only");
+    typedef std::conditional_t<BF16, __bf16, _Float16> act_t;          // X and Y; both 16 bits wide
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     const DecodeProblem &pr = batch.p[GATED ? 2 * blockIdx.y : blockIdx.y];
     const int N = pr.N, K = pr.K;
@@ -1096,8 +1098,8 @@ __global__ __launch_bounds__(512) void decode_stream_kernel(const DecodeBatch ba
     const int32_t *__restrict__ const row_ptr0 = pr.row_ptr;
     const uint16_t *__restrict__ const col_idx0 = pr.col_idx;
     const uint16_t *__restrict__ const out_val0 = pr.out_val;
-    const _Float16 *__restrict__ X = pr.X;
-    _Float16 *__restrict__ Y = pr.Y;                    // of a gated pair both layers' Y is H
+    const act_t *__restrict__ X = reinterpret_cast<const act_t *>(pr.X);
+    act_t *__restrict__ Y = reinterpret_cast<act_t *>(pr.Y);            // of a gated pair both layers' Y is H
     const int csr_last_vec0 = pr.csr_last_vec, sc_last_vec = pr.sc_last_vec, zp_last_vec = pr.zp_last_vec;
     asm volatile("" ::"s"(qweight0), "s"(scales0), "s"(zeros0), "s"(row_ptr0), "s"(col_idx0), "s"(out_val0), "s"(X), "s"(Y),
                  "s"(K), "s"(csr_last_vec0), "s"(sc_last_vec), "s"(zp_last_vec));
@@ -1128,7 +1130,14 @@ __global__ __launch_bounds__(512) void decode_stream_kernel(const DecodeBatch ba
     unsigned char *const meta_lds = reinterpret_cast<unsigned char *>(red) + 2 * (uint32_t)nwaves * 1024;
     const uint32_t meta_bytes = 48u * gpr;              // scales [16][gpr] halves, then zero points [16][gpr] bytes
 
-    const DecodeConsts dc(BITS);
+    const std::conditional_t<BF16, DecodeConstsBf16, DecodeConsts> dc(BITS);
+    typedef act_t act2 __attribute__((ext_vector_type(2)));
+    auto mfma = [](u32x4 a, u32x4 w, float4v c) {
+        if constexpr (BF16)
+            return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, w), c, 0, 0, 0);
+        else
+            return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, a), __builtin_bit_cast(half8, w), c, 0, 0, 0);
+    };
     constexpr uint32_t group_bytes = words_per_group(BITS) * 4;
     const uint32_t code_end = (uint32_t)N * gpr * group_bytes;
 
@@ -1267,8 +1276,9 @@ __global__ __launch_bounds__(512) void decode_stream_kernel(const DecodeBatch ba
 #pragma unroll
         for (int sq = 0; sq < 2; ++sq) {
             const int at = b == 2 * sq + (r >> 3) ? (r & 7) : -1;    // position of this lane's 1.0, if it has one
-            sel[sq] = u32x4{at == 0 ? 0x3C00u : at == 1 ? 0x3C000000u : 0u, at == 2 ? 0x3C00u : at == 3 ? 0x3C000000u : 0u,
-                            at == 4 ? 0x3C00u : at == 5 ? 0x3C000000u : 0u, at == 6 ? 0x3C00u : at == 7 ? 0x3C000000u : 0u};
+            constexpr uint32_t one = BF16 ? 0x3F80u : 0x3C00u;
+            sel[sq] = u32x4{at == 0 ? one : at == 1 ? one << 16 : 0u, at == 2 ? one : at == 3 ? one << 16 : 0u,
+                            at == 4 ? one : at == 5 ? one << 16 : 0u, at == 6 ? one : at == 7 ? one << 16 : 0u};
         }
 #pragma unroll
         for (int u = 0; u < U; ++u)
@@ -1279,23 +1289,34 @@ __global__ __launch_bounds__(512) void decode_stream_kernel(const DecodeBatch ba
                 for (int j = 0; j < 4; ++j)
 #pragma unroll
                     for (int sq = 0; sq < 2; ++sq)
-                        t[j][sq] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-                            __builtin_bit_cast(half8, xa[u][j]), __builtin_bit_cast(half8, sel[sq]),
-                            float4v{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                        t[j][sq] = mfma(xa[u][j], sel[sq], float4v{0.f, 0.f, 0.f, 0.f});
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
 #pragma unroll
                     for (int sq = 0; sq < 2; ++sq) {
                         const uint32_t col = (uint32_t)(g0 + u) * kGroup + 64 * sq + 32 * (r >> 3) + 8 * j + (r & 7);
-                        const half2v lo = half2v{(_Float16)t[j][sq][0], (_Float16)t[j][sq][1]};
-                        const half2v hi = half2v{(_Float16)t[j][sq][2], (_Float16)t[j][sq][3]};
+                        const act2 lo = act2{(act_t)t[j][sq][0], (act_t)t[j][sq][1]};
+                        const act2 hi = act2{(act_t)t[j][sq][2], (act_t)t[j][sq][3]};
                         if (b < RB)
                             *reinterpret_cast<uint2 *>(xt + xt_offset<MR>(col, b)) =
                                 uint2{__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
                     }
                 __builtin_amdgcn_sched_barrier(0);
             }
+    }
+
+    // bfloat16: the operands are 128 + q (exact), so a group's product with the zero point is taken off with the sums of X
+    // over the group: the same for every tile.
+    float4v xsum[BF16 ? U : 1];
+    if constexpr (BF16) {
+        const u32x4 ones = u32x4{kBf16Ones, kBf16Ones, kBf16Ones, kBf16Ones};
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            xsum[u] = float4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) xsum[u] = mfma(xa[u][j], ones, xsum[u]);
+        }
     }
 
     __syncthreads();                                    // tile 0's scales and zero points are in LDS (and XT, for later)
@@ -1319,7 +1340,7 @@ __global__ __launch_bounds__(512) void decode_stream_kernel(const DecodeBatch ba
                 for (int sp = 0; sp < SPLIT; ++sp) sum += src[(w * 4 + e) * 64 + (l & 15) + 16 * (bq + RB * sp)];
             const int nn = row0 + (l & 15), m = 4 * bq + e;
             if (GATED && !(it & 1)) gate_sum = sum;     // this thread adds the same entry of the up tile next (at least 256 threads)
-            else if (nn < N && m < M) Y[(size_t)m * N + nn] = (_Float16)(GATED ? silu(gate_sum) * sum : sum);
+            else if (nn < N && m < M) Y[(size_t)m * N + nn] = (act_t)(GATED ? silu(gate_sum) * sum : sum);
         };
         if (nthreads >= 256) {
             const int grp = (GATED ? it >> 1 : it) % red_groups;
@@ -1353,12 +1374,16 @@ __global__ __launch_bounds__(512) void decode_stream_kernel(const DecodeBatch ba
             const _Float16 s = __builtin_bit_cast(_Float16, (uint16_t)(sc_lane[u] & keep));
             const uint32_t z = BITS == 3 ? zp_lane[u] & keep : zp_lane[u];
             u32x4 wb[4];
-            T.slot[u].decode(z, b, dc, wb, tail_lane4);
+            if constexpr (BF16) T.slot[u].decode_bf16(b, dc, wb, tail_lane4);
+            else T.slot[u].decode(z, b, dc, wb, tail_lane4);
             float4v part = float4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                part = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, xa[u][j]),
-                                                              __builtin_bit_cast(half8, wb[j]), part, 0, 0, 0);
+            for (int j = 0; j < 4; ++j) part = mfma(xa[u][j], wb[j], part);
+            if constexpr (BF16) {
+                const float zc = -(float)(128u + zp_lane[u]);           // any byte gives a finite constant
+#pragma unroll
+                for (int e = 0; e < 4; ++e) part[e] = __builtin_fmaf(zc, xsum[u][e], part[e]);
+            }
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[e] = __builtin_fmaf((float)s, part[e], acc[e]);
         }
@@ -1397,7 +1422,7 @@ __global__ __launch_bounds__(512) void decode_stream_kernel(const DecodeBatch ba
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const float v = (float)__builtin_bit_cast(_Float16, (uint16_t)(entry[i] >> 16));
-                const half2v x01 = __builtin_bit_cast(half2v, xv[i].x), x23 = __builtin_bit_cast(half2v, xv[i].y);
+                const act2 x01 = __builtin_bit_cast(act2, xv[i].x), x23 = __builtin_bit_cast(act2, xv[i].y);
                 acc[0] = __builtin_fmaf(v, (float)x01[0], acc[0]);
                 acc[1] = __builtin_fmaf(v, (float)x01[1], acc[1]);
                 acc[2] = __builtin_fmaf(v, (float)x23[0], acc[2]);
@@ -1411,7 +1436,7 @@ __global__ __launch_bounds__(512) void decode_stream_kernel(const DecodeBatch ba
                 const uint32_t col = load_u16_now((GATED ? layer_of(it).col_idx : col_idx0) + j);
                 const float v = (float)__builtin_bit_cast(_Float16, (uint16_t)load_u16_now((GATED ? layer_of(it).out_val : out_val0) + j));
                 const uint2 x = *reinterpret_cast<const uint2 *>(xt + xt_offset<MR>(col, xq));
-                const half2v x01 = __builtin_bit_cast(half2v, x.x), x23 = __builtin_bit_cast(half2v, x.y);
+                const act2 x01 = __builtin_bit_cast(act2, x.x), x23 = __builtin_bit_cast(act2, x.y);
                 acc[0] = __builtin_fmaf(v, (float)x01[0], acc[0]);
                 acc[1] = __builtin_fmaf(v, (float)x01[1], acc[1]);
                 acc[2] = __builtin_fmaf(v, (float)x23[0], acc[2]);
@@ -1610,7 +1635,7 @@ hipError_t launch_decode(int count, const gwq_packed *const *P, const void *cons
     }
     // The streaming kernel: rows of at most 32 groups (8 waves of 4), XT[K][rows] in LDS.  By default for
     // the batches the lean kernel does not take.
-    if (!fine && !tune.bf16 && tune.stream != 1 && (M > 4 || (tune.stream == 2 && !tune.gated_pairs)) && max_gpr <= 8 * kStreamU) {
+    if (!fine && tune.stream != 1 && (M > 4 || (tune.stream == 2 && !tune.gated_pairs && !tune.bf16)) && max_gpr <= 8 * kStreamU) {
         const int nwaves = (max_gpr + kStreamU - 1) / kStreamU, nthreads = 64 * nwaves;
         const int mr = M <= 4 ? 4 : M <= 8 ? 8 : 16;
         const size_t xt = (size_t)max_gpr * kGroup * 2 * mr, red = (size_t)2 * nwaves * 1024;
@@ -1631,37 +1656,46 @@ hipError_t launch_decode(int count, const gwq_packed *const *P, const void *cons
             int tpb = tune.tiles;
             if (tpb <= 0)
                 for (tpb = 1;; ++tpb) {
-                    int total = 0;
-                    for (int i = 0; i < count; i += step) total += ((P[i]->N + 15) / 16 + tpb - 1) / tpb;
-                    if (total <= slots) break;
+                    int needed = 0;
+                    for (int i = 0; i < count; i += step) needed += ((P[i]->N + 15) / 16 + tpb - 1) / tpb;
+                    if (needed <= slots) break;
                 }
-            // A block that gets a single tile has nothing to pipeline and pays the set-up of XT for it: the wide
-            // kernel is faster there (4096 channels on 256 CUs).  A gated block has two tiles at least: it loses to two
+            int total = 0;
+            for (int i = 0; i < count; ++i) total += (P[i]->N + 15) / 16;
+            // A block that gets a single tile has nothing to pipeline and pays the set-up of XT for it: with long rows the wide
+            // kernel is faster there (4096 channels on 256 CUs).  Not with rows of up to 2048: this one's blocks have a wave per
+            // four groups and several of them share a CU, the wide kernel's stage X with few waves in one block per CU and go
+            // from tile to tile (us, M = 16, FP16: 4096 x 2048 7.3 against 6.6 here, 8192 x 512 9.7 against 6.0, 28672 x 512 24.7
+            // against 9.2); up to 12 rows only below 1280 or where the wide kernel's blocks have several tiles (M = 9: 1024 x 1664
+            // 6.4 against 6.7 here, 2048 x 1024 6.4 against 5.7).  bfloat16 has a second term per group to add up: two tiles do not pay with long rows (M = 9: 8192 x
+            // 4096 10.8 against 11.7 here), three do (11008 x 4096 14.1 against 13.8, 32000 x 4096 32.4 against 23.6).  A gated block has two tiles at least: it loses to two
             // products and silu_mul_kernel with one pair and long rows (us, 2048 x 4096, M = 16: 11.3 against 9.3), not with
             // rows of 2048 (1000 x 2048: 8.3 against 9.3) or several pairs (11008 x 4096: 20.8 against 22.2).  The threads that add
             // up a tile must be there for both: four waves.
             const bool take = tune.gated_pairs ? nthreads >= 256 && (tpb >= 2 || max_gpr <= 16 || tune.tiles > 0)
-                                               : tune.stream == 2 || tune.tiles > 0 || tpb >= 2;
+                                               : tune.stream == 2 || tune.tiles > 0 || tpb >= (tune.bf16 ? 3 : 2) ||
+                                                     (max_gpr <= 16 && (max_gpr <= 10 || M > 12 || total > device_cus()));
             batch.nwaves = nwaves;
             const int grid = (blocks + tpb - 1) / tpb;
             if (take && describe) {
                 snprintf(describe->text, sizeof(describe->text),
-                         "decode_stream_kernel<%d,%d> grid %dx%d block %d lds %zu tiles_per_block %d", bits, mr, grid,
-                         count, nthreads, lds, tpb);
+                         "decode_stream_kernel<%d,%d%s> grid %dx%d block %d lds %zu tiles_per_block %d", bits, mr,
+                         tune.bf16 ? ",false,true" : "", grid, count, nthreads, lds, tpb);
                 return hipSuccess;
             }
             hipError_t e = hipErrorInvalidValue;
-#define GWQ_STREAM(B, RR, G) \
-    if (take && bits == B && mr == RR && tune.gated_pairs == G) { \
+#define GWQ_STREAM(B, RR, G, H) \
+    if (take && bits == B && mr == RR && tune.gated_pairs == G && tune.bf16 == H) { \
         static std::atomic<uint32_t> lds_allowed{0}; \
-        e = allow_dynamic_lds(reinterpret_cast<const void *>(&decode_stream_kernel<B, RR, G>), (int)kMaxLds, lds_allowed); \
+        e = allow_dynamic_lds(reinterpret_cast<const void *>(&decode_stream_kernel<B, RR, G, H>), (int)kMaxLds, lds_allowed); \
         if (e != hipSuccess) return e; \
-        decode_stream_kernel<B, RR, G><<<dim3(grid, count / step), nthreads, lds, st>>>(batch, tpb, ent_cap); \
+        decode_stream_kernel<B, RR, G, H><<<dim3(grid, count / step), nthreads, lds, st>>>(batch, tpb, ent_cap); \
         return hipGetLastError(); \
     }
-            GWQ_STREAM(4, 4, false) GWQ_STREAM(4, 8, false) GWQ_STREAM(4, 16, false)
-            GWQ_STREAM(3, 4, false) GWQ_STREAM(3, 8, false) GWQ_STREAM(3, 16, false)
-            GWQ_STREAM(4, 8, true) GWQ_STREAM(4, 16, true) GWQ_STREAM(3, 8, true) GWQ_STREAM(3, 16, true)
+            GWQ_STREAM(4, 4, false, false) GWQ_STREAM(4, 8, false, false) GWQ_STREAM(4, 16, false, false)
+            GWQ_STREAM(3, 4, false, false) GWQ_STREAM(3, 8, false, false) GWQ_STREAM(3, 16, false, false)
+            GWQ_STREAM(4, 8, true, false) GWQ_STREAM(4, 16, true, false) GWQ_STREAM(3, 8, true, false) GWQ_STREAM(3, 16, true, false)
+            GWQ_STREAM(4, 8, false, true) GWQ_STREAM(4, 16, false, true) GWQ_STREAM(3, 8, false, true) GWQ_STREAM(3, 16, false, true)
 #undef GWQ_STREAM
             if (take) return e;
         }

@@ -153,3 +153,26 @@ def test_bf16_7b_shape_full():
     rng = np.random.default_rng(4)
     for M in (1, 16, 256):
         _check(D, P, gs.activations(M, 4096, rng).astype(np.float32), f"bf16 4096x4096 M={M}")
+
+
+@pytest.mark.parametrize("bits", [4, 3])
+@pytest.mark.parametrize("N,K,ppm,tiles", [(40, 128, 10000, 1), (200, 640, 10000, 2), (100, 4096, 10000, 3), (330, 2176, 300000, 7),
+                                           (16 * 300 + 5, 2560, 10000, 0)])
+def test_bf16_streaming_decode(bits, N, K, ppm, tiles):
+    """The streaming kernel with bfloat16 activations: one, two and more tiles a block, the last one cut; waves whose groups
+    end early; channels with more outliers than the staged window holds; its own choice (tiles = 0: 301 tiles) last.
+    Activations beyond the FP16 range go through its transposed copy of X too."""
+    import paper_2411_00850_amd as gwq
+    from gpu_helpers import upload_packed
+    P, rng = _problem(N + K + bits, N, K, bits, ppm)
+    D = upload_packed(P)
+    gwq.tuning_set("decode_stream", 2 if tiles else 0)
+    gwq.tuning_set("decode_tiles", tiles)
+    try:
+        for M in (5, 8, 9, 11, 16):
+            x = gs.activations(M, K, rng).astype(np.float32)
+            x[:, 3] *= 1e8
+            _check(D, P, x, f"bf16 stream N={N} K={K} M={M} bits={bits}")
+    finally:
+        gwq.tuning_set("decode_stream", 0)
+        gwq.tuning_set("decode_tiles", 0)
