@@ -13,12 +13,13 @@
 // per SIMD, multiply; four or eight producer waves turn the next group's codes into FP16 (exact q - z, one multiply by the
 // scale) and store them to one of two LDS buffers, then the group's outliers over their zeros.  One barrier per group.
 //
-// What bounds it: a group takes a producer wave about 1000 clocks per run of 16 channels beside its neighbours (85 vector
-// instructions, six stores), which is longer than the MFMAs of a tile of 128 rows or less; hence eight producers where the
-// registers allow them (28672 x 8192, M = 64: 83 us with four, 61 with eight; M = 301, tiles of 160: 191 and 166).  With 256 rows
-// MFMAs take 2048 of about 3300 clocks; over whole launches the matrix cores are busy 53 (11008 x 4096) to 60 % of the
-// clocks.  The clock is 1.9 to 2.0 GHz under this load, that of a loop of nothing but MFMAs, so clocks saved gain less than their
-// share (8192 x 8192, M = 1024: 139 us through the LDS, 118 here, 1.16 PFLOP/s).
+// What bounds it: a group takes a producer wave 500 to 900 clocks per run of 16 channels beside its neighbours (95 vector
+// instructions, two producers a SIMD one after the other) and 400 for its stores, which is longer than the MFMAs of a tile of
+// 128 rows or less; hence eight producers where the registers allow them (28672 x 8192, M = 64: 83 us with four, 61 with eight;
+// M = 301, tiles of 160: 191 and 166).  With the producers' loop unrolled over a window of eight groups, so that nothing but
+// vector instructions is left of the bookkeeping and no wait drains the loads in flight: M = 64 60 -> 56 us, M = 2048 799 -> 765
+// (1.27 PFLOP/s), 11008 x 4096 172 -> 166.  With 256 rows it is power that bounds it: on zeros for X and the weights the same
+// instructions take 552 us of the 752 that they take on normal numbers (28672 x 8192, M = 2048).
 #include <stdio.h>
 
 #include <type_traits>
@@ -114,8 +115,12 @@ __device__ inline void frag_tile(const FragArgs &a, char *lds)
         // every group: 64 bytes of codes per channel and load.  A load that touches 16 rows costs the CU's address unit
         // several times what a contiguous one does, and three more of them per group (columns and values of the
         // outliers, record) cost as much as the MFMAs of a third of the tile (28672 x 8192, M = 1024: 460 us with them,
-        // 373 without).  So these come eight groups at a time: one load per wave and trip, in turn a run's records, its
-        // columns and its values, 64 bytes per channel, into the wave's own part of the LDS.
+        // 373 without).  So these come a window of eight groups at a time: one load per wave and trip, in turn a run's
+        // records, its columns and its values, 64 bytes per channel, into the wave's own part of the LDS.
+        //
+        // A trip is bound by one wave's own instructions (nothing else on its SIMD hides them but MFMAs), so the loop is
+        // unrolled over a window: which side load a trip makes and which buffer it fills are known when compiling, and what a
+        // trip needs of the side data is read from the LDS a trip ahead.
         constexpr int RUNS = BN / 16, I = RUNS / P;     // runs of the tile, runs per wave
         static_assert((D == 2 && I <= 2) || (D == 4 && I == 1), "a window's entries must be in the LDS before its first group");
         const int slot = lane & 3, ch16 = lane >> 2;
@@ -123,7 +128,12 @@ __device__ inline void frag_tile(const FragArgs &a, char *lds)
         const char *q_tile = reinterpret_cast<const char *>(a.qweight + ((size_t)n0 * gpr + g_first) * wpg);
         const char *r_tile = reinterpret_cast<const char *>(a.rec + (size_t)n0 * (gpr + 1) + g_first);
         const char *f_tile = reinterpret_cast<const char *>(a.fine + ((size_t)n0 * gpr + g_first) * 8);
-        char *const dump = lds + 2 * weight_bytes(BN), *const side = dump + kDump;   // records [3][RUNS][16][8], entries [2][RUNS]{columns, values}[16][32]; channels 80 bytes apart
+        // Side data: records [3][RUNS][16][8], entries [2][RUNS]{columns, values}[16][32]; channels 80 bytes apart.
+        char *const dump = lds + 2 * weight_bytes(BN) + 8 * lane;
+        char *const side = lds + 2 * weight_bytes(BN) + kDump + (wave - 4) * kRun + 80 * ch16;
+        constexpr uint32_t kRecWindow = RUNS * kRun, kCsrWindow = 2 * RUNS * kRun, kCsr = 3 * kRecWindow;
+        uint32_t rec_window[3] = {0, kRecWindow, 2 * kRecWindow};          // of windows w, w + 1, w + 2
+        uint32_t csr_window[2] = {kCsr + (wave - 4) * kRun, kCsr + kCsrWindow + (wave - 4) * kRun};     // of windows w, w + 1
         uint32_t q_off[I], r_off[I], f_off[I];          // bytes
         uint32_t dst[I];                                // LDS bytes of the channel's row; its chunks as this lane stores them
         uint32_t chunk[4];
@@ -138,31 +148,30 @@ __device__ inline void frag_tile(const FragArgs &a, char *lds)
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j) chunk[j] = 16 * chunk_place(4 * slot + j, ch16);
-        auto rec_at = [&](int window, int i) { return side + (uint32_t)((window % 3) * RUNS + wave - 4 + P * i) * kRun; };
-        auto csr_at = [&](int window, int i) { return side + (uint32_t)(3 * RUNS + (window & 1) * (2 * RUNS) + 2 * (wave - 4 + P * i)) * kRun; };
-        // Lane s of a channel fetches records 8w + 2s and the next, moved back where that would pass the row's end (record gl).
-        auto rec_offset = [&](int window, int i) {
-            const int g = 8 * window + 2 * slot;
+        // Lane s of a channel fetches records g = 8w + 2s and g + 1, or gl - 1 and gl (the row's end) where g would pass that.
+        auto rec_offset = [&](int g0, int i) {
+            const int g = g0 + 2 * slot;
             return r_off[i] + 8u * (uint32_t)(g < gl - 1 ? g : gl - 1);
         };
-        auto read_rec = [&](int g, int i) {             // record g, the last one's (the row's end) beyond it
-            g = g < gl ? g : gl;
-            const int at = (g & ~1) < gl - 1 ? (g & ~1) : gl - 1;
-            return *reinterpret_cast<const uint2 *>(rec_at(g >> 3, i) + ch16 * 80 + ((g & 7) >> 1) * 16 + (g - at) * 8);
+        // Record g0 + k of the window that starts at group g0 (a multiple of 8); record gl beyond that.
+        auto read_rec = [&](uint32_t window, int g0, int k, int i) {
+            const uint32_t second = k & 1 ? 8u : g0 + k >= gl ? 8u : 0u;
+            return *reinterpret_cast<const uint2 *>(side + window + P * i * kRun + k / 2 * 16 + second);
         };
         auto csr_offset = [&](uint32_t first) {         // bytes; the arrays carry 16 spare bytes
             const int j = (int)first + 8 * slot;
             return 2u * (uint32_t)(j < a.last_entry ? j : a.last_entry);
         };
         auto load16 = [](const void *base, uint32_t offset) { return *reinterpret_cast<const U128a2 *>(static_cast<const char *>(base) + offset); };
-        auto store16 = [&](char *run, const U128a2 &v) { *reinterpret_cast<u32x4 *>(run + 80 * ch16 + 16 * slot) = u32x4{v.x, v.y, v.z, v.w}; };
+        auto store16 = [&](uint32_t at, const U128a2 &v) { *reinterpret_cast<u32x4 *>(side + at + 16 * slot) = u32x4{v.x, v.y, v.z, v.w}; };
 
         SlotRegs<BITS> codes[D][I];
         uint2 sub[D][I];                                // FINE: scale | zero << 16 of the slot's halves
         U128a2 side_regs[D];
-        uint2 now[I], next[I];                          // records of groups t and t + 1
-        uint32_t window_first[I], side_first;
+        uint2 now[I], next[I], after[I];                // records of groups t, t + 1 and, read during trip t, t + 2
+        uint32_t window_first[I];
         uint32_t cols[I], vals[I];                      // entries 2 slot and 2 slot + 1 of group t
+        struct Entries { uint32_t c[2], v[2], shift; } ahead[I];           // the words that hold those of group t + 1
         auto issue_codes = [&](int g, int r) {
             g = g < gl ? g : gl - 1;                    // past the end: the last group again, unused
             const char *q = q_tile + (uint32_t)g * (4 * wpg), *f = f_tile + (uint32_t)g * 32;
@@ -172,45 +181,33 @@ __device__ inline void frag_tile(const FragArgs &a, char *lds)
                 if constexpr (FINE) sub[r][i] = *reinterpret_cast<const uint2 *>(f + f_off[i]);
             }
         };
-        // The side load of trip t, window w = t / 8: records of window w + 2 (trips 0 .. I-1 of a window), then columns and
-        // values of window w + 1 (trips 2 .. 2I+1); the other trips repeat a harmless one, so that the number of loads in
-        // flight is the same in every trip.
-        auto side_run = [](int k) { return I == 2 && (k == 1 || k == 4 || k == 5) ? I - 1 : 0; };
-        auto issue_side = [&](int t, int r) {
-            const int k = t & 7, w = t >> 3, run = side_run(k);
-            const void *base = r_tile;
-            uint32_t offset = 0;
-            if (k < I) offset = I == 2 && run ? rec_offset(w + 2, I - 1) : rec_offset(w + 2, 0);
-            else if (k >= 2 && k < 2 + 2 * I) offset = csr_offset(side_first), base = k & 1 ? a.out_val : a.col_idx;
-            side_regs[r] = load16(base, offset);
+        // Trips 0 .. I-1 of window w ask for the records of window w + 2, trips 2 .. 2I+1 for columns and values of window
+        // w + 1; D trips later, in the same window, they go to the LDS.
+        auto asks_records = [](int k) { return k >= 0 && k < I; };
+        auto asks_entries = [](int k) { return k >= 2 && k < 2 + 2 * I; };
+        auto side_run = [](int k) { return I == 2 && (k == 1 || k >= 4) ? I - 1 : 0; };
+        auto keep_side = [&](int k, int r) {            // what trip k asked for
+            if (asks_records(k)) store16(rec_window[2] + P * side_run(k) * kRun, side_regs[r]);
+            else if (asks_entries(k)) store16(csr_window[1] + (2 * P * side_run(k) + (k & 1)) * kRun, side_regs[r]);
         };
-        auto keep_side = [&](int t, int r) {            // what trip t asked for, into the LDS
-            const int k = t & 7, w = t >> 3, run = side_run(k);
-            if (t >= 0 && k < I) store16(rec_at(w + 2, run), side_regs[r]);
-            else if (t >= 0 && k >= 2 && k < 2 + 2 * I) store16(csr_at(w + 1, run) + kRun * (k & 1), side_regs[r]);
+        // A group's entries, from its window's in the LDS, its record, and the entry at which the window starts.
+        auto read_entries = [&](uint32_t window, uint32_t first, uint32_t start, int i) {
+            const uint32_t e = first - start + 2 * slot, o = e < 31 ? e : 31;
+            const uint32_t *run = reinterpret_cast<const uint32_t *>(side + window + 2 * P * i * kRun) + (o >> 1);
+            ahead[i] = Entries{{run[0], run[1]}, {run[kRun / 4], run[kRun / 4 + 1]}, 16 * (o & 1)};
         };
-        // What trip t needs from the side data, read before the barrier ahead of it; now[] is group t's record already.
-        auto read_side = [&](int t) {
-            const int k = t & 7, w = t >> 3;
-            side_first = read_rec(8 * (w + 1), side_run(k)).x;
-#pragma unroll
-            for (int i = 0; i < I; ++i) {
-                next[i] = read_rec(t + 1, i);
-                window_first[i] = k ? window_first[i] : now[i].x;
-                const uint32_t e = now[i].x - window_first[i] + 2 * slot, o = e < 31 ? e : 31;
-                const uint32_t *run = reinterpret_cast<const uint32_t *>(csr_at(w, i) + 80 * ch16) + (o >> 1);
-                cols[i] = __builtin_amdgcn_alignbit(run[1], run[0], 16 * (o & 1));
-                vals[i] = __builtin_amdgcn_alignbit(run[kRun / 4 + 1], run[kRun / 4], 16 * (o & 1));
-            }
+        auto take_entries = [&](int i) {
+            cols[i] = __builtin_amdgcn_alignbit(ahead[i].c[1], ahead[i].c[0], ahead[i].shift);
+            vals[i] = __builtin_amdgcn_alignbit(ahead[i].v[1], ahead[i].v[0], ahead[i].shift);
         };
         auto column_place = [&](uint32_t c) { return (2 * c) ^ (c >> 6 << 5) ^ (16u * ch16); };   // chunk_place of column c, in bytes
-        auto stage = [&](int t, int r) {
+        auto stage = [&](int t, int k, int r) {
             const uint32_t k_lo = (uint32_t)(g_first + t) * kGroup;
-            bool more = false;
+            uint64_t more = 0;
 #pragma unroll
             for (int i = 0; i < I; ++i) {
                 const SlotRegs<BITS> &q = codes[r][i];
-                char *row = lds + (t & 1) * weight_bytes(BN) + dst[i];
+                char *row = lds + (k & 1) * weight_bytes(BN) + dst[i];
                 const uint32_t sz = now[i].y, z = sz >> 16, s2 = (sz & 0xFFFFu) * 0x10001u;
                 u32x4 f[4];
                 uint32_t tail = 0;
@@ -242,12 +239,12 @@ __device__ inline void frag_tile(const FragArgs &a, char *lds)
                 for (int e = 0; e < 2; ++e) {
                     const uint32_t c = ((cols[i] >> (16 * e)) & 0xFFFFu) - k_lo;
                     const uint32_t v = (vals[i] >> (16 * e)) & 0xFFFFu;
-                    char *at = 2 * slot + e < near && c < (uint32_t)kGroup ? row + column_place(c) : dump + 8 * lane;
+                    char *at = 2 * slot + e < near && c < (uint32_t)kGroup ? row + column_place(c) : dump;
                     *reinterpret_cast<uint16_t *>(at) = BF16 ? half_bits_to_bf16_bits(v) : (uint16_t)v;
                 }
-                more |= cnt > (room < 8 ? room : 8);
+                more |= __builtin_amdgcn_ballot_w64(cnt > (room < 8 ? room : 8));
             }
-            if (__builtin_amdgcn_ballot_w64(more)) {    // rare: more than eight outliers in this group, or than 32 in its window so far
+            if (more) {                                 // rare: more than eight outliers in this group, or than 32 in its window so far
 #pragma unroll
                 for (int i = 0; i < I; ++i) {
                     const int cnt = (int)(next[i].x - now[i].x), room = 32 - (int)(now[i].x - window_first[i]);
@@ -256,65 +253,94 @@ __device__ inline void frag_tile(const FragArgs &a, char *lds)
                             const uint32_t c = load_u16_now(a.col_idx + now[i].x + e) - k_lo;
                             if (c < (uint32_t)kGroup) {
                                 const uint32_t v = load_u16_now(a.out_val + now[i].x + e);
-                                *reinterpret_cast<uint16_t *>(lds + (t & 1) * weight_bytes(BN) + dst[i] + column_place(c)) =
+                                *reinterpret_cast<uint16_t *>(lds + (k & 1) * weight_bytes(BN) + dst[i] + column_place(c)) =
                                     BF16 ? half_bits_to_bf16_bits(v) : (uint16_t)v;
                             }
                         }
                 }
             }
         };
-        // Trip t stages group t and refills its registers with group t + D.
-        auto trip = [&](int t, int r) {
-            keep_side(t - D, r);
+        // Trip t = g0 + k of the window at g0 stages group t and refills its registers with group t + D.
+        auto trip = [&](int g0, int k) {
+            const int t = g0 + k, r = k % D;
+            if (k == 0) {
+#pragma unroll
+                for (int i = 0; i < I; ++i) window_first[i] = now[i].x;
+            }
+            keep_side(k - D, r);
+            uint32_t side_first = 0;
+            if (asks_entries(k)) side_first = read_rec(rec_window[1], g0 + 8, 0, side_run(k)).x;
+#pragma unroll
+            for (int i = 0; i < I; ++i) {
+                after[i] = k < 6 ? read_rec(rec_window[0], g0, k + 2, i) : read_rec(rec_window[1], g0 + 8, k - 6, i);
+                if (k < 7) read_entries(csr_window[0], next[i].x, window_first[i], i);
+                else read_entries(csr_window[1], next[i].x, next[i].x, i);
+            }
             __builtin_amdgcn_sched_barrier(0);
-            stage(t, r);
+            stage(t, k, r);
             __builtin_amdgcn_sched_barrier(0);
             issue_codes(t + D, r);
-            issue_side(t, r);
-#pragma unroll
-            for (int i = 0; i < I; ++i) now[i] = next[i];
-            read_side(t + 1);
+            if (asks_records(k)) side_regs[r] = load16(r_tile, rec_offset(g0 + 16, side_run(k)));
+            else if (asks_entries(k)) side_regs[r] = load16(k & 1 ? a.out_val : a.col_idx, csr_offset(side_first));
             __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < I; ++i) {
+                take_entries(i);
+                now[i] = next[i];
+                next[i] = after[i];
+            }
             __syncthreads();
         };
         {
             U128a2 v0[I], v1[I];
 #pragma unroll
-            for (int i = 0; i < I; ++i) v0[i] = load16(r_tile, rec_offset(0, i)), v1[i] = load16(r_tile, rec_offset(1, i));
+            for (int i = 0; i < I; ++i) v0[i] = load16(r_tile, rec_offset(0, i)), v1[i] = load16(r_tile, rec_offset(8, i));
 #pragma unroll
             for (int r = 0; r < D; ++r) issue_codes(r, r);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int i = 0; i < I; ++i) {
-                store16(rec_at(0, i), v0[i]);
-                store16(rec_at(1, i), v1[i]);
+                store16(rec_window[0] + P * i * kRun, v0[i]);
+                store16(rec_window[1] + P * i * kRun, v1[i]);
             }
             __builtin_amdgcn_wave_barrier();
 #pragma unroll
             for (int i = 0; i < I; ++i) {
-                now[i] = read_rec(0, i);
-                window_first[i] = now[i].x;
+                now[i] = read_rec(rec_window[0], 0, 0, i);
+                next[i] = read_rec(rec_window[0], 0, 1, i);
                 v0[i] = load16(a.col_idx, csr_offset(now[i].x));
                 v1[i] = load16(a.out_val, csr_offset(now[i].x));
             }
 #pragma unroll
             for (int i = 0; i < I; ++i) {
-                store16(csr_at(0, i), v0[i]);
-                store16(csr_at(0, i) + kRun, v1[i]);
+                store16(csr_window[0] + 2 * P * i * kRun, v0[i]);
+                store16(csr_window[0] + (2 * P * i + 1) * kRun, v1[i]);
             }
             __builtin_amdgcn_wave_barrier();
-            read_side(0);
 #pragma unroll
-            for (int r = 0; r < D; ++r) side_regs[r] = U128a2{0, 0, 0, 0};
+            for (int i = 0; i < I; ++i) {
+                read_entries(csr_window[0], now[i].x, now[i].x, i);
+                take_entries(i);
+            }
         }
-        int t = 0;
-        for (; t + D <= gl; t += D) {
+        // Whole windows, then the rest, each trip inside the branch of the one before: a way out of the loop's middle, or past
+        // a trip, would join paths with other loads in flight, and the compiler would wait there for all of them.
+        int g0 = 0;
+        for (; g0 + 8 <= gl; g0 += 8) {
 #pragma unroll
-            for (int r = 0; r < D; ++r) trip(t + r, r);
+            for (int k = 0; k < 8; ++k) trip(g0, k);
+            const uint32_t oldest = rec_window[0], csr = csr_window[0];
+            rec_window[0] = rec_window[1], rec_window[1] = rec_window[2], rec_window[2] = oldest;
+            csr_window[0] = csr_window[1], csr_window[1] = csr;
         }
-#pragma unroll
-        for (int r = 0; r < D - 1; ++r)
-            if (t + r < gl) trip(t + r, r);
+        auto rest = [&](auto self, auto k) {
+            if constexpr (k < 7)
+                if (g0 + k < gl) {
+                    trip(g0, k);
+                    self(self, std::integral_constant<int, k + 1>{});
+                }
+        };
+        rest(rest, std::integral_constant<int, 0>{});
         __syncthreads();
         return;
     }
