@@ -595,14 +595,13 @@ template <int BITS> __device__ inline void scale_and_zero(float mn, float mx, ui
 {
     constexpr float maxq = (float)((1 << BITS) - 1);
     const float d = mx - mn, bb = d - mx, err = (mx - (d - bb)) + (-mn - bb);
-    auto covers = [&](uint32_t sb) {
-        const float top = half_bits_to_float(sb) * maxq;
-        return top > d || (top == d && err <= 0.f);
-    };
+    // s * maxq >= d + err: as s * maxq and d are either equal or further apart than |err|, the sign of their difference less
+    // err (which a rounding does not change) decides; an infinite d is never covered.
+    auto covers = [&](uint32_t sb) { return __builtin_fmaf(half_bits_to_float(sb), maxq, -d) >= err; };
     uint32_t sb = __builtin_bit_cast(uint16_t, (_Float16)(d * (1.f / maxq)));
     sb = sb == 0 ? 1 : sb;
-    sb = sb < 0x7BFFu && !covers(sb) ? sb + 1 : sb;
-    sb = sb > 1 && covers(sb - 1) ? sb - 1 : sb;
+    sb += (uint32_t)(sb < 0x7BFFu) & (uint32_t)!covers(sb);
+    sb -= (uint32_t)(sb > 1) & (uint32_t)covers(sb - 1);
     if (d == 0.f) sb = 0x3C00u;                         // an empty range: s = 1 and, as -mn / 1 = 0, z = 0
     s_bits = sb;
     s = half_bits_to_float(sb);
@@ -610,16 +609,46 @@ template <int BITS> __device__ inline void scale_and_zero(float mn, float mx, ui
     z = rintf(__builtin_amdgcn_fmed3f(quotient(-mn, s, r), 0.f, maxq));     // (a NaN gives the lower end)
 }
 
-template <int CTRL> __device__ inline float dpp_f32(float v)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
-}
 template <int CTRL> __device__ inline uint32_t dpp_u32(uint32_t v)
 {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
 }
 // DPP controls: lanes exchange within pairs, within quads, halves of eight and of sixteen are mirrored, a row rotates.
 constexpr int kDppPair = 0xB1, kDppQuad = 0x4E, kDppHalfMirror = 0x141, kDppMirror = 0x140, kDppRor4 = 0x124, kDppRor8 = 0x128;
+
+// Range of the 2^STEPS lanes that share a group, from each lane's own.  Both bounds contain 0, so as bit patterns the upper one
+// orders like a signed integer and the lower one, downwards, like an unsigned one: one instruction a step, where the
+// floating-point minimum also quiets its operand first.
+template <int STEPS> __device__ inline void group_range(float &mn, float &mx)
+{
+    uint32_t lo = __builtin_bit_cast(uint32_t, mn);
+    int32_t hi = __builtin_bit_cast(int32_t, mx);
+    auto meet = [&](auto ctrl) {
+        const uint32_t l = dpp_u32<decltype(ctrl)::value>(lo);
+        const int32_t h = (int32_t)dpp_u32<decltype(ctrl)::value>((uint32_t)hi);
+        lo = l > lo ? l : lo;
+        hi = h > hi ? h : hi;
+    };
+    meet(std::integral_constant<int, kDppPair>{});
+    if constexpr (STEPS > 1) meet(std::integral_constant<int, kDppQuad>{});
+    if constexpr (STEPS > 2) meet(std::integral_constant<int, kDppHalfMirror>{});
+    if constexpr (STEPS > 3) meet(std::integral_constant<int, kDppMirror>{});
+    mn = __builtin_bit_cast(float, lo);
+    mx = __builtin_bit_cast(float, hi);
+}
+
+// Sum over the lanes up to and including this one.
+__device__ inline uint32_t wave_sum_to_here(uint32_t v)
+{
+    auto add = [&](auto ctrl, auto rows) { v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, decltype(rows)::value, 0xF, false); };
+    add(std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xF>{});       // row_shr 1, 2, 4, 8: within rows of 16
+    add(std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xF>{});
+    add(std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xF>{});
+    add(std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xF>{});
+    add(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xA>{});       // row_bcast 15: to rows 1 and 3
+    add(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xC>{});       // row_bcast 31: to rows 2 and 3
+    return v;
+}
 
 // Lanes below this one whose bit is set, added to `base`.
 __device__ inline uint32_t count_below(uint64_t mask, uint32_t base)
@@ -630,13 +659,13 @@ __device__ inline uint32_t count_below(uint64_t mask, uint32_t base)
 // What a lane holds of one trip: eight weights and their scores as they lie in memory.
 template <bool F16> struct EncodeRegs {
     uint4 w, s[F16 ? 1 : 2];
-    __device__ inline void load(const uint16_t *W, const void *score, size_t idx)
+    __device__ inline void load(const uint16_t *W, const char *score, uint32_t k)    // of a row, from column k
     {
-        w = *reinterpret_cast<const uint4 *>(W + idx);
+        w = *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(W) + 2 * k);
         if (F16) {
-            s[0] = *reinterpret_cast<const uint4 *>(static_cast<const uint16_t *>(score) + idx);
+            s[0] = *reinterpret_cast<const uint4 *>(score + 2 * k);
         } else {
-            const uint4 *p = reinterpret_cast<const uint4 *>(static_cast<const uint32_t *>(score) + idx);
+            const uint4 *p = reinterpret_cast<const uint4 *>(score + 4 * k);
             s[0] = p[0];
             s[F16 ? 0 : 1] = p[1];
         }
@@ -682,21 +711,36 @@ __global__ __launch_bounds__(kThreads) void encode_kernel(const uint16_t *__rest
     const int trips = (K + kTrip - 1) / kTrip, per_part = (trips + parts - 1) / parts;
     const int t_begin = parts == 1 ? 0 : wave * per_part;
     const int t_end = t_begin + per_part < trips ? t_begin + per_part : trips;
-    const size_t row = (size_t)n * K;
     const uint32_t thr = ws[kWsPrefix];
     const uint32_t take = ws[kWsRows + 2 * N + n];      // of the row's keys equal to the threshold the first `take` are kept
     const int gpr = K / kGroup, spr = K / group;
-    uint32_t pos = (uint32_t)row_ptr[n], ties_seen = 0;
-    if (rec && lane == 0 && t_begin == 0) rec[(size_t)n * (gpr + 1) + gpr] = GroupRecord{row_ptr[n + 1], 0u};
+    const uint32_t row_start = (uint32_t)row_ptr[n];
+    // The row's part of each array: uniform, so that a lane's place is a 32-bit offset.
+    W += (size_t)n * K;
+    const char *const row_score = static_cast<const char *>(score) + (size_t)n * K * (F16 ? 2 : 4);
+    qweight += (size_t)n * gpr * wpg;
+    scales += (size_t)n * spr;
+    zeros += (size_t)n * spr;
+    col_idx += row_start;
+    out_val += row_start;
+    uint32_t pos = 0, ties_seen = 0;                    // kept and equal to the threshold in the row so far
+    if (rec) {
+        rec += (size_t)n * (gpr + 1);
+        fine += (size_t)n * (K / 16);
+        if (lane == 0 && t_begin == 0) rec[gpr] = GroupRecord{row_ptr[n + 1], 0u};
+    }
 
     // Lanes beyond the end of the row (whole groups of lanes) repeat its last weights and keep nothing.
-    auto column = [&](int t) { return t * kTrip + lane * 8; };
+    auto column = [&](int t) { return (uint32_t)(t * kTrip + lane * 8); };
     auto request = [&](int t, EncodeRegs<F16> &R) {
-        const int k = column(t < t_end ? t : t_end - 1);
-        R.load(W, score, row + (k < K ? k : K - 8));
+        const uint32_t k = column(t < t_end ? t : t_end - 1);
+        R.load(W, row_score, k < (uint32_t)K ? k : (uint32_t)K - 8);
     };
-    EncodeRegs<F16> next;
-    if (t_begin < t_end) request(t_begin, next);
+    EncodeRegs<F16> even, odd;
+    if (t_begin < t_end) {
+        request(t_begin, even);
+        request(t_begin + 1, odd);
+    }
 
     if (parts > 1) {                                    // what the parts before this one keep
         uint32_t gt = 0, eq = 0;
@@ -707,8 +751,8 @@ __global__ __launch_bounds__(kThreads) void encode_kernel(const uint16_t *__rest
             R.keys(key);
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                gt += column(t) < K && key[i] > thr;
-                eq += column(t) < K && key[i] == thr;
+                gt += column(t) < (uint32_t)K && key[i] > thr;
+                eq += column(t) < (uint32_t)K && key[i] == thr;
             }
         }
 #pragma unroll
@@ -719,63 +763,61 @@ __global__ __launch_bounds__(kThreads) void encode_kernel(const uint16_t *__rest
         pos += ties_seen < take ? ties_seen : take;
     }
 
-    for (int t = t_begin; t < t_end; ++t) {
-        const EncodeRegs<F16> R = next;
-        request(t + 1, next);
-        const int k = column(t);
-        const bool active = k < K;
+    // One trip; TIES: the row keeps some of its keys that equal the threshold.
+    auto trip = [&](int t, const EncodeRegs<F16> &R, auto TIES) {
+        const uint32_t k = column(t);
+        const bool active = k < (uint32_t)K;
         const uint32_t vw[4] = {R.w.x, R.w.y, R.w.z, R.w.w};
-        bool keep[8];
+        float w[8];
+        uint32_t kept = 0;                              // bit i: weight i is an outlier
         {
             uint32_t key[8];
             R.keys(key);
-            if (take == 0) {                            // uniform over the wave; nearly every row
+            const uint32_t above = active ? thr : ~0u;  // no key is larger than that, or equal to it
+            bool keep[8];
+            if constexpr (!decltype(TIES)::value) {
 #pragma unroll
-                for (int i = 0; i < 8; ++i) keep[i] = active && key[i] > thr;
+                for (int i = 0; i < 8; ++i) keep[i] = key[i] > above;
             } else {
                 uint32_t rank = ties_seen;
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
-                    const uint64_t m = __ballot(active && key[i] == thr);
+                    const uint64_t m = __ballot(key[i] == above);
                     rank = count_below(m, rank);
                     ties_seen += (uint32_t)__builtin_popcountll(m);
                 }
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
-                    const bool tie = active && key[i] == thr;
-                    keep[i] = (active && key[i] > thr) || (tie && rank < take);
+                    const bool tie = key[i] == above;
+                    keep[i] = key[i] > above || (tie && rank < take);
                     rank += tie;
                 }
             }
-        }
-        uint32_t at = pos;                              // CSR position of this lane's first kept entry
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const uint64_t m = __ballot(keep[i]);
-            at = count_below(m, at);
-            pos += (uint32_t)__builtin_popcountll(m);
-        }
-        const uint32_t first = at;
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-            if (keep[i]) {
-                col_idx[at] = (uint16_t)(k + i);
-                out_val[at] = (uint16_t)(i & 1 ? vw[i >> 1] >> 16 : vw[i >> 1] & 0xFFFFu);
-                ++at;
+            for (int i = 7; i >= 0; --i) {
+                kept = 2 * kept + keep[i];
+                w[i] = keep[i] ? 0.f : half_bits_to_float(i & 1 ? vw[i >> 1] >> 16 : vw[i >> 1] & 0xFFFFu);
             }
+        }
+        const uint32_t count = (uint32_t)__builtin_popcount(kept), to_here = wave_sum_to_here(count);
+        const uint32_t first = pos + to_here - count;   // of the row's outliers, this lane's first
+        pos += (uint32_t)__builtin_amdgcn_readlane((int)to_here, 63);
+        // A lane has more than one of its eight to store once in a few hundred lanes, so the wave goes round once, or twice.
+        for (uint32_t at = first; kept; ++at) {
+            const uint32_t i = (uint32_t)__builtin_ctz(kept);
+            kept &= kept - 1;
+            const uint32_t pair = i & 4 ? (i & 2 ? vw[3] : vw[2]) : (i & 2 ? vw[1] : vw[0]);
+            col_idx[at] = (uint16_t)(k + i);
+            out_val[at] = (uint16_t)(pair >> (16 * (i & 1)));
+        }
 
-        float w[8], mn = 0.f, mx = 0.f;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) w[i] = keep[i] || !active ? 0.f : half_bits_to_float(i & 1 ? vw[i >> 1] >> 16 : vw[i >> 1] & 0xFFFFu);
+        float mn = 0.f, mx = 0.f;
 #pragma unroll
         for (int i = 0; i < 8; i += 2) {
             mn = __builtin_fminf(__builtin_fminf(w[i], w[i + 1]), mn);      // a NaN loses against a number
             mx = __builtin_fmaxf(__builtin_fmaxf(w[i], w[i + 1]), mx);
         }
-        mn = __builtin_fminf(mn, dpp_f32<kDppPair>(mn)); mx = __builtin_fmaxf(mx, dpp_f32<kDppPair>(mx));
-        if (STEPS > 1) { mn = __builtin_fminf(mn, dpp_f32<kDppQuad>(mn)); mx = __builtin_fmaxf(mx, dpp_f32<kDppQuad>(mx)); }
-        if (STEPS > 2) { mn = __builtin_fminf(mn, dpp_f32<kDppHalfMirror>(mn)); mx = __builtin_fmaxf(mx, dpp_f32<kDppHalfMirror>(mx)); }
-        if (STEPS > 3) { mn = __builtin_fminf(mn, dpp_f32<kDppMirror>(mn)); mx = __builtin_fmaxf(mx, dpp_f32<kDppMirror>(mx)); }
+        group_range<STEPS>(mn, mx);
         uint32_t s_bits;
         float s, r, zf;
         scale_and_zero<BITS>(mn, mx, s_bits, s, r, zf);
@@ -793,9 +835,8 @@ __global__ __launch_bounds__(kThreads) void encode_kernel(const uint16_t *__rest
             codes += __builtin_bit_cast(uint32_t, q) << (16 * (i & 1) + BITS * (i >> 1));
         }
 
-        const size_t block = (size_t)n * gpr + (k >> 7);
         if (BITS == 4) {
-            if (active) qweight[block * wpg + (lane & 15)] = codes;
+            if (active) qweight[k >> 3] = codes;
         } else {
             // A quad of lanes holds a slot: 16 codes of the even and 16 of the odd positions, 48 bits each.  Lane q < 3 of the
             // quad makes word q of the slot (15 bits of each), lane 3 the slot's two codes of the tail word.
@@ -804,22 +845,35 @@ __global__ __launch_bounds__(kThreads) void encode_kernel(const uint16_t *__rest
                 return (uint64_t)((p0 >> sh & 0xFFFu) | (p1 >> sh & 0xFFFu) << 12) | (uint64_t)((p2 >> sh & 0xFFFu) | (p3 >> sh & 0xFFFu) << 12) << 24;
             };
             const int q = lane & 3, b = (lane >> 2) & 3;
-            const uint32_t even = (uint32_t)(stream(0) >> (15 * q)) & 0x7FFFu, odd = (uint32_t)(stream(16) >> (15 * q)) & 0x7FFFu;
-            uint32_t tail = q == 3 ? (even & 7u) << (3 * b) | (odd & 7u) << (16 + 3 * b) : 0u;
+            const uint32_t even_codes = (uint32_t)(stream(0) >> (15 * q)) & 0x7FFFu, odd_codes = (uint32_t)(stream(16) >> (15 * q)) & 0x7FFFu;
+            uint32_t tail = q == 3 ? (even_codes & 7u) << (3 * b) | (odd_codes & 7u) << (16 + 3 * b) : 0u;
             tail |= dpp_u32<kDppRor4>(tail);
             tail |= dpp_u32<kDppRor8>(tail);
-            if (active && (q < 3 || b == 3)) qweight[block * wpg + 3 * b + q] = q < 3 ? even | odd << 16 : tail;
+            if (active && (q < 3 || b == 3)) qweight[(k >> 7) * wpg + 3 * b + q] = q < 3 ? even_codes | odd_codes << 16 : tail;
         }
         if (active && (lane & ((1 << STEPS) - 1)) == 0) {
-            scales[(size_t)n * spr + k / group] = (uint16_t)s_bits;
-            zeros[(size_t)n * spr + k / group] = (uint8_t)z;
+            scales[k / group] = (uint16_t)s_bits;
+            zeros[k / group] = (uint8_t)z;
         }
         if (rec && active) {
             const uint32_t pair = (s_bits < cap ? s_bits : cap) | z << 16;
-            if ((lane & 15) == 0) rec[(size_t)n * (gpr + 1) + (k >> 7)] = GroupRecord{(int32_t)first, STEPS == 4 ? pair : 0u};
-            if (STEPS < 4 && (lane & 1) == 0) fine[(size_t)n * (K / 16) + (k >> 4)] = pair;
+            if ((lane & 15) == 0) rec[k >> 7] = GroupRecord{(int32_t)(row_start + first), STEPS == 4 ? pair : 0u};
+            if (STEPS < 4 && (lane & 1) == 0) fine[k >> 4] = pair;
         }
-    }
+    };
+    // Two trips' weights and scores are on their way.
+    auto walk = [&](auto TIES) {
+        int t = t_begin;
+        for (; t + 2 <= t_end; t += 2) {
+            trip(t, even, TIES);
+            request(t + 2, even);
+            trip(t + 1, odd, TIES);
+            request(t + 3, odd);
+        }
+        if (t < t_end) trip(t, even, TIES);
+    };
+    if (take == 0) walk(std::false_type{});             // uniform over the wave; nearly every row
+    else walk(std::true_type{});
 }
 
 template <bool F16>
