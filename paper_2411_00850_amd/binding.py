@@ -104,6 +104,28 @@ def lib():
     return _lib
 
 
+_plain_call = None
+
+
+def _plain():
+    """call(layer, X, out or None, bf16) of the extension module (csrc/gwq_call.cpp): gwq.linear without the interpreter's
+    share of a call.  Returns the result, (status, None), or None where the call is not the plain case."""
+    global _plain_call
+    if _plain_call is None:
+        import torch                                   # its libraries first: the module is linked with them
+        L = lib()
+        try:
+            from . import _call
+        except ImportError as e:
+            raise RuntimeError("_call.so is not built, or not for this torch: run __graft_entry__.build() (or "
+                               "python -m paper_2411_00850_amd.build) first") from e
+        address = lambda f: ctypes.cast(f, ctypes.c_void_p).value
+        _call.bind(address(L.gwq_linear), address(L.gwq_linear_bf16), address(L.gwq_layout),
+                   torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice)
+        _plain_call = _call.call
+    return _plain_call
+
+
 def version():
     return lib().gwq_version().decode()
 
@@ -381,6 +403,12 @@ def linear_index(P, stream=None):
 def linear(P, X, out=None, stream=None, workspace=None, index=None, scratch="auto"):
     """gwq_linear: X FP16 [M, K] on the GPU -> Y FP16 [M, N].  With `index` (from linear_index) the call
     is gwq_linear_indexed; its scratch is allocated here unless one (or None) is passed."""
+    if stream is None and workspace is None and index is None:
+        got = (_plain_call or _plain())(P, X, out, False)
+        if got is not None:
+            if type(got) is tuple:
+                raise GwqError(got[0], "gwq_linear")
+            return got
     import torch
     assert X.is_cuda and X.dtype == torch.float16 and X.is_contiguous() and X.shape[1] == P.K
     M = X.shape[0]
@@ -410,6 +438,12 @@ def linear(P, X, out=None, stream=None, workspace=None, index=None, scratch="aut
 
 def linear_bf16(P, X, out=None, stream=None, workspace=None):
     """gwq_linear_bf16: X bfloat16 [M, K] on the GPU -> Y bfloat16 [M, N] (layers with groups of 128)."""
+    if stream is None and workspace is None:
+        got = (_plain_call or _plain())(P, X, out, True)
+        if got is not None:
+            if type(got) is tuple:
+                raise GwqError(got[0], "gwq_linear_bf16")
+            return got
     import torch
     assert X.is_cuda and X.dtype == torch.bfloat16 and X.is_contiguous() and X.shape[1] == P.K
     M = X.shape[0]

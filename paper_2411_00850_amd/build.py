@@ -1,6 +1,8 @@
-"""Build libgwq.so (HIP, gfx950 only) in-tree with hipcc."""
+"""Build libgwq.so (HIP, gfx950 only) with hipcc and the extension module _call.so (C++) in-tree."""
+import importlib.util
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -11,6 +13,9 @@ SOURCES = ["gwq_api.hip", "gwq_pack.hip", "gwq_decode.hip", "gwq_gemm.hip", "gwq
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wno-unused-command-line-argument"]
+
+
+CALL = os.path.join(HERE, "_call.so")                  # Python extension module: the plain gwq.linear call
 
 
 STAMP_LIB = os.path.join(HERE, "libgwq_stamp.so")     # measurement build: kernels record device timestamps
@@ -42,14 +47,30 @@ def build(verbose: bool = False, stamps: bool = False, sanitize_host: bool = Fal
         print("\n".join(l for l in (res.stdout + res.stderr).splitlines() if noise not in l))
     if res.returncode:
         raise RuntimeError("hipcc failed building " + os.path.basename(out))
+    if not stamps:
+        build_call(verbose)
     return out
 
 
+def build_call(verbose: bool = False) -> str:
+    """Builds _call.so against the headers of the installed torch (host code: no GPU compiler)."""
+    torch = os.path.dirname(importlib.util.find_spec("torch").origin)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", INCLUDE, "-I", os.path.join(torch, "include"),
+           "-I", os.path.join(torch, "include", "torch", "csrc", "api", "include"), "-I", sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "gwq_call.cpp"), "-L", os.path.join(torch, "lib"), "-ltorch_python", "-ltorch_cpu", "-ltorch", "-lc10", "-o", CALL]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if verbose or res.returncode:
+        print(res.stdout + res.stderr)
+    if res.returncode:
+        raise RuntimeError("building " + os.path.basename(CALL) + " failed")
+    return CALL
+
+
 def stale() -> bool:
-    """True when the built library is older than one of its sources or the public header."""
-    if not os.path.exists(LIB):
+    """True when a built file is missing or older than one of the sources or the public header."""
+    if not (os.path.exists(LIB) and os.path.exists(CALL)):
         return True
-    built = os.path.getmtime(LIB)
+    built = min(os.path.getmtime(LIB), os.path.getmtime(CALL))
     deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC)] + [os.path.join(INCLUDE, "gwq.h")]
     return any(os.path.getmtime(d) > built for d in deps)
 
