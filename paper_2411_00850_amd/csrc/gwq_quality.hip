@@ -4,13 +4,15 @@
 // layer: s * (q - z) (Sec. 3.2, Eq. 10) where a weight was quantised, the stored FP16 value where it
 // was kept as an outlier.
 //
-// One block per output channel.  The codes are read through the format's definition (position of a
+// One or four waves per output channel.  The codes are read through the format's definition (position of a
 // code inside its word), not through the magic-number decoders of the linear kernels, and every
 // difference is formed in fp64 from exact operands (an FP16 weight, an FP16 scale times a small
 // integer: all multiples of 2^-24 below 2^21), so it is the exact value.  The sums are fp64 and run in
-// a fixed order: threads over their strided columns, a shuffle tree, the block's waves in order, and a
+// a fixed order: lanes over their strided columns, a shuffle tree, the channel's waves in order, and a
 // second kernel over the channels; no floating-point atomics, results identical from run to run.
-// Bound by HBM: W (2 bytes), the score (4 or 2) and the packed layer (about 0.5) per weight, read once.
+// Bound by HBM: W (2 bytes), the score (4 or 2) and the packed layer (about 0.5) per weight, read once: 295 MB of
+// 11008 x 4096 with FP32 scores at 5.4 TB/s.  (A block of four waves per channel and a branch per kept weight: FP16 scores
+// 54.4 us, now 50.1; 8192 x 1024 27.2, now 19.8; 3 bits, groups of 16 70.5, now 64.)
 #include "gwq_internal.h"
 
 namespace gwq {
@@ -34,16 +36,23 @@ __device__ inline Merit merit_shuffle_down(const Merit &m, int delta)
     return Merit{__shfl_down(m.sq, delta), __shfl_down(m.first, delta), __shfl_down(m.mx, delta)};
 }
 
-// Fixed-order sum over the block: lanes by a shuffle tree, then the waves in order.  Valid in thread 0.
-__device__ inline Merit block_sum(Merit m, Merit *wave_part)
+// Fixed-order sum over a wave, by a shuffle tree.  Valid in lane 0.
+__device__ inline Merit wave_sum(Merit m)
 {
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) merit_add(m, merit_shuffle_down(m, d));
+    return m;
+}
+
+// Fixed-order sum over the block: its waves in order.  Valid in thread 0.
+template <int WAVES> __device__ inline Merit block_sum(Merit m, Merit *wave_part)
+{
+    m = wave_sum(m);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (lane == 0) wave_part[wave] = m;
     __syncthreads();
     if (threadIdx.x == 0)
-        for (int w = 1; w < kQThreads / 64; ++w) merit_add(m, wave_part[w]);
+        for (int w = 1; w < WAVES; ++w) merit_add(m, wave_part[w]);
     return m;
 }
 
@@ -72,6 +81,9 @@ template <int BITS> __device__ inline int code_of(uint32_t w0, uint32_t w1, uint
     return (int)((word >> (16 * (p & 1) + 3 * (p >> 1))) & 7u);
 }
 
+constexpr int kQTrip = 512;                             // weights per wave and trip
+
+// parts: waves per channel, 1 (four channels to a block, which never meet) or 4.
 template <int BITS, bool F16>
 __global__ __launch_bounds__(kQThreads) void quality_kernel(const uint32_t *__restrict__ qweight,
                                                             const uint16_t *__restrict__ scales,
@@ -80,38 +92,50 @@ __global__ __launch_bounds__(kQThreads) void quality_kernel(const uint32_t *__re
                                                             const uint16_t *__restrict__ col_idx,
                                                             const uint16_t *__restrict__ out_val,
                                                             const _Float16 *__restrict__ W, const void *__restrict__ score,
-                                                            int K, int group, Merit *__restrict__ partial)
+                                                            int N, int K, int group, int parts, Merit *__restrict__ partial)
 {
-    __shared__ uint32_t kept[65536 / 32];               // one bit per column: kept as an outlier
+    extern __shared__ uint32_t kept_lds[];              // one bit per column of each channel: kept as an outlier
     __shared__ Merit wave_part[kQThreads / 64];
-    const int n = blockIdx.x, tid = threadIdx.x;
-    const int gpr = K / kGroup, spr = K / group;        // blocks of 128 codes and scale groups per row
-    const size_t row = (size_t)n * K;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int n = parts == 1 ? (int)blockIdx.x * (kQThreads / 64) + wave : (int)blockIdx.x;
+    if (n >= N) return;                                 // whole waves, and only where nobody waits for them (parts = 1)
+    const int part = parts == 1 ? 0 : wave, trips = (K + kQTrip - 1) / kQTrip;
+    uint32_t *const kept = kept_lds + (parts == 1 ? wave * (K / 32) : 0);
+    // The channel's part of each array: uniform, so that a lane's place is a 32-bit offset.
+    qweight += (size_t)n * (K / kGroup) * words_per_group(BITS);
+    scales += (size_t)n * (K / group);
+    zeros += (size_t)n * (K / group);
+    W += (size_t)n * K;
+    score = static_cast<const char *>(score) + (size_t)n * K * (F16 ? 2 : 4);
+    const __attribute__((address_space(4))) int32_t *row_ptr_k =
+        (const __attribute__((address_space(4))) int32_t *)(uintptr_t)row_ptr;
+    const int e_begin = row_ptr_k[n], e_end = row_ptr_k[n + 1];
+    const int group_shift = 31 - __builtin_clz(group);
     Merit m{0.0, 0.0, 0.0};
 
-    // Requests for the chunk at k0 (clamped to the row: a chunk past its end is fetched again and not used).
-    auto fetch = [&](int k0, Chunk<BITS, F16> &c) {
-        k0 = k0 < K ? k0 : K - 8;
-        const int g = k0 / kGroup, slot = (k0 % kGroup) >> 5, j8 = (k0 & 31) >> 3;
-        const uint32_t *words = qweight + ((size_t)n * gpr + g) * words_per_group(BITS);
-        c.w = *reinterpret_cast<const uint4 *>(W + row + k0);
-        if (F16) {
-            c.g[0] = *reinterpret_cast<const uint4 *>(static_cast<const _Float16 *>(score) + row + k0);
-        } else {
-            c.g[0] = *reinterpret_cast<const uint4 *>(static_cast<const float *>(score) + row + k0);
-            c.g[F16 ? 0 : 1] = *reinterpret_cast<const uint4 *>(static_cast<const float *>(score) + row + k0 + 4);
-        }
+    // Requests for trip t (clamped to the row: a chunk past its end is fetched again and not used).
+    auto column = [&](int t) { return (uint32_t)(t * kQTrip + 8 * lane); };
+    auto fetch = [&](int t, Chunk<BITS, F16> &c) {
+        uint32_t k0 = column(t);
+        k0 = k0 < (uint32_t)K ? k0 : (uint32_t)K - 8;
+        const uint32_t slot = (k0 % kGroup) >> 5;
+        const uint32_t *words = qweight + (k0 / kGroup) * words_per_group(BITS);
+        c.w = *reinterpret_cast<const uint4 *>(W + k0);
+        const uint4 *g = reinterpret_cast<const uint4 *>(static_cast<const char *>(score) + k0 * (F16 ? 2 : 4));
+        c.g[0] = g[0];
+        if (!F16) c.g[F16 ? 0 : 1] = g[1];
         if (BITS == 4) {
-            c.code[0] = words[4 * slot + j8];
+            c.code[0] = qweight[k0 >> 3];
         } else {
             c.code[0] = words[3 * slot]; c.code[BITS == 4 ? 0 : 1] = words[3 * slot + 1]; c.code[BITS == 4 ? 0 : 2] = words[3 * slot + 2];
             c.code[BITS == 4 ? 0 : 3] = words[12];
         }
-        c.scale = scales[(size_t)n * spr + k0 / group];
-        c.zero = zeros[(size_t)n * spr + k0 / group];
+        c.scale = scales[k0 >> group_shift];
+        c.zero = zeros[k0 >> group_shift];
     };
-    auto consume = [&](int k0, const Chunk<BITS, F16> &c) {
-        if (k0 >= K) return;
+    auto consume = [&](int t, const Chunk<BITS, F16> &c) {
+        const uint32_t k0 = column(t);
+        if (k0 >= (uint32_t)K) return;
         const int slot = (k0 % kGroup) >> 5, c0 = k0 & 31;
         const double s = (double)(float)__builtin_bit_cast(_Float16, c.scale);
         const int z = c.zero;
@@ -119,51 +143,59 @@ __global__ __launch_bounds__(kQThreads) void quality_kernel(const uint32_t *__re
         uint32_t g4[8];
         g4[0] = c.g[0].x; g4[1] = c.g[0].y; g4[2] = c.g[0].z; g4[3] = c.g[0].w;
         if (!F16) { g4[4] = c.g[F16 ? 0 : 1].x; g4[5] = c.g[F16 ? 0 : 1].y; g4[6] = c.g[F16 ? 0 : 1].z; g4[7] = c.g[F16 ? 0 : 1].w; }
-        const uint32_t kept8 = (kept[k0 >> 5] >> (k0 & 31)) & 0xFFu;
+        const uint32_t kept8 = kept[k0 >> 5] >> (k0 & 31);
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            if (kept8 >> t & 1) continue;
-            const double w = (double)(float)__builtin_bit_cast(_Float16, (uint16_t)(w2[t >> 1] >> (16 * (t & 1))));
-            const double g = F16 ? (double)(float)__builtin_bit_cast(_Float16, (uint16_t)(g4[t >> 1] >> (16 * (t & 1))))
-                                 : (double)__builtin_bit_cast(float, g4[t]);
-            const double d = w - s * (double)(code_of<BITS>(c.code[0], c.code[BITS == 4 ? 0 : 1], c.code[BITS == 4 ? 0 : 2],
-                                                           c.code[BITS == 4 ? 0 : 3], slot, c0, t) - z);
+        for (int i = 0; i < 8; ++i) {
+            // A kept weight counts as 0 in all three, without a branch (a branch each made up half of the kernel).
+            const bool out = kept8 >> i & 1;
+            const float w = (float)__builtin_bit_cast(_Float16, (uint16_t)(w2[i >> 1] >> (16 * (i & 1))));
+            const float g = F16 ? (float)__builtin_bit_cast(_Float16, (uint16_t)(g4[i >> 1] >> (16 * (i & 1)))) : __builtin_bit_cast(float, g4[i]);
+            const int q = code_of<BITS>(c.code[0], c.code[BITS == 4 ? 0 : 1], c.code[BITS == 4 ? 0 : 2], c.code[BITS == 4 ? 0 : 3], slot, c0, i) - z;
+            const double d = (double)(out ? 0.f : w) - s * (double)(out ? 0 : q);
             m.sq += d * d;
-            m.first += g * d;
+            m.first += (double)(out ? 0.f : g) * d;
             m.mx = m.mx > fabs(d) ? m.mx : fabs(d);
         }
     };
 
     // The first two chunks are on their way while the channel's outliers are looked at.
-    constexpr int kStride = 8 * kQThreads;
     Chunk<BITS, F16> a, b;
-    fetch(8 * tid, a);
-    fetch(8 * tid + kStride, b);
+    fetch(part, a);
+    fetch(part + parts, b);
 
-    for (int i = tid; i < K / 32; i += kQThreads) kept[i] = 0u;
-    __syncthreads();
+    const int lanes = 64 * parts, at = lane + 64 * part;
+    auto meet = [&] {                                   // of the waves that share `kept`
+        if (parts > 1) __syncthreads();
+        else __builtin_amdgcn_wave_barrier();           // a wave's LDS accesses are in order
+    };
+    for (int i = at; i < K / 32; i += lanes) kept[i] = 0u;
+    meet();
     // The channel's outliers: mark their columns and take their own difference (zero when the stored
     // value is the weight's copy, as gwq_pack writes it).
-    for (int j = row_ptr[n] + tid; j < row_ptr[n + 1]; j += kQThreads) {
+    for (int j = e_begin + at; j < e_end; j += lanes) {
         const int c = col_idx[j];
         atomicOr(&kept[c >> 5], 1u << (c & 31));
-        const double d = (double)(float)W[row + c] - (double)(float)__builtin_bit_cast(_Float16, out_val[j]);
-        const double g = F16 ? (double)(float)static_cast<const _Float16 *>(score)[row + c]
-                             : (double)static_cast<const float *>(score)[row + c];
+        const double d = (double)(float)W[c] - (double)(float)__builtin_bit_cast(_Float16, out_val[j]);
+        const double g = F16 ? (double)(float)static_cast<const _Float16 *>(score)[c] : (double)static_cast<const float *>(score)[c];
         m.sq += d * d;
         m.first += g * d;
         m.mx = m.mx > fabs(d) ? m.mx : fabs(d);
     }
-    __syncthreads();
-    // Everything else, eight consecutive columns per thread and chunk, two chunks in flight.
-    for (int k0 = 8 * tid; k0 < K; k0 += 2 * kStride) {
-        consume(k0, a);
-        fetch(k0 + 2 * kStride, a);
-        consume(k0 + kStride, b);
-        fetch(k0 + 3 * kStride, b);
+    meet();
+    // Everything else, eight consecutive columns per lane and trip, two trips in flight.
+    for (int t = part; t < trips; t += 2 * parts) {
+        consume(t, a);
+        fetch(t + 2 * parts, a);
+        consume(t + parts, b);
+        fetch(t + 3 * parts, b);
     }
-    m = block_sum(m, wave_part);
-    if (tid == 0) partial[n] = m;
+    if (parts > 1) {
+        m = block_sum<kQThreads / 64>(m, wave_part);
+        if (threadIdx.x == 0) partial[n] = m;
+    } else {
+        m = wave_sum(m);
+        if (lane == 0) partial[n] = m;
+    }
 }
 
 // out[0..2] = the channels' partial results added in the order of n: thread t takes channels
@@ -183,7 +215,7 @@ __global__ __launch_bounds__(kQThreads) void quality_reduce_kernel(const Merit *
         for (int i = 0; i < 8; ++i) merit_add(m, p[i]);
     }
     for (; n < N; n += kQThreads) merit_add(m, partial[n]);
-    m = block_sum(m, wave_part);
+    m = block_sum<kQThreads / 64>(m, wave_part);
     if (threadIdx.x == 0) {
         out[0] = m.sq;
         out[1] = m.first;
@@ -200,9 +232,14 @@ hipError_t launch_quality(const gwq_packed &P, const void *W, const void *score,
 {
     Merit *partial = static_cast<Merit *>(workspace);
     const _Float16 *w = static_cast<const _Float16 *>(W);
+    // Short channels: one wave each, which nobody waits for (us of the call, one wave against four: 8192 x 1024 19.8 and 27.2;
+    // 11008 x 4096 with FP16 scores 50.1 and 53.7).  Long ones, or few: four (4096 x 11008 62.5 and 58.5; 16 x 65536 58 and 20).
+    const int parts = P.K <= (score_is_f16 ? 4096 : 2048) ? 1 : kQThreads / 64;
+    const int blocks = parts == 1 ? (P.N + kQThreads / 64 - 1) / (kQThreads / 64) : P.N;
+    const size_t lds = (size_t)(parts == 1 ? kQThreads / 64 : 1) * (P.K / 8);
 #define GWQ_QUALITY(B, F) \
-    quality_kernel<B, F><<<P.N, kQThreads, 0, st>>>(P.qweight, P.scales, P.zeros, P.row_ptr, P.col_idx, P.out_val, w, \
-                                                    score, P.K, P.group, partial)
+    quality_kernel<B, F><<<blocks, kQThreads, lds, st>>>(P.qweight, P.scales, P.zeros, P.row_ptr, P.col_idx, P.out_val, w, \
+                                                         score, P.N, P.K, P.group, parts, partial)
     if (P.bits == 4) {
         if (score_is_f16) GWQ_QUALITY(4, true); else GWQ_QUALITY(4, false);
     } else {
