@@ -11,8 +11,8 @@
 // a fixed order: lanes over their strided columns, a shuffle tree, the channel's waves in order, and a
 // second kernel over the channels; no floating-point atomics, results identical from run to run.
 // Bound by HBM: W (2 bytes), the score (4 or 2) and the packed layer (about 0.5) per weight, read once: 295 MB of
-// 11008 x 4096 with FP32 scores at 5.4 TB/s.  (A block of four waves per channel and a branch per kept weight: FP16 scores
-// 54.4 us, now 50.1; 8192 x 1024 27.2, now 19.8; 3 bits, groups of 16 70.5, now 64.)
+// 11008 x 4096 with FP32 scores at 5.4 TB/s.  (A block of four waves for every channel and a branch per kept weight: 8192 x
+// 1024 27.2 us, now 19.5; 11008 x 2048 43, now 34; 11008 x 4096 at 3 bits, groups of 16 69, now 67.)
 #include "gwq_internal.h"
 
 namespace gwq {
@@ -232,9 +232,10 @@ hipError_t launch_quality(const gwq_packed &P, const void *W, const void *score,
 {
     Merit *partial = static_cast<Merit *>(workspace);
     const _Float16 *w = static_cast<const _Float16 *>(W);
-    // Short channels: one wave each, which nobody waits for (us of the call, one wave against four: 8192 x 1024 19.8 and 27.2;
-    // 11008 x 4096 with FP16 scores 50.1 and 53.7).  Long ones, or few: four (4096 x 11008 62.5 and 58.5; 16 x 65536 58 and 20).
-    const int parts = P.K <= (score_is_f16 ? 4096 : 2048) ? 1 : kQThreads / 64;
+    // Short channels: one wave each, which nobody waits for (us of the call, one wave against four: 8192 x 1024 19.5 and 27.2;
+    // 11008 x 2048 34 and 43).  Long ones: four, which share the outliers of a channel that has many (4096 x 4096, FP16 scores,
+    // outliers in 2 % of the channels: 38.5 and 27; outliers all over 25 and 26; 4096 x 11008, FP32 62.5 and 58.5).
+    const int parts = P.K <= 2048 ? 1 : kQThreads / 64;
     const int blocks = parts == 1 ? (P.N + kQThreads / 64 - 1) / (kQThreads / 64) : P.N;
     const size_t lds = (size_t)(parts == 1 ? kQThreads / 64 : 1) * (P.K / 8);
 #define GWQ_QUALITY(B, F) \
