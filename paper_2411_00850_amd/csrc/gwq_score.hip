@@ -359,6 +359,17 @@ __global__ __launch_bounds__(kBigThreads) void score_big_kernel(const _Float16 *
             for (int u = 0; u < 2; ++u) acc[s][u] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[set][s], fb[set][u], acc[s][u], 0, 0, 0);
     };
 
+    // The twelve reads of the next batch go between the eight MFMAs of this one, two behind each.
+    auto interleave = [] {
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);          // an MFMA
+            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);          // LDS reads
+        }
+        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
     // Steps 0, 1, 2 requested (unaligned: dY of steps 0 and 1); all of that staged.
     u32x4s first[2], second[2];
     if constexpr (!N8) {
@@ -386,10 +397,10 @@ __global__ __launch_bounds__(kBigThreads) void score_big_kernel(const _Float16 *
             if (more) request_b(t + 3);
             if (t + 2 < steps) request_piece(t + 2, piece);
         }
+        __builtin_amdgcn_sched_barrier(0);
         read_batch(t, 1, 1);
-        __builtin_amdgcn_sched_barrier(0);
         multiply(0);
-        __builtin_amdgcn_sched_barrier(0);
+        interleave();
         if constexpr (N8) {
             // Step t + 1 has landed, the two behind it may be on their way.
             if (more) wait_loads<8>();
@@ -397,10 +408,10 @@ __global__ __launch_bounds__(kBigThreads) void score_big_kernel(const _Float16 *
             if (t + 1 < steps) zero_tail(t + 1);
         }
         __syncthreads();
+        __builtin_amdgcn_sched_barrier(0);
         read_batch(t + 1, 0, 0);                        // past the last step: stale bytes, not used
-        __builtin_amdgcn_sched_barrier(0);
         multiply(1);
-        __builtin_amdgcn_sched_barrier(0);
+        interleave();
         if constexpr (!N8) {
             // Step t + 2 is staged a barrier before it is read: its pieces have had this whole step to arrive, and X of the
             // steps up to t + 3 arrives with them.
