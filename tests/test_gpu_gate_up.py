@@ -91,6 +91,22 @@ def test_small_groups(bits, group, N, K):
         _check(layers, rng, M, f"gate_up group={group} N={N} K={K} M={M} bits={bits}")
 
 
+@pytest.mark.parametrize("bits", [4, 3])
+@pytest.mark.parametrize("group", [16, 64, 128])
+@pytest.mark.parametrize("N,K", [(16, 128), (50, 1152), (333, 2048), (77, 2432), (2070, 4096), (2100, 4992), (4200, 2176)])
+def test_two_sets_of_waves(bits, group, N, K):
+    """Up to eight rows with one set of waves for gate and one for up, and the calls beside them: one wave a set to seven, half
+    a block per CU to two, ragged last tiles, both layers' outlier counts, the up layer's beyond a set's staged window (6 %)."""
+    layers, rng = _pair(group + N + K + bits, N, K, bits, group, ppm=(10000, 60000 if N < 100 else 10000))
+    for M in (1, 2, 3, 4, 5, 6, 7, 8) if N * K < 1000000 else (1, 4, 5, 8)[bits - 3::2]:
+        _check(layers, rng, M, f"gate_up group={group} N={N} K={K} M={M} bits={bits}")
+
+
+@pytest.mark.parametrize("M,group", [(1, 128), (5, 32), (8, 64)])
+def test_two_sets_replayed_from_a_graph(M, group):
+    test_replayed_from_a_graph(M, group)
+
+
 @pytest.mark.parametrize("M,group", [(4, 16), (8, 128), (16, 128)])
 def test_replayed_from_a_graph(M, group):
     import torch
