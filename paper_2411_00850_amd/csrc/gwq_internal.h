@@ -47,7 +47,8 @@ __host__ __device__ constexpr uint32_t index_scale_cap(int bits) { return bits =
 // kWsStep + 2 i, + 1     after digit i: what is known of the threshold, and how many entries are still wanted from there
 // kWsRows + 0*N ..       per row: count of keys above the threshold
 // kWsRows + 1*N ..       per row: count of keys equal to the threshold
-// kWsRows + 2*N ..       per row: how many of its threshold ties are kept
+// kWsRows + 2*N ..       per row: how many of its threshold ties are kept; up to kSummedRows rows: the first two of the counts
+//                        above, summed over blocks of rows, each in a line of its own
 // kWsRows + 3*N ..       kSelBins words: three times kSpread whose sums are the keys above the band, where it is a single key
 //                        the keys equal to it, and the candidates
 // then                   per row: number of candidates; then the candidates' keys, [N][pack_candidates_per_row(K)]
@@ -74,7 +75,7 @@ inline size_t pack_workspace_bytes(int64_t N, int64_t K)
 enum class PackWay { by_size = 0, scores = 1, list = 2 };
 hipError_t launch_pack(const void *W, const void *score, int score_is_f16, const gwq_packed &P,
                        uint32_t *ws, PackWay way, hipStream_t stream);
-// Measurement overrides of the decode launch (0 = built-in choice): waves per block of the kernel for M <= 4;
+// Measurement overrides of the decode launch (0 = built-in choice): waves per block of the lean kernel;
 // streaming kernel 1 = never, 2 = for every M <= 16 it can take; its tiles per block.
 struct DecodeTuning {
     int waves, stream, tiles;
@@ -121,7 +122,7 @@ hipError_t launch_quality(const gwq_packed &P, const void *W, const void *score,
 hipError_t launch_probe_stream(const void *src, size_t bytes, void *sink, hipStream_t stream);
 hipError_t launch_probe_mfma(int blocks, int iters, void *sink, hipStream_t stream);
 
-// H = silu(G) * U elementwise over `count` FP16 values (the unfused form of the gated pair, for M > 4).
+// H = silu(G) * U elementwise over `count` FP16 values (the unfused form of the gated pair).
 hipError_t launch_silu_mul(const void *G, const void *U, void *H, size_t count, hipStream_t stream);
 
 // score = beta * score + alpha * dY^T X (dY [M][N], X [M][K] FP16; score [N][K] FP32); K a multiple of 128.

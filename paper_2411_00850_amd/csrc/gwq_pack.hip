@@ -110,7 +110,8 @@ template <int WAVES> __device__ inline uint32_t block_exclusive_scan(uint32_t v,
 // The line: sample, band and candidates are three launches and 20 us (a block for the band alone takes 10), which a pass over
 // all scores takes less than from the caches up to about nine million of them.  us of a whole gwq_pack replayed from a graph,
 // 4 bits, 1 % outliers: the histograms in global memory / by list / by scores, * the one taken ("few rows": all outliers
-// in 2 % of the rows, which by list ends by scores):
+// in 2 % of the rows, which by list ends by scores), with an encoder that took 1 to 4 us
+// more and the launch of row_scan_kernel on all sides:
 //     scores                  512 x 512        1000 x 2048        1024 x 4096        1024 x 8192       11008 x 1024        4096 x 4096
 //     normal, FP32        35 / 39 / 29*      46 / 40 / 36*      54 / 44 / 44*      70 / 56 / 56*      86 / 70* / 79      94 / 70* / 89
 //     normal, FP16        30 / 33 / 26*      41 / 37 / 34*      49 / 42 / 40*      65 / 54 / 54*      77 / 67* / 68      90 / 66* / 73
@@ -122,6 +123,29 @@ template <int WAVES> __device__ inline uint32_t block_exclusive_scan(uint32_t v,
 // Larger, normal scores: 11008 x 4096 193 / 124*, 8192 x 28672 895 / 592*.
 constexpr size_t kScoresUpTo = (size_t)8 << 20;
 enum Way { kByList = 1, kByScores = 2, kSingleKey = 3 };        // what the launches found, in the workspace
+
+// Where a row's outliers start is the count of what the rows before it keep.  Up to kSummedRows rows each wave of the encoder
+// adds that up for itself (rows_before), from the rows of its own block of rows and the sums of the blocks before it, which
+// rows_kernel has made, and writes row_ptr; beyond, one block of threads does it for all rows (row_scan_kernel), a launch that
+// waits for the one before and takes 4.0 us up to 4096 rows, 8.2 at 11008.  The sums are added up with atomics, and those on one
+// line are served one after another, 15 ns each: a line for each sum, several rows to an atomic, and up to 1024 rows are a
+// single block, which needs none.  The line: a wave reads a line for every 256 rows before its own.  us of a whole gwq_pack replayed
+// from a graph, 4 bits, with the launch / without:
+//     scores         64 x 512      1024 x 4096    4096 x 4096    11008 x 4096     28672 x 1024     65536 x 128      65536 x 1024     131072 x 1024
+//     FP32        26.8 / 23.8*    43.0 / 40.3*   67.0 / 63.8*   118.7 / 111.4*   115.2 / 98.7*   154.2 / 128.5*   241.0 / 234.0*   450.1* / 487.2
+//     FP16        24.1 / 21.0*    38.6 / 36.7*   62.6 / 59.9*   104.8 / 97.7*    108.2 / 95.0*   164.0 / 132.8*   203.6 / 194.5*   399.7* / 437.3
+constexpr int kSummedRows = 65536, kSumStride = 32;     // words from one block's sums to the next
+__host__ __device__ constexpr int block_rows_log2(int N) { return N <= 1024 ? 10 : 8; }
+__device__ inline uint32_t *block_sums(uint32_t *ws, int N) { return ws + kWsRows + 2 * (size_t)N; }
+// Adds to the sums of row n's block: keys above the threshold and equal to it.  The last block's nobody reads.
+__device__ inline void add_to_block(uint32_t *ws, int N, int n, uint32_t gt, uint32_t eq)
+{
+    const int b = n >> block_rows_log2(N);
+    if (N > kSummedRows || b >= (N - 1) >> block_rows_log2(N)) return;
+    uint32_t *s = block_sums(ws, N) + (size_t)b * kSumStride;
+    if (gt) atomicAdd(&s[0], gt);
+    if (eq) atomicAdd(&s[1], eq);
+}
 
 // The sample: pieces of 16 bytes, one at a pseudo-random place of each of as many equal parts of the scores - one of 32 there
 // are, 8192 (FP16 scores: 4096) at most; as keys into the part of the workspace where the candidates come later, which holds
@@ -138,6 +162,8 @@ __global__ __launch_bounds__(kThreads) void sample_kernel(const void *__restrict
     const uint32_t j = blockIdx.x * kThreads + threadIdx.x, threads = gridDim.x * kThreads;
     for (uint32_t i = j; i < kWsRows; i += threads) ws[i] = i == kWsWanted ? k_out : i == kWsCandOverflow ? parts == 0 : 0u;
     for (uint32_t i = j; i < 3 * kSpread; i += threads) ws[kWsRows + 3 * N + i] = 0;
+    if (N <= kSummedRows)
+        for (uint32_t i = j; i < 2u * (uint32_t)((N - 1) >> block_rows_log2(N)); i += threads) block_sums(ws, N)[i / 2 * kSumStride + i % 2] = 0;
     if (j >= parts) return;
     const uint64_t pieces = total / kKeys;              // total is a multiple of 128
     const uint64_t lo = j * pieces / parts, hi = (j + 1) * pieces / parts;
@@ -432,13 +458,25 @@ __global__ __launch_bounds__(kDigitThreads) void digit_kernel(const void *score,
         if (h[i]) atomicAdd(&g[i], h[i]);
 }
 
-// Picks the last digit, and per row: how many keys are above the threshold and how many are equal to it.
+// Picks the last digit, and per row: how many keys are above the threshold and how many are equal to it; and the sums of both
+// over blocks of rows.
 template <bool F16>
 __global__ __launch_bounds__(kThreads) void rows_kernel(const void *score, int K, uint32_t *ws, int N, int per_row)
 {
     __shared__ uint32_t red[2][kWaves], smem[kWaves];
     const uint32_t way = ws[kWsWay];
-    if (way == kSingleKey) return;                      // both are known
+    if (way == kSingleKey) {                            // both are known
+        if (N > kSummedRows) return;
+        const int wave = blockIdx.x * kWaves + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+        for (int n0 = 64 * wave; n0 < N; n0 += 64 * kWaves * (int)gridDim.x) {
+            uint32_t gt = 0, eq = 0;
+            if (n0 + lane < N) gt = ws[kWsRows + n0 + lane], eq = ws[kWsRows + N + n0 + lane];
+#pragma unroll
+            for (int d = 32; d > 0; d >>= 1) { gt += __shfl_xor(gt, d); eq += __shfl_xor(eq, d); }
+            if (lane == 0) add_to_block(ws, N, n0, gt, eq);
+        }
+        return;
+    }
     int last = F16 ? 1 : 2, below = 0;                  // the last digit counted
     if (way == kByList) {
         const uint32_t lo = ws[kWsBandLo], hi = ws[kWsBandHi];
@@ -458,12 +496,26 @@ __global__ __launch_bounds__(kThreads) void rows_kernel(const void *score, int K
         }, [&](int n) {
 #pragma unroll
             for (int d = 8; d > 0; d >>= 1) { gt += __shfl_xor(gt, d); eq += __shfl_xor(eq, d); }
-            if ((threadIdx.x & 15) == 0 && n < N) { ws[kWsRows + n] += gt; ws[kWsRows + N + n] = eq; }
+            if ((threadIdx.x & 15) == 0 && n < N) {
+                gt += ws[kWsRows + n];
+                ws[kWsRows + n] = gt;
+                ws[kWsRows + N + n] = eq;
+            } else {
+                gt = eq = 0;
+            }
+            gt += __shfl_xor(gt, 16);                   // lane 0: the wave's four rows
+            eq += __shfl_xor(eq, 16);
+            gt += __shfl_xor(gt, 32);
+            eq += __shfl_xor(eq, 32);
+            if ((threadIdx.x & 63) == 0) add_to_block(ws, N, n, gt, eq);
             gt = eq = 0;
         });
         return;
     }
-    for (int n = blockIdx.x; n < N; n += gridDim.x) {
+    // Neighbouring rows to a block of threads: one atomic for those of one block of rows.
+    const int rows = (N + (int)gridDim.x - 1) / (int)gridDim.x, n_begin = (int)blockIdx.x * rows, n_end = min(n_begin + rows, N);
+    uint32_t sum_gt = 0, sum_eq = 0;
+    for (int n = n_begin; n < n_end; ++n) {
         uint32_t gt = 0, eq = 0;
         for (int k = threadIdx.x * 8; k < K; k += kElemsPerIter) {
             uint32_t key[8];
@@ -481,10 +533,17 @@ __global__ __launch_bounds__(kThreads) void rows_kernel(const void *score, int K
             for (int i = 0; i < kWaves; ++i) { a += red[0][i]; b += red[1][i]; }
             ws[kWsRows + n] = a;
             ws[kWsRows + N + n] = b;
+            sum_gt += a;
+            sum_eq += b;
+            if (n + 1 == n_end || (n + 1) >> block_rows_log2(N) != n >> block_rows_log2(N)) {
+                add_to_block(ws, N, n, sum_gt, sum_eq);
+                sum_gt = sum_eq = 0;
+            }
         }
     }
 }
 
+// More than kSummedRows rows: the kept ties of every row and row_ptr.
 // Ties at the threshold are kept in flat-index order until `remaining` of them are taken;
 // row_ptr is the running count of kept entries.  One block, since every row needs the sum of those before it; a chain of
 // two block scans and their barriers per round bounds it, so a round takes many rows (4096: four consecutive rows for each
@@ -565,14 +624,15 @@ __global__ __launch_bounds__(kScanThreads) void row_scan_kernel(uint32_t *ws, in
 // by DPP, the 3-bit words are put together across a quad of lanes.  (The four waves of a shared row exchange once, before
 // their trips, what each part keeps.)  The next trip's weights and scores are requested before this trip's are worked on.
 //
-// Bound by HBM (6.56 bytes per weight at FP32 scores), which needs the instruction stream short: about 300 vector
+// Bound by HBM (6.56 bytes per weight at FP32 scores), which needs the instruction stream short: about 180 vector
 // instructions per trip and wave.  A kept weight is replaced by 0: a group's range always contains 0 and 0 gets the code
 // z, so masking it once serves the range and the code.  The quotient w / s is one reciprocal per group and three
 // instructions per weight (see quotient).
 //
-// Measured, 11008 x 4096 and 4096 x 11008, 4 bits, FP32 scores, with the layer's index: 51 .. 56 us = 5.3 .. 5.8 TB/s (a
-// block of four waves per row with a barrier per 2048 weights, IEEE divisions and fp64 scales took 88 .. 92 us, and 7 .. 12 us
-// more for a kernel that wrote the index).
+// Measured, 11008 x 4096, 4 bits, with the layer's index, medians of a kernel trace (in brackets, on the same machine, with 300
+// instructions a trip: ranges as numbers, a branch per kept weight, register sets copied): FP32 scores 48.9 us = 6.0 TB/s
+// (52.7), FP16 41.3 (48.0), 3 bits in groups of 16 53.1 (57.1).  (A block of four waves per row with a barrier per 2048
+// weights, IEEE divisions and fp64 scales took 88 .. 92 us, and 7 .. 12 us more for a kernel that wrote the index.)
 
 // w / s for an FP16 number w and the FP16 scale s (r: its reciprocal to 1 ulp), by one step of Markstein's correction with
 // fused multiply-adds: the product with r is within 2^-22 of the quotient, its residual w - t s has at most 13 significant bits and is exact, and the correction leaves an error below
@@ -689,12 +749,37 @@ template <bool F16> struct EncodeRegs {
 
 constexpr int kTrip = 512;                              // weights per wave and trip
 
+// What the rows before row n keep, by a wave: `start`; of row n's keys equal to the threshold the first `take` are kept;
+// `end`: start and what row n keeps.  Of the ties in the rows before, in flat-index order, the first `need` are kept.
+struct RowRange { uint32_t start, take, end; };
+__device__ inline RowRange rows_before(const uint32_t *ws, int N, int n)
+{
+    const int lane = threadIdx.x & 63, log2 = block_rows_log2(N), block = n >> log2;
+    const uint32_t *gt_of = ws + kWsRows, *eq_of = gt_of + N, *sums = eq_of + N;
+    uint32_t gt = 0, eq = 0;
+    // The block's rows, four to a lane.  (What lies behind the counts of equal keys is the block sums, at 4 bytes' alignment.)
+    for (int r0 = block << log2; r0 < n; r0 += 256) {
+        const int r = r0 + 4 * lane;
+        if (r < n) {
+            const Keys4 g = *reinterpret_cast<const Keys4 *>(gt_of + r), e = *reinterpret_cast<const Keys4 *>(eq_of + r);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) { gt += r + i < n ? g.k[i] : 0u; eq += r + i < n ? e.k[i] : 0u; }
+        }
+    }
+    for (int b = lane; b < block; b += 64) { gt += sums[b * kSumStride]; eq += sums[b * kSumStride + 1]; }
+    const uint32_t need = ws[kWsRemaining], mine = gt_of[n], ties = eq_of[n];
+    gt = (uint32_t)__builtin_amdgcn_readlane((int)wave_sum_to_here(gt), 63);
+    eq = (uint32_t)__builtin_amdgcn_readlane((int)wave_sum_to_here(eq), 63);
+    const uint32_t taken = eq < need ? eq : need, left = need - taken, take = ties < left ? ties : left;
+    return {gt + taken, take, gt + taken + mine + take};
+}
+
 // STEPS: log2 of the lanes that share a group (group = 16, 32, 64, 128: 1 to 4).  parts: waves per row, 1 or 4.
 // rec, fine: the layer's index (gwq_internal.h), or NULL.
 template <int BITS, bool F16, int STEPS>
 __global__ __launch_bounds__(kThreads) void encode_kernel(const uint16_t *__restrict__ W, const void *__restrict__ score, int N, int K,
                                                           int parts, const uint32_t *__restrict__ ws,
-                                                          const int32_t *__restrict__ row_ptr, uint32_t *__restrict__ qweight,
+                                                          int32_t *__restrict__ row_ptr, uint32_t *__restrict__ qweight,
                                                           uint16_t *__restrict__ scales, uint8_t *__restrict__ zeros,
                                                           uint16_t *__restrict__ col_idx, uint16_t *__restrict__ out_val,
                                                           GroupRecord *__restrict__ rec, uint32_t *__restrict__ fine)
@@ -712,9 +797,19 @@ __global__ __launch_bounds__(kThreads) void encode_kernel(const uint16_t *__rest
     const int t_begin = parts == 1 ? 0 : wave * per_part;
     const int t_end = t_begin + per_part < trips ? t_begin + per_part : trips;
     const uint32_t thr = ws[kWsPrefix];
-    const uint32_t take = ws[kWsRows + 2 * N + n];      // of the row's keys equal to the threshold the first `take` are kept
     const int gpr = K / kGroup, spr = K / group;
-    const uint32_t row_start = (uint32_t)row_ptr[n];
+    RowRange row;
+    if (N <= kSummedRows) {
+        row = rows_before(ws, N, n);
+        if (lane == 0 && t_begin == 0) {
+            row_ptr[n] = (int32_t)row.start;
+            if (n == N - 1) row_ptr[N] = (int32_t)row.end;
+        }
+    } else {
+        row = {(uint32_t)row_ptr[n], ws[kWsRows + 2 * N + n], (uint32_t)row_ptr[n + 1]};
+    }
+    const uint32_t take = row.take;                     // of the row's keys equal to the threshold the first `take` are kept
+    const uint32_t row_start = row.start;
     // The row's part of each array: uniform, so that a lane's place is a 32-bit offset.
     W += (size_t)n * K;
     const char *const row_score = static_cast<const char *>(score) + (size_t)n * K * (F16 ? 2 : 4);
@@ -727,7 +822,7 @@ __global__ __launch_bounds__(kThreads) void encode_kernel(const uint16_t *__rest
     if (rec) {
         rec += (size_t)n * (gpr + 1);
         fine += (size_t)n * (K / 16);
-        if (lane == 0 && t_begin == 0) rec[gpr] = GroupRecord{row_ptr[n + 1], 0u};
+        if (lane == 0 && t_begin == 0) rec[gpr] = GroupRecord{(int32_t)row.end, 0u};
     }
 
     // Lanes beyond the end of the row (whole groups of lanes) repeat its last weights and keep nothing.
@@ -896,7 +991,7 @@ hipError_t run_select(const void *score, int N, int K, uint32_t *ws, int32_t *ro
     } else {
         nothing_kernel<<<8, kThreads, 0, st>>>(ws, N);
     }
-    row_scan_kernel<<<1, kScanThreads, 0, st>>>(ws, N, row_ptr);
+    if (N > kSummedRows) row_scan_kernel<<<1, kScanThreads, 0, st>>>(ws, N, row_ptr);
     return hipGetLastError();
 }
 

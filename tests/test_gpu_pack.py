@@ -408,3 +408,21 @@ def test_pack_at_the_line_between_the_two_ways(N):
     W = gs.weight(N, 8192, rng, planted_cols=2)
     S = gs.score_from_weight(W, rng)
     assert_packed_equal(_gpu_pack(W, S, 4, 10000), orc.pack(W, S, 4, 10000))
+
+
+@pytest.mark.parametrize("f16", [False, True])
+@pytest.mark.parametrize("kind", ["normal", "ties", "all_equal"])
+@pytest.mark.parametrize("N", [256, 1024, 1025, 1281, 2560, 65536, 65537])
+def test_pack_row_starts(N, kind, f16, way):
+    """Where each row's outliers start: summed up by the encoder from its block of 256 rows (up to 1024 rows: all rows) and the
+    sums of the blocks before, beyond 65536 rows by a launch of its own; with the last kept of the ties in a middle block."""
+    from gpu_helpers import assert_packed_equal
+    W, S = _small(N + len(kind), N, 128, score_dtype=np.float16 if f16 else np.float32)
+    ppm = 10000
+    if kind == "ties":                              # 3 % at the largest value but for the first rows, a third of them kept
+        rng = np.random.default_rng(N)
+        S[N // 8:][rng.random((N - N // 8, 128)) < 0.03] = 1e4
+    elif kind == "all_equal":
+        S[:] = 0.125
+        ppm = 500000
+    assert_packed_equal(_gpu_pack(W, S, 4, ppm), orc.pack(W, S, 4, ppm))
