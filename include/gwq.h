@@ -230,10 +230,11 @@ gwq_status gwq_score(const void *dY_f16, const void *X_f16, int32_t M, int32_t N
 /* The gated pair of a decoder layer's MLP in decode (M <= 16):
  *   H[m][n] = silu(G[m][n]) * U[m][n],   G = gwq_linear(P_gate, X),  U = gwq_linear(P_up, X),  silu(x) = x / (1 + e^-x)
  * What the efficiency table (Sec. 4.2) times is whole-model generation, where every decoder layer runs this pair
- * and then the down projection on H; at decode sizes a launch is bound by latency, so for groups of 128 both products
- * and the gate are one launch where a kernel holds the rows and is faster than two (M <= 4: K <= 16384; 5 <= M <= 8: two blocks'
- * data fit the LDS of a compute unit, and above K = 4096 not for 257 to 384 blocks of 16 channels; up to M = 16 else:
- * 1536 < K <= 4096, above 2048 with at least two 16-channel tiles of each layer per block, and tiles that are shared out
+ * and then the down projection on H; at decode sizes a launch is bound by latency, so both products
+ * and the gate are one launch where a kernel holds the rows and is faster than two (M <= 4, groups of 128: K <= 16384; 5 <= M <= 8, and
+ * M <= 8 with smaller groups: two blocks' data fit the LDS of a compute unit, by the number of blocks and the length of
+ * the rows; up to M = 16 else, groups of 128: 1536 < K <= 4096, above 2048 with at least two 16-channel tiles of each layer
+ * per block, and tiles that are shared out
  * as evenly as those of two products): the FP32 sums of the gate product never leave the block and
  * G and U are never written.  Otherwise the two products go to `workspace` (device, >= 4*M*N bytes, 16-byte aligned; may be
  * NULL for M <= 4 with K <= 16384 and groups of 128) and a third launch combines them.

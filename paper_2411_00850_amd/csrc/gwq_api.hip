@@ -343,7 +343,7 @@ gwq_status gwq_linear_gate_up(const gwq_packed *P_gate, const gwq_packed *P_up, 
         if (e == hipSuccess) return GWQ_OK;
         if (e != hipErrorNotSupported) return GWQ_ERR_DEVICE;
     }
-    // Rows too long for those kernels, and more than four rows with groups below 128: the two products, then H.
+    // Where no such kernel holds the rows or is the faster way: the two products, then H.
     if (!room) return GWQ_ERR_WORKSPACE;
     void *y[2] = {workspace, static_cast<char *>(workspace) + each};
     hipError_t e = gwq::launch_decode(2, p, x, M, y, decode_tuning(), st);

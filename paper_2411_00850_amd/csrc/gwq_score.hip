@@ -208,10 +208,14 @@ __global__ __launch_bounds__(kScoreThreads, N8 ? 2 : 1) void score_kernel(const 
 //
 // Measured at M = 2048 (128 x 128 tiles in brackets), calls replayed from a graph on normally distributed inputs:
 // 4096 x 4096, one round of tiles, 73.7 us = 932 TFLOP/s (104.9); 4096 x 11008 192 us (262), accumulating 210 us (318);
-// unaligned 3333 x 4096 75 us (336), 9001 x 4096 193 us (753).  The matrix cores work 43 to 45 % of the time, the LDS sees
+// unaligned 3333 x 4096 75 us (336), 9001 x 4096 193 us (753).  That was with all reads of a batch before its MFMAs; with two
+// behind each MFMA (interleave), on another machine, both in turn: 4096 x 4096 71.7 -> 68.9 us (1.0 PFLOP/s), 11008 x 4096
+// 196 -> 185, two samples into one score 4096 x 11008 410 -> 397, unaligned 9001 x 4096 406 -> 394.  On zeros 158 -> 147 where
+// normal inputs take 196 -> 185: the difference is power.  The matrix cores work 53 to 55 % of the time (48 to 50 before), the LDS sees
 // no bank conflict.  What is left at 4096 x 11008: 688 tiles on 256 CUs are three rounds at 2.69 rounds' work, and 180 MB
 // of FP32 scores (36 us at HBM speed) are written at the rounds' ends.  Four waves of 128 x 128 (a third less LDS traffic,
-// one wave per SIMD): 10 % slower.
+// one wave per SIMD): 10 % slower, and slower with the reads so placed too; nontemporal stores: 10 % slower; the old score
+// requested a tile ahead: no difference.
 //
 // N8 = false: rows of dY are not 16-byte aligned.  Their pieces come through registers (loads at 2-byte alignment, requested
 // at the start of a step and stored at its end); only the piece that would reach beyond the end of dY is read from 16 bytes before
