@@ -268,6 +268,7 @@ __device__ inline void frag_tile(const FragArgs &a, char *lds)
                 for (int i = 0; i < I; ++i) window_first[i] = now[i].x;
             }
             keep_side(k - D, r);
+            if (k == 7) wave_meet();                    // the next window's entries, stored up to now, are read in this trip
             uint32_t side_first = 0;
             if (asks_entries(k)) side_first = read_rec(rec_window[1], g0 + 8, 0, side_run(k)).x;
 #pragma unroll
@@ -303,7 +304,7 @@ __device__ inline void frag_tile(const FragArgs &a, char *lds)
                 store16(rec_window[0] + P * i * kRun, v0[i]);
                 store16(rec_window[1] + P * i * kRun, v1[i]);
             }
-            __builtin_amdgcn_wave_barrier();
+            wave_meet();
 #pragma unroll
             for (int i = 0; i < I; ++i) {
                 now[i] = read_rec(rec_window[0], 0, 0, i);
@@ -316,7 +317,7 @@ __device__ inline void frag_tile(const FragArgs &a, char *lds)
                 store16(csr_window[0] + 2 * P * i * kRun, v0[i]);
                 store16(csr_window[0] + (2 * P * i + 1) * kRun, v1[i]);
             }
-            __builtin_amdgcn_wave_barrier();
+            wave_meet();
 #pragma unroll
             for (int i = 0; i < I; ++i) {
                 read_entries(csr_window[0], now[i].x, now[i].x, i);
@@ -449,7 +450,7 @@ __device__ inline void frag_tile(const FragArgs &a, char *lds)
         for (int n = 0; n < NB; ++n)
             *reinterpret_cast<act4 *>(out + (16 * j + row) * kOut + 32 * n + 8 * b) =
                 act4{(act_t)acc[j][n][0], (act_t)acc[j][n][1], (act_t)acc[j][n][2], (act_t)acc[j][n][3]};
-    __builtin_amdgcn_wave_barrier();
+    wave_meet();
     const int ch = n_wave + 8 * (lane % kLanes);
 #pragma unroll
     for (int i = 0; i < 16 * J * kLanes / 64; ++i) {

@@ -15,6 +15,15 @@ constexpr int kMaxBatch = GWQ_MAX_BATCH;   // layers per grouped decode launch
 
 __host__ __device__ constexpr int words_per_group(int bits) { return bits == 4 ? 16 : 13; }
 
+// What lanes of a wave wrote to the LDS before this, its other lanes read after it.  A wave's LDS accesses are carried out in
+// order, so nothing is waited for; the fences hold the compiler to the order of the source, which the barrier alone does not.
+__device__ inline void wave_meet()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Compute units of the current device, asked once per device (256 on MI355X; 256 if the query fails).
 int device_cus();
 

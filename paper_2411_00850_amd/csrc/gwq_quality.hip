@@ -166,7 +166,7 @@ __global__ __launch_bounds__(kQThreads) void quality_kernel(const uint32_t *__re
     const int lanes = 64 * parts, at = lane + 64 * part;
     auto meet = [&] {                                   // of the waves that share `kept`
         if (parts > 1) __syncthreads();
-        else __builtin_amdgcn_wave_barrier();           // a wave's LDS accesses are in order
+        else wave_meet();
     };
     for (int i = at; i < K / 32; i += lanes) kept[i] = 0u;
     meet();

@@ -43,3 +43,13 @@ def test_the_check_tells_the_forms_apart():
             'asm volatile("s_mov_b32 m0, %0\\n\\ts_nop 0\\n\\tglobal_load_lds_dwordx4 %1, %2" ::"s"(d), "v"(o), "s"(b) : "memory");',
             'asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");  // asm("global_load_dword")']
     assert len(loads_in_flight(bad)) == 1 and not any(loads_in_flight(g) for g in good)
+
+
+@pytest.mark.parametrize("name", sorted(f for f in os.listdir(CSRC) if f.endswith((".hip", ".h"))))
+def test_wave_barriers_order_memory(name):
+    """Lanes of a wave that hand data to each other through the LDS need no wait, but the barrier of a wave orders no memory
+    accesses for the compiler: it stands between fences of the wave's scope."""
+    text = re.sub(r"//[^\n]*|/\*.*?\*/", "", open(os.path.join(CSRC, name)).read(), flags=re.S)
+    fenced = (r'__builtin_amdgcn_fence\(__ATOMIC_RELEASE, "wavefront"\);\s*__builtin_amdgcn_wave_barrier\(\);\s*'
+              r'__builtin_amdgcn_fence\(__ATOMIC_ACQUIRE, "wavefront"\);')
+    assert "__builtin_amdgcn_wave_barrier" not in re.sub(fenced, "", text)
