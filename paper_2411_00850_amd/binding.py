@@ -4,10 +4,12 @@ The library is loaded from this directory.  It is built by `__graft_entry__.buil
 `python -m paper_2411_00850_amd.build`); if it is missing, it is built here once - but only while this
 process has not touched the GPU yet (a compiler run started from a process that holds the GPU, or from
 under a profiler's preload, is not safe), otherwise loading raises.  A library older than its sources
-is loaded with a warning.  There is no fallback path: without the library every call raises.
+is loaded with a warning.  There is no fallback path: without the library every call raises.  The extension
+module _call.so is a shorter way to two of the calls; where it is missing they go through ctypes.
 """
 import ctypes
 import os
+import warnings
 from dataclasses import dataclass
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -61,8 +63,7 @@ def lib():
                                    "__graft_entry__.build() (or python -m paper_2411_00850_amd.build) first")
             _build.build(sanitize_host=_LIB_PATH.endswith("libgwq_san.so"))
         elif _build.stale():
-            import warnings
-            warnings.warn("libgwq.so is older than its sources: rebuild with __graft_entry__.build()")
+            warnings.warn(f"older than the sources: {', '.join(_build.stale())}; rebuild with __graft_entry__.build()")
         L = ctypes.CDLL(_LIB_PATH)
         vp, i32, u32 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_uint32
         L.gwq_layout.restype = ctypes.c_int
@@ -109,16 +110,21 @@ _plain_call = None
 
 def _plain():
     """call(layer, X, out or None, bf16) of the extension module (csrc/gwq_call.cpp): gwq.linear without the interpreter's
-    share of a call.  Returns the result, (status, None), or None where the call is not the plain case."""
+    share of a call.  Returns the result, (status, None), or None where the call is not the plain case - for every call where
+    the module is missing or reads the objects of another torch or Python."""
     global _plain_call
     if _plain_call is None:
         import torch                                   # its libraries first: the module is linked with them
         L = lib()
         try:
-            from . import _call
+            from . import _call, build as _build
+            if getattr(_call, "built_for", "") != _build.built_for():
+                raise ImportError(f"built for {getattr(_call, 'built_for', '')}, not {_build.built_for()}")
         except ImportError as e:
-            raise RuntimeError("_call.so is not built, or not for this torch: run __graft_entry__.build() (or "
-                               "python -m paper_2411_00850_amd.build) first") from e
+            warnings.warn(f"_call.so is not used ({e}): the plain gwq.linear call goes through ctypes, 3 us of host time more; "
+                          "rebuild with __graft_entry__.build()")
+            _plain_call = lambda *args: None
+            return _plain_call
         address = lambda f: ctypes.cast(f, ctypes.c_void_p).value
         _call.bind(address(L.gwq_linear), address(L.gwq_linear_bf16), address(L.gwq_layout),
                    torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice)

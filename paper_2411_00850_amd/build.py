@@ -1,8 +1,11 @@
 """Build libgwq.so (HIP, gfx950 only) with hipcc and the extension module _call.so (C++) in-tree."""
+import importlib.metadata
 import importlib.util
 import os
 import subprocess
+import sys
 import sysconfig
+import warnings
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -48,14 +51,26 @@ def build(verbose: bool = False, stamps: bool = False, sanitize_host: bool = Fal
     if res.returncode:
         raise RuntimeError("hipcc failed building " + os.path.basename(out))
     if not stamps:
-        build_call(verbose)
+        try:
+            build_call(verbose)
+        except (ImportError, OSError, RuntimeError) as e:
+            warnings.warn(f"_call.so is not built ({e}): the plain gwq.linear call will go through ctypes")
     return out
 
 
+def built_for() -> str:
+    """The Python and the torch whose objects _call.so reads; compiled into it."""
+    return f"torch {importlib.metadata.version('torch')}, Python {sys.version_info[0]}.{sys.version_info[1]}"
+
+
 def build_call(verbose: bool = False) -> str:
-    """Builds _call.so against the headers of the installed torch (host code: no GPU compiler)."""
+    """Builds _call.so against the headers of the installed torch (host code: no GPU compiler).  Where that fails, none is left."""
+    if os.path.exists(CALL):
+        os.remove(CALL)
+    what = built_for()
     torch = os.path.dirname(importlib.util.find_spec("torch").origin)
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", INCLUDE, "-I", os.path.join(torch, "include"),
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f'-DGWQ_BUILT_FOR="{what}"',
+           "-I", INCLUDE, "-I", os.path.join(torch, "include"),
            "-I", os.path.join(torch, "include", "torch", "csrc", "api", "include"), "-I", sysconfig.get_paths()["include"],
            os.path.join(CSRC, "gwq_call.cpp"), "-L", os.path.join(torch, "lib"), "-ltorch_python", "-ltorch_cpu", "-ltorch", "-lc10", "-o", CALL]
     res = subprocess.run(cmd, capture_output=True, text=True)
@@ -66,15 +81,13 @@ def build_call(verbose: bool = False) -> str:
     return CALL
 
 
-def stale() -> bool:
-    """True when a built file is missing or older than one of the sources or the public header."""
-    if not (os.path.exists(LIB) and os.path.exists(CALL)):
-        return True
-    built = min(os.path.getmtime(LIB), os.path.getmtime(CALL))
-    deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC)] + [os.path.join(INCLUDE, "gwq.h")]
-    return any(os.path.getmtime(d) > built for d in deps)
+def stale() -> list:
+    """Names of the built files that are older than one of their sources or the public header."""
+    call = ["gwq_call.cpp"]
+    sources = {LIB: [f for f in os.listdir(CSRC) if f not in call], CALL: call}
+    return [os.path.basename(built) for built, names in sources.items() if os.path.exists(built) and
+            any(os.path.getmtime(d) > os.path.getmtime(built) for d in [os.path.join(CSRC, f) for f in names] + [os.path.join(INCLUDE, "gwq.h")])]
 
 
 if __name__ == "__main__":
-    import sys
     print(build(verbose=True, stamps="--stamps" in sys.argv, sanitize_host="--sanitize-host" in sys.argv))

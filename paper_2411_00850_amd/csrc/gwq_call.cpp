@@ -144,5 +144,7 @@ PyMODINIT_FUNC PyInit__call()
         if (!(g_scalar_names[i] = PyUnicode_InternFromString(scalars[i]))) return nullptr;
     for (int i = 0; i < 7; ++i)
         if (!(g_tensor_names[i] = PyUnicode_InternFromString(tensors[i]))) return nullptr;
-    return PyModule_Create(&g_module);
+    PyObject *m = PyModule_Create(&g_module);
+    if (m && PyModule_AddStringConstant(m, "built_for", GWQ_BUILT_FOR) < 0) Py_CLEAR(m);
+    return m;
 }
