@@ -82,6 +82,37 @@ def test_one_launch_where_it_is_the_faster_way(N, K, M, bits, one_launch):
     assert error < 5e-4 and (error < 2.0 ** -11 / 3 ** 0.5) == one_launch, error
 
 
+@pytest.mark.parametrize("N,K,M,group,one_launch", [
+    (16384, 1152, 2, 32, True), (16400, 1152, 2, 32, False), (16400, 1152, 6, 32, False), (16400, 1664, 2, 64, True),
+    (2048, 2176, 3, 16, True), (4096, 2176, 3, 16, True), (4112, 2176, 3, 16, False), (12288, 2176, 1, 32, True), (14352, 2176, 1, 32, False),
+    (2048, 3200, 4, 32, False), (2064, 3200, 4, 32, True), (2064, 4224, 3, 64, True), (6176, 4224, 3, 64, False),
+    (5000, 2176, 7, 64, True), (2048, 3200, 5, 64, False), (2064, 3200, 5, 64, True),
+    (2048, 4224, 5, 64, False), (2064, 4224, 5, 64, True), (4112, 4224, 5, 64, False)])
+def test_small_groups_one_launch_where_it_is_the_faster_way(N, K, M, group, one_launch):
+    """Both sides of launch_decode's rules for groups below 128.  One launch rounds H alone, two products round G and U to FP16
+    first: H is nearer to the fp64 products so rounded, and one launch is the more exact."""
+    import types
+    import torch
+    import paper_2411_00850_amd as gwq
+    from gpu_helpers import download_packed, to_gpu
+    bits = 3 + K // 128 % 2
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(N + K)
+    rng = np.random.default_rng(N + K)
+    X = gs.activations(M, K, rng)
+    D, products = [], []
+    for _ in range(2):                                  # packed on the GPU: byte for byte as the oracle packs
+        W = torch.randn((N, K), generator=gen, device="cuda").mul_(0.02).half()
+        D.append(gwq.pack(W, torch.rand((N, K), generator=gen, device="cuda"), bits, 10000, group=group))
+        P = types.SimpleNamespace(N=N, K=K, bits=bits, group=group, **download_packed(D[-1]))
+        products.append(orc.linear_f64(P, X))
+    H = gwq.linear_gate_up(*D, to_gpu(X)).cpu().numpy().astype(np.float64)
+    exact = orc.gate_up(*products)
+    twice = orc.gate_up(*(y.astype(np.float16) for y in products)).astype(np.float16)
+    off = [np.linalg.norm(H - ref) / np.linalg.norm(exact) for ref in (exact.astype(np.float16), twice, exact)]
+    assert (off[0] < off[1]) == one_launch and off[2] < 5e-4, off
+
+
 @pytest.mark.parametrize("bits", [4, 3])
 @pytest.mark.parametrize("group", [16, 32, 64])
 @pytest.mark.parametrize("N,K", [(50, 1152), (130, 4096), (20, 128)])
@@ -93,9 +124,10 @@ def test_small_groups(bits, group, N, K):
 
 @pytest.mark.parametrize("bits", [4, 3])
 @pytest.mark.parametrize("group", [16, 64, 128])
-@pytest.mark.parametrize("N,K", [(16, 128), (50, 1152), (333, 2048), (77, 2432), (2070, 4096), (2100, 4992), (4200, 2176)])
+@pytest.mark.parametrize("N,K", [(16, 128), (50, 1152), (333, 2048), (77, 2432), (2070, 4096), (2100, 4992), (4200, 2176),
+                                 (50, 6272), (77, 8192)])
 def test_two_sets_of_waves(bits, group, N, K):
-    """Up to eight rows with one set of waves for gate and one for up, and the calls beside them: one wave a set to seven, half
+    """Up to eight rows with one set of waves for gate and one for up, and the calls beside them: one wave a set to eight, half
     a block per CU to two, ragged last tiles, both layers' outlier counts, the up layer's beyond a set's staged window (6 %)."""
     layers, rng = _pair(group + N + K + bits, N, K, bits, group, ppm=(10000, 60000 if N < 100 else 10000))
     for M in (1, 2, 3, 4, 5, 6, 7, 8) if N * K < 1000000 else (1, 4, 5, 8)[bits - 3::2]:

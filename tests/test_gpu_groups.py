@@ -201,8 +201,7 @@ def test_small_groups_extreme_scales(bits):
 
 @pytest.mark.parametrize("M", [1, 8])
 def test_grouped_launch_and_gate_up_with_small_groups(M):
-    """gwq_linear_batch over layers of one group size, and the gated pair (two products and the elementwise
-    kernel: the fused decode launch is for groups of 128)."""
+    """gwq_linear_batch over layers of one group size, and the gated pair."""
     import paper_2411_00850_amd as gwq
     from gpu_helpers import to_gpu, upload_packed
     N, K = 176, 512

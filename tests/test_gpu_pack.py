@@ -341,9 +341,10 @@ def test_pack_where_rows_stop_being_shared(N, f16):
     assert_packed_equal(gwq.pack(to_gpu(W), to_gpu(S), 4, 30000), orc.pack(W, S, 4, 30000))
 
 
-@pytest.mark.parametrize("N", [4095, 4096, 4097, 8193])
+@pytest.mark.parametrize("N", [4095, 4096, 4097, 8193, 65536 + 4095, 65536 + 4096, 65536 + 4097])
 def test_pack_row_scan_rounds(N):
-    """The scan over the rows at the ends of its rounds of 4096 rows, ties at the threshold taken across them."""
+    """Row starts around multiples of 4096 rows, ties at the threshold taken across them: summed up by the encoder, and beyond
+    65536 rows by the scan at the ends of its rounds of 4096 rows."""
     import paper_2411_00850_amd as gwq
     from gpu_helpers import assert_packed_equal, to_gpu
     rng = np.random.default_rng(N)

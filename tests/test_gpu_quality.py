@@ -57,6 +57,25 @@ def test_quality_fp16_scores_signed_scores_and_foreign_outlier_values(bits):
     assert got[2] > 0
 
 
+@pytest.mark.parametrize("bits,group", [(4, 128), (3, 16)])
+@pytest.mark.parametrize("f16", [False, True])
+@pytest.mark.parametrize("K", [2048, 2176, 4096])
+@pytest.mark.parametrize("rows", ["all", "few"])
+def test_quality_one_and_four_waves_a_channel(K, f16, bits, group, rows):
+    """The longest channel of a wave, the shortest of four and one with two trips a wave, four channels to a block with a ragged
+    last one, per type of score; outliers all over, and all of them in two channels (more than any pass over them takes at once)."""
+    rng = np.random.default_rng(K + bits)
+    N = 37
+    W = gs.weight(N, K, rng, planted_cols=2)
+    S = gs.score_from_weight(W, rng)
+    if rows == "few":
+        S[[5, 36]] += 2 * S.max()
+    S = S.astype(np.float16 if f16 else np.float32)
+    P = orc.pack(W, S, bits, 30000, group)
+    assert rows == "all" or P.row_ptr[37] - P.row_ptr[36] > 256
+    _check(P, W, S, f"K={K} f16={f16} bits={bits} group={group} outliers in {rows} channels")
+
+
 @pytest.mark.parametrize("bits", [4, 3])
 def test_quality_is_deterministic_and_takes_gpu_packed_layers(bits):
     import paper_2411_00850_amd as gwq
