@@ -11,8 +11,9 @@
 // a fixed order: lanes over their strided columns, a shuffle tree, the channel's waves in order, and a
 // second kernel over the channels; no floating-point atomics, results identical from run to run.
 // Bound by HBM: W (2 bytes), the score (4 or 2) and the packed layer (about 0.5) per weight, read once: 295 MB of
-// 11008 x 4096 with FP32 scores at 5.4 TB/s.  (A block of four waves for every channel and a branch per kept weight: 8192 x
-// 1024 27.2 us, now 19.5; 11008 x 2048 43, now 34; 11008 x 4096 at 3 bits, groups of 16 69, now 67.)
+// 11008 x 4096 with FP32 scores in 55.3 us a call, the second kernel included, 5.3 TB/s.  (Four waves for every channel: 8192 x
+// 1024 24.5 us, now 18.1.  A kept weight is skipped by a branch: counted as 0 by masks, three selects more for every
+// weight, 11008 x 4096 takes 60.8, with FP16 scores 57.0 where it is 49.0, at 3 bits 68.2 where it is 61.)
 #include "gwq_internal.h"
 
 namespace gwq {
@@ -146,14 +147,13 @@ __global__ __launch_bounds__(kQThreads) void quality_kernel(const uint32_t *__re
         const uint32_t kept8 = kept[k0 >> 5] >> (k0 & 31);
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            // A kept weight counts as 0 in all three, without a branch (a branch each made up half of the kernel).
-            const bool out = kept8 >> i & 1;
+            if (kept8 >> i & 1) continue;
             const float w = (float)__builtin_bit_cast(_Float16, (uint16_t)(w2[i >> 1] >> (16 * (i & 1))));
             const float g = F16 ? (float)__builtin_bit_cast(_Float16, (uint16_t)(g4[i >> 1] >> (16 * (i & 1)))) : __builtin_bit_cast(float, g4[i]);
             const int q = code_of<BITS>(c.code[0], c.code[BITS == 4 ? 0 : 1], c.code[BITS == 4 ? 0 : 2], c.code[BITS == 4 ? 0 : 3], slot, c0, i) - z;
-            const double d = (double)(out ? 0.f : w) - s * (double)(out ? 0 : q);
+            const double d = (double)w - s * (double)q;
             m.sq += d * d;
-            m.first += (double)(out ? 0.f : g) * d;
+            m.first += (double)g * d;
             m.mx = m.mx > fabs(d) ? m.mx : fabs(d);
         }
     };
@@ -232,9 +232,10 @@ hipError_t launch_quality(const gwq_packed &P, const void *W, const void *score,
 {
     Merit *partial = static_cast<Merit *>(workspace);
     const _Float16 *w = static_cast<const _Float16 *>(W);
-    // Short channels: one wave each, which nobody waits for (us of the call, one wave against four: 8192 x 1024 19.5 and 27.2;
-    // 11008 x 2048 34 and 43).  Long ones: four, which share the outliers of a channel that has many (4096 x 4096, FP16 scores,
-    // outliers in 2 % of the channels: 38.5 and 27; outliers all over 25 and 26; 4096 x 11008, FP32 62.5 and 58.5).
+    // Short channels: one wave each, which nobody waits for; long ones: four, which share the outliers of a channel that has many.
+    // us of the call, one wave / four, outliers all over and, in brackets, all in 2 % of the channels; FP32 scores: 8192 x 1024 18.1 / 24.5
+    // (20.7 / 23.3), 11008 x 2048 33.7 / 42.1 (42.4 / 41.1), 8192 x 2176 29.1 / 34.2 (39.1 / 34.7), 4096 x 4096 27.3 / 26.0 (46.5 / 28.0),
+    // 4096 x 11008 66.3 / 59.2 (129.6 / 70.1).
     const int parts = P.K <= 2048 ? 1 : kQThreads / 64;
     const int blocks = parts == 1 ? (P.N + kQThreads / 64 - 1) / (kQThreads / 64) : P.N;
     const size_t lds = (size_t)(parts == 1 ? kQThreads / 64 : 1) * (P.K / 8);
