@@ -158,7 +158,8 @@ def tuning_set(key, value):
 
 def prepare_linear_gate_up(Pg, Pu, X, out):
     """Pre-marshalled gwq_linear_gate_up call: out = silu(X Wg^T) * (X Wu^T) (FP16 [M, N]); returns a zero-argument
-    callable that enqueues it on the current torch stream.  The workspace (needed beyond M = 4) is allocated here."""
+    callable that enqueues it on the current torch stream.  The workspace is allocated here: the call asks for one beyond four
+    rows or 16384 columns and for groups below 128, whether or not the kernel that it takes writes to it."""
     import torch
     assert X.is_cuda and X.dtype == torch.float16 and X.is_contiguous() and X.shape[1] == Pg.K == Pu.K
     M = X.shape[0]

@@ -18,8 +18,8 @@
 // 128 rows or less; hence eight producers where the registers allow them (28672 x 8192, M = 64: 83 us with four, 61 with eight;
 // M = 301, tiles of 160: 191 and 166).  With the producers' loop unrolled over a window of eight groups, so that nothing but
 // vector instructions is left of the bookkeeping and no wait drains the loads in flight: M = 64 60 -> 56 us, M = 2048 799 -> 765
-// (1.27 PFLOP/s), 11008 x 4096 172 -> 166.  With 256 rows it is power that bounds it: on zeros for X and the weights the same
-// instructions take 552 us of the 752 that they take on normal numbers (28672 x 8192, M = 2048).
+// (1.26 PFLOP/s), 11008 x 4096 172 -> 166.  With 256 rows it is power that bounds it: on another machine the same instructions took
+// 752 us on normal numbers and 552 on zeros for X and the weights (28672 x 8192, M = 2048).
 #include <stdio.h>
 
 #include <type_traits>

@@ -620,9 +620,9 @@ __global__ __launch_bounds__(kScanThreads) void row_scan_kernel(uint32_t *ws, in
 //
 // One wave walks a row (or, where there are few rows, one of four consecutive parts of it) in flat-index order, 512
 // weights per trip, eight per lane: it marks the kept entries, appends them to the CSR arrays, and quantises and packs the
-// rest.  The trips need no barrier and no LDS: positions come from the compare masks (mbcnt), a group's 2 to 16 lanes meet
-// by DPP, the 3-bit words are put together across a quad of lanes.  (The four waves of a shared row exchange once, before
-// their trips, what each part keeps.)  The next trip's weights and scores are requested before this trip's are worked on.
+// rest.  The trips need no barrier and no LDS: positions are a sum over the lanes by DPP (compare masks only rank ties), a
+// group's 2 to 16 lanes meet by DPP, the 3-bit words are put together across a quad of lanes.  (The four waves of a shared row exchange
+// once, before their trips, what each part keeps.)  Two trips' weights and scores are on their way while one is worked on.
 //
 // Bound by HBM (6.56 bytes per weight at FP32 scores), which needs the instruction stream short: about 180 vector
 // instructions per trip and wave.  A kept weight is replaced by 0: a group's range always contains 0 and 0 gets the code
